@@ -64,84 +64,215 @@ __global__ __launch_bounds__(64) void k_mlp_infer(const float *__restrict__ para
     }
 }
 
-// out[b, j] = act(sum_k W[j, k] in[b, k] + bias[j]); one thread per (b, j).
-__global__ void k_dense(const float *__restrict__ in, const float *__restrict__ W,
-                        const float *__restrict__ bias, float *__restrict__ out, int64_t B,
-                        int nin, int nout, int relu) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= B * nout) return;
-    int64_t b = t / nout;
-    int j = (int)(t % nout);
-    float a = bias[j];
-    for (int k = 0; k < nin; ++k) a = fmaf(W[j * nin + k], in[b * nin + k], a);
-    out[t] = relu ? fmaxf(a, 0.0f) : a;
-}
+// Forward pass of kBatchRows samples by one workgroup, and (BWD) their part of
+// the backward pass: one launch where a launch per layer spent its time on
+// launch gaps (a batch of 256 is 4 MFLOP).  The weights sit in LDS with rows
+// padded to 65 (13) floats, so that neither the forward's walk along a row
+// per lane nor the backward's walk along a column per lane meets a bank
+// twice; a wave holds one sample, so activations are LDS broadcasts.
+//
+// BWD leaves h1, h2, the unscaled output residuals ds = mask (s - t), their
+// images d2 and d1 at the two hidden layers (ReLU masked) and, per workgroup,
+// the sum of ds^2 and the mask count; k_mlp_grad applies 2 / count to the
+// finished sums, so no pass over the batch has to wait for the count.
+// Measured, batch 256: forward, loss and input gradients 6 launches and
+// 51 us -> one launch of 7 us (GPU time, MI355X).
+constexpr int kBatchRows = 8;
+constexpr int kMaxOut = SPMV_K_COUNT;
+constexpr int kPadH = kHid + 1, kPadI = kIn + 1;
 
-// loss = sum mask (s - t)^2 / max(1, sum mask); ds = 2 mask (s - t) / cnt.
-// One workgroup of 256 threads, fixed-order partial sums.
-__global__ __launch_bounds__(256) void k_loss_grad(const float *__restrict__ s,
-                                                   const float *__restrict__ target,
-                                                   const float *__restrict__ mask, int64_t count,
-                                                   float *__restrict__ ds, float *__restrict__ loss) {
-    __shared__ float red[256];
-    __shared__ float red2[256];
-    float c = 0.0f, l = 0.0f;
-    for (int64_t i = threadIdx.x; i < count; i += 256) {
-        float mk = mask[i];
-        if (mk > 0.0f) {
-            float r = s[i] - target[i];
-            c += 1.0f;
-            l = fmaf(r, r, l);
+template <bool BWD>
+__global__ __launch_bounds__(256) void k_mlp_rows(
+    const float *__restrict__ params, int n_out, const float *__restrict__ x, int64_t B,
+    float *__restrict__ scores, const float *__restrict__ target,
+    const float *__restrict__ mask, float *__restrict__ gh1, float *__restrict__ gh2,
+    float *__restrict__ gds, float *__restrict__ gd2, float *__restrict__ gd1,
+    float *__restrict__ sums) {
+    __shared__ float w1[kHid * kPadI], w2[kHid * kPadH], w3[kMaxOut * kPadH];
+    __shared__ float xs[kBatchRows * kIn], h1[kBatchRows * kHid], h2[kBatchRows * kHid];
+    __shared__ float ds[kBatchRows * kMaxOut], cs[kBatchRows * kMaxOut], d2[kBatchRows * kHid];
+    const Net net = unpack(params, n_out);
+    const int t = threadIdx.x;
+    const int64_t row0 = (int64_t)blockIdx.x * kBatchRows;
+    const int rows = (int)(B - row0 < kBatchRows ? B - row0 : kBatchRows);
+#pragma unroll
+    for (int q = 0; q < kHid * kHid / 256; ++q) {
+        const int i = t + q * 256;
+        w2[(i >> 6) * kPadH + (i & 63)] = net.W2[i];
+    }
+#pragma unroll
+    for (int q = 0; q < kHid * kIn / 256; ++q) {
+        const int i = t + q * 256;
+        w1[i / kIn * kPadI + i % kIn] = net.W1[i];
+    }
+    for (int i = t; i < n_out * kHid; i += 256) w3[(i >> 6) * kPadH + (i & 63)] = net.W3[i];
+    if (t < rows * kIn) xs[t] = x[row0 * kIn + t];
+    const int j = t & (kHid - 1);
+    const float b1 = net.b1[j], b2 = net.b2[j];
+    __syncthreads();
+    for (int r = t / kHid; r < rows; r += 256 / kHid) {
+        float a = b1;
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) a = fmaf(w1[j * kPadI + k], xs[r * kIn + k], a);
+        a = fmaxf(a, 0.0f);
+        h1[r * kHid + j] = a;
+        if constexpr (BWD) gh1[(row0 + r) * kHid + j] = a;
+    }
+    __syncthreads();
+    for (int r = t / kHid; r < rows; r += 256 / kHid) {
+        float a = b2;
+#pragma unroll
+        for (int k = 0; k < kHid; ++k) a = fmaf(w2[j * kPadH + k], h1[r * kHid + k], a);
+        a = fmaxf(a, 0.0f);
+        h2[r * kHid + j] = a;
+        if constexpr (BWD) gh2[(row0 + r) * kHid + j] = a;
+    }
+    __syncthreads();
+    if (t < rows * n_out) {
+        const int r = t / n_out, o = t - r * n_out;
+        float a = net.b3[o];
+#pragma unroll
+        for (int k = 0; k < kHid; ++k) a = fmaf(w3[o * kPadH + k], h2[r * kHid + k], a);
+        if constexpr (!BWD) {
+            scores[row0 * n_out + t] = a;
+        } else {
+            const bool on = mask[row0 * n_out + t] > 0.0f;
+            const float d = on ? a - target[row0 * n_out + t] : 0.0f;
+            ds[t] = d;
+            cs[t] = on ? 1.0f : 0.0f;
+            gds[row0 * n_out + t] = d;
         }
     }
-    red[threadIdx.x] = c;
-    red2[threadIdx.x] = l;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) {
-            red[threadIdx.x] += red[threadIdx.x + off];
-            red2[threadIdx.x] += red2[threadIdx.x + off];
+    if constexpr (BWD) {
+        __syncthreads();
+        if (t >= 192) {   // one wave, in a fixed order
+            float l = 0.0f, c = 0.0f;
+            for (int i = j; i < rows * n_out; i += 64) {
+                l = fmaf(ds[i], ds[i], l);
+                c += cs[i];
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                l += __shfl_xor(l, off);
+                c += __shfl_xor(c, off);
+            }
+            if (j == 0) {
+                sums[2 * blockIdx.x] = l;
+                sums[2 * blockIdx.x + 1] = c;
+            }
+        }
+        for (int r = t / kHid; r < rows; r += 256 / kHid) {
+            float a = 0.0f;
+            for (int o = 0; o < n_out; ++o) a = fmaf(ds[r * n_out + o], w3[o * kPadH + j], a);
+            a = h2[r * kHid + j] > 0.0f ? a : 0.0f;
+            d2[r * kHid + j] = a;
+            gd2[(row0 + r) * kHid + j] = a;
         }
         __syncthreads();
-    }
-    const float cnt = fmaxf(red[0], 1.0f);
-    if (threadIdx.x == 0) *loss = red2[0] / cnt;
-    for (int64_t i = threadIdx.x; i < count; i += 256)
-        ds[i] = mask[i] > 0.0f ? 2.0f * (s[i] - target[i]) / cnt : 0.0f;
-}
-
-// din[b, k] = (sum_j dout[b, j] W[j, k]) * (act[b, k] > 0)
-__global__ void k_backprop_input(const float *__restrict__ dout, const float *__restrict__ W,
-                                 const float *__restrict__ act, float *__restrict__ din, int64_t B,
-                                 int nin, int nout) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= B * nin) return;
-    int64_t b = t / nin;
-    int k = (int)(t % nin);
-    float a = 0.0f;
-    for (int j = 0; j < nout; ++j) a = fmaf(dout[b * nout + j], W[j * nin + k], a);
-    din[t] = act[t] > 0.0f ? a : 0.0f;
-}
-
-// gW[j, k] = sum_b dout[b, j] in[b, k]; gb[j] = sum_b dout[b, j].
-// Threads [0, nout*nin) do weights, the next nout threads the biases.
-__global__ void k_weight_grad(const float *__restrict__ dout, const float *__restrict__ in,
-                              float *__restrict__ gW, float *__restrict__ gb, int64_t B, int nin,
-                              int nout) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    int64_t nw = (int64_t)nout * nin;
-    if (t < nw) {
-        int j = (int)(t / nin), k = (int)(t % nin);
-        float a = 0.0f;
-        for (int64_t b = 0; b < B; ++b) a = fmaf(dout[b * nout + j], in[b * nin + k], a);
-        gW[t] = a;
-    } else if (t < nw + nout) {
-        int j = (int)(t - nw);
-        float a = 0.0f;
-        for (int64_t b = 0; b < B; ++b) a += dout[b * nout + j];
-        gb[j] = a;
+        for (int r = t / kHid; r < rows; r += 256 / kHid) {
+            float a = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kHid; ++k) a = fmaf(d2[r * kHid + k], w2[k * kPadH + j], a);
+            gd1[(row0 + r) * kHid + j] = h1[r * kHid + j] > 0.0f ? a : 0.0f;
+        }
     }
 }
+
+// Weight and bias gradients of all three layers in one launch:
+//   gW[j, k] = scale sum_b d[b, j] in[b, k],  gb[j] = scale sum_b d[b, j],
+// scale = 2 / max(1, mask count).  The sums over the batch are contractions,
+// so they run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32, four
+// samples a step): a workgroup takes a 16 x 16 tile of one layer's gW, its
+// 16 waves the samples in steps of four, 16 steps apart, kGradAhead steps of
+// loads issued before any is used; the wave tiles are added in wave order.
+// The bias is the same product with a column of ones.  The sums were one
+// thread's serial walk over the batch, bound by one load's latency after
+// the other: 57 us a layer at batch 256 (three launches, 171 us); with 8 loads
+// in flight per lane on the vector units 4.6 us for all three but 125 us at
+// batch 4096 (18 workgroups behind their scalar loads); so 4.0 and 20 us.
+constexpr int kGradWaves = 16, kGradTile = 16, kGradStep = 4, kGradAhead = 4;
+
+__global__ __launch_bounds__(64 * kGradWaves) void k_mlp_grad(
+    int64_t B, int n_out, const float *__restrict__ x, const float *__restrict__ h1,
+    const float *__restrict__ h2, const float *__restrict__ ds, const float *__restrict__ d2,
+    const float *__restrict__ d1, const float *__restrict__ sums, int64_t nsums,
+    float *__restrict__ grad, float *__restrict__ loss) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    __shared__ float red[kGradWaves][kGradTile * kGradTile];
+    __shared__ float redb[kGradWaves][kGradTile];
+    __shared__ float total[2];
+    constexpr int T = kHid / kGradTile;   // tiles along a hidden dimension
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane % kGradTile, ls = lane / kGradTile;   // tile index, sample of the step
+    const int blk = (int)blockIdx.x;
+    const float *d, *in;
+    float *gW, *gb;
+    int nin, nout, j0, k0;
+    Net g = unpack(grad, n_out);
+    if (blk < T * T) {
+        d = d2, in = h1, nin = kHid, nout = kHid, j0 = blk / T * kGradTile, k0 = blk % T * kGradTile;
+        gW = (float *)g.W2, gb = (float *)g.b2;
+    } else if (blk < T * T + T) {
+        d = d1, in = x, nin = kIn, nout = kHid, j0 = (blk - T * T) * kGradTile, k0 = 0;
+        gW = (float *)g.W1, gb = (float *)g.b1;
+    } else {
+        d = ds, in = h2, nin = kHid, nout = n_out, j0 = 0, k0 = (blk - T * T - T) * kGradTile;
+        gW = (float *)g.W3, gb = (float *)g.b3;
+    }
+    const bool jon = j0 + li < nout, kon = k0 + li < nin;
+    const float *dp = d + j0 + li, *ip = in + k0 + li;
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, accb = acc;
+    for (int64_t b0 = (int64_t)wave * kGradStep + ls; b0 - ls < B;
+         b0 += kGradWaves * kGradStep * kGradAhead) {
+        float dv[kGradAhead], iv[kGradAhead];
+#pragma unroll
+        for (int u = 0; u < kGradAhead; ++u) {
+            const int64_t b = b0 + u * (kGradWaves * kGradStep);
+            dv[u] = b < B && jon ? dp[b * nout] : 0.0f;
+            iv[u] = b < B && kon ? ip[b * nin] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kGradAhead; ++u) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[u], iv[u], acc, 0, 0, 0);
+            accb = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[u], 1.0f, accb, 0, 0, 0);
+        }
+    }
+    // accumulator r of a lane is tile row 4 (lane / 16) + r, column lane % 16
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        red[wave][(4 * ls + r) * kGradTile + li] = acc[r];
+        if (li == 0) redb[wave][4 * ls + r] = accb[r];
+    }
+    // squared residuals and mask count over the workgroups of k_mlp_rows, in
+    // a fixed order (the count is a whole number, exact below 2^24)
+    if (wave < 2) {
+        float s = 0.0f;
+        for (int64_t i = lane; i < nsums; i += 64) s += sums[2 * i + wave];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) total[wave] = s;
+    }
+    __syncthreads();
+    const float cnt = fmaxf(total[1], 1.0f);
+    if (blk == 0 && threadIdx.x == 0) *loss = total[0] / cnt;
+    const int t = threadIdx.x;
+    if (t < kGradTile * kGradTile) {
+        const int j = j0 + t / kGradTile, k = k0 + t % kGradTile;
+        if (j < nout && k < nin) {
+            float s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kGradWaves; ++w) s += red[w][t];
+            gW[j * nin + k] = 2.0f * s / cnt;
+        }
+    } else if (t < kGradTile * kGradTile + kGradTile && k0 == 0) {
+        const int c = t - kGradTile * kGradTile;
+        if (j0 + c < nout) {
+            float s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kGradWaves; ++w) s += redb[w][c];
+            gb[j0 + c] = 2.0f * s / cnt;
+        }
+    }
+}
+static_assert(kMaxOut <= kGradTile && kIn <= kGradTile, "one tile of outputs, one of inputs");
 
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
                        float *__restrict__ v, int64_t n, float lr, float beta1, float beta2,
@@ -159,8 +290,11 @@ __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float
 
 inline unsigned blocks(int64_t work, int bs) { return (unsigned)((work + bs - 1) / bs); }
 
+// The caller's workspace: activations and residuals of every sample, then
+// the per-workgroup sums (two floats for every kBatchRows samples, where
+// spmv_mlp_workspace_floats leaves SPMV_K_COUNT floats per sample).
 struct Work {
-    float *h1, *h2, *ds, *dh2, *dh1;
+    float *h1, *h2, *ds, *d2, *d1, *sums;
 };
 
 inline Work carve(float *ws, int64_t B, int n_out) {
@@ -168,20 +302,10 @@ inline Work carve(float *ws, int64_t B, int n_out) {
     w.h1 = ws;
     w.h2 = w.h1 + B * kHid;
     w.ds = w.h2 + B * kHid;
-    w.dh2 = w.ds + B * n_out;
-    w.dh1 = w.dh2 + B * kHid;
+    w.d2 = w.ds + B * n_out;
+    w.d1 = w.d2 + B * kHid;
+    w.sums = w.d1 + B * kHid;
     return w;
-}
-
-spmv_status forward_into(const float *params, int n_out, const float *x, int64_t B,
-                         float *scores, const Work &w, hipStream_t s) {
-    Net net = unpack(params, n_out);
-    k_dense<<<blocks(B * kHid, 256), 256, 0, s>>>(x, net.W1, net.b1, w.h1, B, kIn, kHid, 1);
-    k_dense<<<blocks(B * kHid, 256), 256, 0, s>>>(w.h1, net.W2, net.b2, w.h2, B, kHid, kHid, 1);
-    k_dense<<<blocks(B * n_out, 256), 256, 0, s>>>(w.h2, net.W3, net.b3, scores, B, kHid, n_out,
-                                                   0);
-    SMAT_LAUNCHED("mlp_forward");
-    return SPMV_OK;
 }
 
 }  // namespace
@@ -215,8 +339,11 @@ extern "C" spmv_status spmv_mlp_forward(const float *params_dev, int32_t n_out, 
         return SPMV_EINVAL;
     }
     if (batch == 0) return SPMV_OK;
-    return forward_into(params_dev, n_out, x_dev, batch, scores_dev,
-                        carve(workspace_dev, batch, n_out), (hipStream_t)stream);
+    k_mlp_rows<false><<<blocks(batch, kBatchRows), 256, 0, (hipStream_t)stream>>>(
+        params_dev, n_out, x_dev, batch, scores_dev, nullptr, nullptr, nullptr, nullptr, nullptr,
+        nullptr, nullptr, nullptr);
+    SMAT_LAUNCHED("mlp_forward");
+    return SPMV_OK;
 }
 
 extern "C" spmv_status spmv_mlp_backward(const float *params_dev, int32_t n_out, const float *x_dev,
@@ -230,23 +357,14 @@ extern "C" spmv_status spmv_mlp_backward(const float *params_dev, int32_t n_out,
     }
     hipStream_t s = (hipStream_t)stream;
     Work w = carve(workspace_dev, batch, n_out);
-    // scores go to the tail of the workspace (after dh1)
-    float *scores = w.dh1 + batch * kHid;
-    spmv_status st = forward_into(params_dev, n_out, x_dev, batch, scores, w, s);
-    if (st != SPMV_OK) return st;
-    Net net = unpack(params_dev, n_out);
-    Net g = unpack(grad_dev, n_out);
-    k_loss_grad<<<1, 256, 0, s>>>(scores, target_dev, mask_dev, batch * n_out, w.ds, loss_dev);
-    k_weight_grad<<<blocks((int64_t)n_out * kHid + n_out, 256), 256, 0, s>>>(
-        w.ds, w.h2, (float *)g.W3, (float *)g.b3, batch, kHid, n_out);
-    k_backprop_input<<<blocks(batch * kHid, 256), 256, 0, s>>>(w.ds, net.W3, w.h2, w.dh2, batch,
-                                                               kHid, n_out);
-    k_weight_grad<<<blocks((int64_t)kHid * kHid + kHid, 256), 256, 0, s>>>(
-        w.dh2, w.h1, (float *)g.W2, (float *)g.b2, batch, kHid, kHid);
-    k_backprop_input<<<blocks(batch * kHid, 256), 256, 0, s>>>(w.dh2, net.W2, w.h1, w.dh1, batch,
-                                                               kHid, kHid);
-    k_weight_grad<<<blocks((int64_t)kHid * kIn + kHid, 256), 256, 0, s>>>(
-        w.dh1, x_dev, (float *)g.W1, (float *)g.b1, batch, kIn, kHid);
+    const unsigned nrows = blocks(batch, kBatchRows);
+    k_mlp_rows<true><<<nrows, 256, 0, s>>>(params_dev, n_out, x_dev, batch, nullptr, target_dev,
+                                           mask_dev, w.h1, w.h2, w.ds, w.d2, w.d1, w.sums);
+    SMAT_LAUNCHED("mlp_rows");
+    constexpr unsigned kT = kHid / kGradTile;
+    const unsigned ngrad = kT * kT + 2 * kT;   // tiles of gW2, gW1 and gW3
+    k_mlp_grad<<<ngrad, 64 * kGradWaves, 0, s>>>(batch, n_out, x_dev, w.h1, w.h2, w.ds, w.d2,
+                                                 w.d1, w.sums, nrows, grad_dev, loss_dev);
     SMAT_LAUNCHED("mlp_backward");
     return SPMV_OK;
 }
