@@ -118,11 +118,18 @@ typedef struct {
                                    banded matrices, off otherwise)           */
     int32_t panel_kib;          /* CSR_PANEL: most bytes of x per column
                                    panel, in KiB (default 4096)              */
-    int32_t panel_xcd;          /* CSR_PANEL: 1 = all panels in one launch,
+    int32_t panel_xcd;          /* CSR_PANEL: 0 = default: two steps -- x
+                                   expanded panel by panel out of LDS, then
+                                   blocks of rows summed out of LDS -- unless
+                                   panel_kib or panel_direct_max is given or
+                                   the matrix is beyond that form's indices
+                                   (n above about 20 million float32 or 10
+                                   million float64), then as 1;
+                                   1 = all panels in one launch,
                                    eight at a time, one per XCD, each panel
                                    summing into its own partial vector that a
-                                   second kernel adds in panel order
-                                   (default); 2 = one launch per panel, the
+                                   second kernel adds in panel order;
+                                   2 = one launch per panel, the
                                    running sums carried in y               */
     int32_t wide_loads;         /* DIA and ELL: 1 = a lane takes 16 bytes'
                                    worth of consecutive rows (4 in float32,

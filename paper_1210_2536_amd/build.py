@@ -16,7 +16,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsmat_spmv.so")
 ARCH = os.environ.get("SMAT_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["api.hip", "k_features.hip", "k_convert.hip", "k_spmv.hip", "k_mlp.hip", "batch.hip",
+SOURCES = ["api.hip", "k_features.hip", "k_convert.hip", "k_spmv.hip", "k_expand.hip", "k_mlp.hip", "batch.hip",
            "noalloc.hip"]
 
 # Packed-fp32 instructions are disabled for every device compile.
@@ -29,7 +29,7 @@ FLAGS = [
 
 # The sources that decide what the SpMV kernels cost: the kernels, their
 # launch parameters and plan set-up, the formats they read, the interface.
-TIMING_SOURCES = ["csrc/k_spmv.hip", "csrc/spmv_device.hpp", "csrc/api.hip", "csrc/k_convert.hip",
+TIMING_SOURCES = ["csrc/k_spmv.hip", "csrc/k_expand.hip", "csrc/spmv_device.hpp", "csrc/api.hip", "csrc/k_convert.hip",
                   "csrc/internal.hpp", "csrc/plan.hpp", "../include/spmv.h"]
 
 

@@ -380,7 +380,7 @@ spmv_params default_params(int kernel, const spmv_features &F) {
     p.ell_unroll = 4;
     p.stream_nt = 0;  // resolved per kernel by resolve_params
     p.panel_kib = 4096;
-    p.panel_xcd = 1;
+    p.panel_xcd = 0;  // resolved by build_variant: two steps, or 1
     (void)kernel;
     return p;
 }
@@ -815,6 +815,129 @@ spmv_status build_long_tiles(const spmv_plan_s &P, Variant &V, const std::vector
     return SPMV_OK;
 }
 
+// Column panels in two steps (k_expand.hip) when no other form was asked for
+// (panel_xcd, panel_kib or panel_direct_max) and the matrix fits the form's
+// indices: a block of rows never has more pieces than LDS holds (its entries
+// plus one partly filled piece per panel), scanned positions fit 31 bits, and
+// a row of the blocks takes at most a quarter of one.  Beyond those sizes an
+// entry's piece of x would be almost alone in its 16 bytes, and the XCD panels
+// are the better form.
+int64_t expand_panels(int64_t n, int elt) {
+    const int64_t W = expand_width(elt);
+    return (n + W - 1) / W;
+}
+
+// First-step workgroups resident at once (two per compute unit) and pieces
+// per workgroup: about kExpandShare, at least kExpandShareMin (8192 to 65536
+// pieces are within 1% of each other but for n = 8M, where 8192 is 2% slower:
+// 391 panels are copied into LDS more often).
+constexpr int64_t kExpandResident = 512, kExpandShare = 32768, kExpandShareMin = 2048;
+
+// Streams past the caches from this size on (measured: float64 n = 730k, 551
+// MB, 172 -> 141 us; float32 n = 730k, 326 MB, 89 -> 87 us; 60 MB of short rows
+// beside tiles, 47 -> 53 us).
+constexpr uint64_t kExpandNtBytes = uint64_t(128) << 20;
+
+bool expand_fits(const spmv_plan_s &P, const spmv_params &prm, int64_t lmax) {
+    const int G = 16 / P.elt;
+    const int64_t E = expand_block_entries(P.elt), NP = expand_panels(P.n, P.elt);
+    return prm.panel_xcd == 0 && prm.panel_kib == 4096 && prm.panel_direct_max <= 0 && P.m > 0 &&
+           P.n > 0 && P.nnz > 0 && NP <= kExpandMaxPanels && E / G + NP <= expand_max_pieces() &&
+           lmax <= E / 4 && P.nnz + P.m < (1ll << 31) - 2 * E;
+}
+
+// Both steps' arrays from the plan's CSR copy; rows longer than lmax are left
+// to other kernels.
+spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &V, int32_t lmax,
+                         hipStream_t s) {
+    const int elt = P.elt, G = 16 / elt;
+    const int64_t m = P.m, E = expand_block_entries(elt);
+    const int NP = (int)expand_panels(P.n, elt);
+    const int32_t *rp = P.rp.as<int32_t>(), *col = P.col.as<int32_t>();
+    SMAT_TRY(expand_prepare());
+    Dev len, scan, spos, most;
+    SMAT_TRY(len.alloc(sizeof(int32_t) * (size_t)m));
+    SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(m / 4096 + 2)));
+    SMAT_TRY(spos.alloc(sizeof(int32_t) * (size_t)(m + 1)));
+    SMAT_TRY(most.alloc(sizeof(int)));
+    SMAT_TRY(launch_expand_lengths(m, rp, lmax, len.as<int32_t>(), s));
+    SMAT_TRY(launch_exclusive_scan_rows(m, len.as<int32_t>(), spos.as<int32_t>(),
+                                        scan.as<unsigned>(), s));
+    SMAT_HIP(hipMemsetAsync(most.p, 0, sizeof(int), s));
+    int32_t total = 0;
+    SMAT_HIP(hipMemcpyAsync(&total, spos.as<int32_t>() + m, sizeof(int32_t),
+                            hipMemcpyDeviceToHost, s));
+    SMAT_HIP(hipStreamSynchronize(s));
+    // a block takes the rows that start within `step` entries, so that the
+    // last of them still ends inside the block
+    const int64_t longest = std::max<int64_t>(1, std::min<int64_t>(lmax, F.max_rd));
+    const int64_t step = E - longest + 1, nb = (total + step - 1) / step;
+    int lg = 0;   // lanes per row of the two passes over the rows
+    while (lg < 6 && (4 << lg) < F.aver_rd) ++lg;
+    Dev cnt, runs, scan2;
+    SMAT_TRY(V.ex_blocks.alloc(sizeof(ExpandBlock) * (size_t)nb));
+    SMAT_TRY(cnt.alloc(sizeof(int32_t) * (size_t)(NP * nb)));
+    SMAT_TRY(runs.alloc(sizeof(int32_t) * (size_t)(NP * nb + 1)));
+    SMAT_TRY(scan2.alloc(sizeof(unsigned) * (size_t)(NP * nb / 4096 + 2)));
+    SMAT_TRY(launch_expand_count(elt, m, nb, step, NP, lmax, lg, rp, col, spos.as<int32_t>(),
+                                 V.ex_blocks.as<ExpandBlock>(), cnt.as<int32_t>(),
+                                 most.as<int>(), s));
+    SMAT_TRY(launch_exclusive_scan_rows(NP * nb, cnt.as<int32_t>(), runs.as<int32_t>(),
+                                        scan2.as<unsigned>(), s));
+    SMAT_TRY(V.ex_starts.alloc(sizeof(int32_t) * (size_t)(NP + 1)));
+    SMAT_TRY(launch_expand_starts(NP, nb, runs.as<int32_t>(), V.ex_starts.as<int32_t>(), s));
+    std::vector<int32_t> start(NP + 1);
+    int stride = 0;
+    SMAT_HIP(hipMemcpyAsync(start.data(), V.ex_starts.p, sizeof(int32_t) * (NP + 1),
+                            hipMemcpyDeviceToHost, s));
+    SMAT_HIP(hipMemcpyAsync(&stride, most.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    SMAT_HIP(hipStreamSynchronize(s));
+    if (stride > expand_max_pieces()) {
+        set_error("expanded panels: %d pieces in a row block", stride);
+        return SPMV_EUNSUPPORTED;
+    }
+    // the first step's shares: equal runs of pieces over the 512 workgroups the
+    // GPU holds at once, or a multiple of that, across panel boundaries (a
+    // workgroup copies each panel of x it touches into LDS)
+    const int64_t pieces = start[NP];
+    const int64_t rounds = std::max<int64_t>(
+        1, (pieces + kExpandShare * kExpandResident / 2) / (kExpandShare * kExpandResident));
+    const int64_t parts = std::min<int64_t>(rounds * kExpandResident,
+                                            (pieces + kExpandShareMin - 1) / kExpandShareMin);
+    std::vector<ExpandChunk> chunks;
+    for (int64_t q = 0, p = 0; q < parts; ++q) {
+        const int64_t v0 = pieces * q / parts, v1 = pieces * (q + 1) / parts;
+        while (p + 1 < NP && start[p + 1] <= v0) ++p;
+        chunks.push_back({(int32_t)p, (int32_t)v0, (int32_t)v1, 0});
+    }
+    SMAT_TRY(V.ex_chunks.alloc(sizeof(ExpandChunk) * chunks.size()));
+    if (!chunks.empty())
+        SMAT_HIP(hipMemcpyAsync(V.ex_chunks.p, chunks.data(), sizeof(ExpandChunk) * chunks.size(),
+                                hipMemcpyHostToDevice, s));
+    SMAT_TRY(V.ex_off.alloc(sizeof(uint16_t) * (size_t)(pieces * G)));
+    SMAT_TRY(V.ex_xe.alloc((size_t)16 * (size_t)pieces));
+    SMAT_TRY(V.ex_meta.alloc(sizeof(uint32_t) * (size_t)(nb * (E / expand_per(elt)))));
+    SMAT_TRY(V.ex_slot.alloc(sizeof(uint16_t) * (size_t)(nb * E)));
+    SMAT_TRY(V.ex_val.alloc((size_t)elt * (size_t)(nb * E)));
+    SMAT_TRY(V.ex_piece.alloc(sizeof(int32_t) * (size_t)(nb * stride)));
+    SMAT_TRY(V.ex_rp.alloc(sizeof(int32_t) * (size_t)(m + 1)));
+    SMAT_HIP(hipMemcpyAsync(V.ex_rp.p, rp, sizeof(int32_t) * (size_t)(m + 1),
+                            hipMemcpyDeviceToDevice, s));
+    SMAT_TRY(launch_expand_fill(elt, m, nb, NP, lmax, lg, rp, col, P.val.p, spos.as<int32_t>(),
+                                V.ex_blocks.as<ExpandBlock>(), runs.as<int32_t>(), stride,
+                                V.ex_off.as<uint16_t>(), V.ex_meta.as<uint32_t>(),
+                                V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
+                                s));
+    SMAT_HIP(hipStreamSynchronize(s));
+    V.expand = true;
+    V.ex_P = NP;
+    V.ex_stride = stride;
+    V.ex_lmax = lmax;
+    V.ex_nb = nb;
+    V.ex_nchunks = (int64_t)chunks.size();
+    return SPMV_OK;
+}
+
 spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W, int kernel,
                           const spmv_params &prm_in, hipStream_t s, Variant &V) {
     const spmv_params prm = resolve_params(kernel, prm_in, F, P.elt);
@@ -991,6 +1114,12 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         // restored below when they are not used
         const bool try_tiles = prm.long_lds == 0 || prm.long_lds == 3;
         int wg = try_tiles ? std::min(prm.adaptive_wg_min, prm.tile_row_min) : prm.adaptive_wg_min;
+        // panels in two steps: the longest bin (never in row blocks, which are
+        // cut between rows) starts at the tiles' row length at most
+        const int32_t expand_lmax =
+            std::max(std::min(wg, prm.tile_row_min), prm.adaptive_rows_per_lane << 5);
+        const bool expand = panels && expand_fits(P, prm, expand_lmax);
+        if (expand) wg = std::min(wg, prm.tile_row_min);
         SMAT_TRY(bin(wg));
         // split rows: segment table on the host from their row_ptr entries
         int64_t ns = V.bin_off[9] - V.bin_off[8];
@@ -1084,7 +1213,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
                     if (!V.long_tiles) ll = chunks_ok ? 1 : 2;
                 }
             }
-            if (ll != 3 && wg != prm.adaptive_wg_min && n7 > 0) {
+            if (ll != 3 && wg != prm.adaptive_wg_min && n7 > 0 && !expand) {
                 // no tiles: bins with the binned launch's own threshold
                 V.long_rows.release();
                 wg = prm.adaptive_wg_min;
@@ -1150,6 +1279,18 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
                           (long long)kSplitMin);
                 return SPMV_EUNSUPPORTED;
             }
+            if (expand) {
+                V.along = bins_launch(V.bin_off, 7, 7, 0);
+                V.prm.panel_xcd = 0;
+                SMAT_TRY(build_expand(P, F, V, expand_lmax, s));
+                // streams that leave no room in the 256 MB Infinity Cache for
+                // xe between the two steps are read past it
+                if (prm_in.stream_nt == 0)
+                    V.prm.stream_nt = V.ex_val.bytes + V.ex_slot.bytes + V.ex_off.bytes +
+                                              V.ex_xe.bytes > kExpandNtBytes ? 1 : 2;
+                return SPMV_OK;
+            }
+            if (V.prm.panel_xcd == 0) V.prm.panel_xcd = 1;
             const int64_t L = (int64_t)V.P * (m + 1);
             if (L >= (1ll << 31)) {
                 set_error("%d column panels x %lld rows exceed the int32 panel row pointers",
@@ -1235,6 +1376,16 @@ spmv_status run_variant(const spmv_plan_s &P, const Variant &V, const void *x, v
     case SPMV_K_CSR_PANEL: {
         // binned positions [lo, hi) go through the panels: all rows but the
         // short bins (summed directly) and the longest bin (long-row kernel)
+        if (V.expand) {
+            SMAT_TRY(run_expand(elt, nt, V.ex_nchunks, V.ex_chunks.as<ExpandChunk>(),
+                                V.ex_starts.as<int32_t>(), V.ex_off.as<uint16_t>(), x, P.n, V.ex_xe.p, V.ex_nb,
+                                V.ex_blocks.as<ExpandBlock>(), V.ex_meta.as<uint32_t>(),
+                                V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
+                                V.ex_stride, y, s));
+            if (V.long_tpr) return run_long_rows(P, V, x, y, s);
+            return run_csr_adaptive(elt, nt, true, V.along, V.bin_rows.as<int32_t>(),
+                                    P.rp.as<int32_t>(), P.col.as<int32_t>(), P.val.p, x, y, s);
+        }
         const int64_t lo = V.bin_off[V.short_bins];
         const int64_t hi = V.long_tpr ? V.bin_off[7] : m;
         const AdaptiveLaunch &ap =
@@ -1566,7 +1717,9 @@ bool needs_csr(const Variant &V) {
     return k == SPMV_K_CSR_SCALAR || k == SPMV_K_CSR_VECTOR || k == SPMV_K_CSR_ADAPTIVE ||
            k == SPMV_K_COO ||
            // long rows and directly summed short rows read the CSR copy
-           (k == SPMV_K_CSR_PANEL && (V.long_tpr || V.short_bins));
+           // (panels in two steps: all rows of the longest bin)
+           (k == SPMV_K_CSR_PANEL &&
+            (V.long_tpr || V.short_bins || (V.expand && V.along.first[8] > 0)));
 }
 
 }  // namespace
@@ -2341,6 +2494,23 @@ extern "C" spmv_status spmv_convert_roundtrip(spmv_plan_t P, int32_t *rp, int32_
                                     counts.as<int32_t>(), scan.as<unsigned>(), s));
         break;
     case SPMV_K_CSR_PANEL:
+        if (V.expand) {
+            // rows left to other kernels from the CSR copy they read
+            SMAT_HIP(hipMemcpyAsync(rp, V.ex_rp.p, sizeof(int32_t) * (m + 1),
+                                    hipMemcpyDeviceToDevice, s));
+            if (P->has_csr) {
+                SMAT_HIP(hipMemcpyAsync(col, P->col.p, sizeof(int32_t) * nnz,
+                                        hipMemcpyDeviceToDevice, s));
+                SMAT_HIP(hipMemcpyAsync(val, P->val.p, (size_t)elt * nnz,
+                                        hipMemcpyDeviceToDevice, s));
+            }
+            SMAT_TRY(launch_expand_to_csr(elt, V.ex_nb, V.ex_P, V.ex_lmax,
+                                          V.ex_rp.as<int32_t>(), V.ex_starts.as<int32_t>(),
+                                          V.ex_blocks.as<ExpandBlock>(), V.ex_off.as<uint16_t>(),
+                                          V.ex_slot.as<uint16_t>(), V.ex_val.p,
+                                          V.ex_piece.as<int32_t>(), V.ex_stride, col, val, s));
+            break;
+        }
         SMAT_TRY(launch_panels_to_csr(m, V.bin_rows.as<int32_t>(), V.P, V.prow.as<int32_t>(),
                                       V.pcol.as<int32_t>(), V.pval.p, elt, rp, col, val,
                                       counts.as<int32_t>(), scan.as<unsigned>(), s));

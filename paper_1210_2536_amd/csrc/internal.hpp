@@ -217,6 +217,46 @@ spmv_status launch_panels_to_csr(int64_t m, const int32_t *rows, int P, const in
                                  const int32_t *pcol, const void *pval, int elt, int32_t *rp,
                                  int32_t *col, void *val, int32_t *counts, unsigned *scan,
                                  hipStream_t s);
+// Column panels in two steps (k_expand.hip): x expanded panel by panel into
+// xe, then row blocks summed out of LDS.  A piece is 16 bytes of xe.
+struct ExpandChunk { int32_t panel, begin, end, pad; };   // pieces [begin, end), from `panel` on
+struct ExpandBlock { int32_t row0, rows, entries, pieces; };
+int64_t expand_width(int elt);            // columns per panel
+int expand_per(int elt);                  // entries per thread of a row block
+int64_t expand_block_entries(int elt);    // entries per row block, at most
+int expand_max_pieces();                  // pieces per row block, at most
+constexpr int kExpandMaxPanels = 4096;    // panel counters of the plan-time kernels in LDS
+spmv_status expand_prepare();             // LDS limits (before the first launch)
+// Plan time: entries per row (an empty row and a row longer than lmax, which
+// other kernels write, count 1); per row block of `step` scanned entries its
+// rows and pieces per panel (cnt[p nb + b]; scanned: runs, P nb + 1 ints);
+// first piece per panel (P + 1 ints); both steps' arrays; the CSR entries
+// back from them.  2^lg lanes share a row.
+spmv_status launch_expand_lengths(int64_t m, const int32_t *rp, int32_t lmax, int32_t *len,
+                                  hipStream_t s);
+spmv_status launch_expand_count(int elt, int64_t m, int64_t nb, int64_t step, int P, int32_t lmax,
+                                int lg, const int32_t *rp, const int32_t *col,
+                                const int32_t *spos, ExpandBlock *blocks, int32_t *cnt, int *most,
+                                hipStream_t s);
+spmv_status launch_expand_starts(int P, int64_t nb, const int32_t *runs, int32_t *starts,
+                                 hipStream_t s);
+spmv_status launch_expand_fill(int elt, int64_t m, int64_t nb, int P, int32_t lmax, int lg,
+                               const int32_t *rp, const int32_t *col, const void *val,
+                               const int32_t *spos, const ExpandBlock *blocks,
+                               const int32_t *runs, int pieces_stride, uint16_t *off,
+                               uint32_t *meta, uint16_t *slot, void *oval, int32_t *piece,
+                               hipStream_t s);
+spmv_status launch_expand_to_csr(int elt, int64_t nb, int P, int32_t lmax, const int32_t *rp,
+                                 const int32_t *starts, const ExpandBlock *blocks,
+                                 const uint16_t *off, const uint16_t *slot, const void *oval,
+                                 const int32_t *piece, int pieces_stride, int32_t *col, void *val,
+                                 hipStream_t s);
+// Both steps: every row of the blocks but those longer than lmax.
+spmv_status run_expand(int elt, bool nt, int64_t nchunks, const ExpandChunk *chunks,
+                       const int32_t *starts, const uint16_t *off, const void *x, int64_t n, void *xe, int64_t nb,
+                       const ExpandBlock *blocks, const uint32_t *meta, const uint16_t *slot,
+                       const void *val, const int32_t *piece, int pieces_stride, void *y,
+                       hipStream_t s);
 // split rows: segments (row, begin, end) reduce into partials, then fix-up
 spmv_status run_csr_split(int elt, int64_t nseg, const int64_t *segs, double *partials,
                           int64_t nrows, const int64_t *row_seg_begin, const int32_t *rows,

@@ -117,6 +117,13 @@ struct Variant {
     bool long_tiles = false;
     int64_t tile_P = 0, tile_nb = 0;
     Dev tile_seg, tile_blocks, tile_part, tile_off, tile_pk, tile_val;
+    // column panels in two steps: rows of at most ex_lmax entries
+    bool expand = false;
+    int ex_P = 0, ex_stride = 0;
+    int32_t ex_lmax = 0;
+    int64_t ex_nb = 0, ex_nchunks = 0;
+    AdaptiveLaunch along{};   // the longer rows, a workgroup each
+    Dev ex_rp, ex_off, ex_xe, ex_chunks, ex_blocks, ex_meta, ex_slot, ex_val, ex_piece, ex_starts;
     // BCSR 4x4
     Dev brp, bcol, bval, bpres;
     int64_t nblocks = 0;
@@ -128,7 +135,9 @@ struct Variant {
                ppart.bytes + brp.bytes + bcol.bytes + bval.bytes + bpres.bytes + long_rows.bytes +
                tile_seg.bytes + tile_blocks.bytes + tile_part.bytes + tile_off.bytes +
                tile_pk.bytes + tile_val.bytes + binned_rp.bytes + binned_col.bytes +
-               binned_val.bytes;
+               binned_val.bytes + ex_rp.bytes + ex_off.bytes + ex_xe.bytes + ex_chunks.bytes +
+               ex_blocks.bytes + ex_meta.bytes + ex_slot.bytes + ex_val.bytes + ex_piece.bytes +
+               ex_starts.bytes;
     }
 };
 
