@@ -323,8 +323,10 @@ def main():
             return f"k_bcsr<{t}, {p['bcsr_lanes']}, {nt}>"
         if k == "csr_panel":
             if p["panel_xcd"] == 0:   # two steps; rows above the blocks' limit apart
-                alone = "" if long else f" + k_csr_adaptive_rest<{t}, {nt}, false>"
-                return f"k_panel_expand<{t}, {nt}> + k_panel_rows<{t}, {nt}>{long or alone}"
+                # rows by tiles share the two launches
+                rows = (long if p.get("long_lds") != 3 else "") if long else \
+                    f" + k_csr_adaptive_rest<{t}, {nt}, false>"
+                return f"k_panel_expand<{t}> + k_panel_rows<{t}, {nt}>{rows}"
             if p["panel_xcd"] != 2:
                 return f"k_csr_panel_xcd{rest}<{t}, {nt}> + k_panel_reduce{rest}<{t}>{long}"
             return f"k_csr_panel{rest}<{t}, {nt}, false|true>{long}"

@@ -29,8 +29,9 @@ FLAGS = [
 
 # The sources that decide what the SpMV kernels cost: the kernels, their
 # launch parameters and plan set-up, the formats they read, the interface.
-TIMING_SOURCES = ["csrc/k_spmv.hip", "csrc/k_expand.hip", "csrc/spmv_device.hpp", "csrc/api.hip", "csrc/k_convert.hip",
-                  "csrc/internal.hpp", "csrc/plan.hpp", "../include/spmv.h"]
+TIMING_SOURCES = ["csrc/k_spmv.hip", "csrc/k_expand.hip", "csrc/spmv_device.hpp",
+                  "csrc/tiles_device.hpp", "csrc/api.hip", "csrc/k_convert.hip", "csrc/internal.hpp",
+                  "csrc/plan.hpp", "../include/spmv.h"]
 
 
 def _strip_comments(text: str) -> str:

@@ -385,12 +385,23 @@ spmv_params default_params(int kernel, const spmv_features &F) {
     return p;
 }
 
+constexpr int kTileRowMinMax = 4096;   // of the default
 constexpr int kXcds = 8;  // gfx950: eight accelerator complex dies, one L2 each
 // Column panels: rows of at most this many entries are summed without panels
 // by default (-1: none).
 constexpr int kPanelDirectMaxDefault = -1;
-// Long-row tiles take the rows longer than this by default (params.tile_row_min).
-constexpr int kTileRowMin = 1024;
+// Long-row tiles take the rows longer than this by default
+// (params.tile_row_min): a row costs them a partial written and read (16
+// bytes) per panel and 2 + s bytes an entry, against 3 s + 4 an entry in the
+// two-step panels, so the line follows the panel count.  Measured (rows above
+// 256 | 512 | 1024 | 2048 in tiles): 36 panels float32 296 | 294 | 300 | 319
+// us, 69 float64 467 | 470 | 476 | 515, 99 float32 142 | 142 | 146 | 147, 31
+// float64 63 | 66 | 71 | 80, 394 float32 - | - | 568 | 580, 787 float64 - | -
+// | 1007 | 1033 (-: over kTileExtraShare).
+int default_tile_row_min(int64_t n, int elt) {
+    const int64_t W = long_tile_width(elt), NP = (n + W - 1) / W;
+    return std::max(256, std::min(kTileRowMinMax, pow2_ceil(16 * NP / (2 * elt + 2))));
+}
 constexpr int64_t kDiaLdsMax = 64 * 1024;  // dynamic LDS of one DIA workgroup
 
 // Column-panel geometry: width w columns (a multiple of 64) and panel count P.
@@ -430,7 +441,7 @@ spmv_params resolve_params(int kernel, spmv_params p, const spmv_features &F, in
     // slower on smaller matrices)
     if (p.wide_loads == 0) p.wide_loads = F.m >= (1 << 20) ? 1 : 2;
     if (p.panel_direct_max == 0) p.panel_direct_max = kPanelDirectMaxDefault;
-    if (p.tile_row_min == 0) p.tile_row_min = kTileRowMin;
+    if (p.tile_row_min == 0) p.tile_row_min = default_tile_row_min(F.n, elt);
     if (p.bcsr_lanes == 0) {
         const int64_t mb = std::max<int64_t>(1, (F.m + 3) / 4);
         const int64_t avg = (std::max<int64_t>(0, F.blocks4) + mb - 1) / mb;
@@ -540,16 +551,41 @@ int64_t bcsr_f64_depth(int64_t max_rd, int L) {
 constexpr int64_t kCooMaxChunksPerRow = 3000;
 constexpr int64_t kSplitSegment = 512 * 1024;   // entries per split segment (512 threads)
 constexpr int64_t kSplitMin = 256 * 4000;       // longer rows than this are split
-constexpr int64_t kTileRowsDefault = 1024;   // default: tiles from this many such rows
-// Tiles: lanes per row of a row block, the fewest (at least 2^kTileLanesLog2Min)
-// that give about kTileEntriesPerLane entries per lane of the block's mean
-// segment (raised further where the float64 chain bound needs it).
-constexpr int kTileLanesLog2Min = 3;
-// Tiles are built only when their partial sums and segment starts cost at
-// most 1/kTileExtraShare of the long rows' own bytes per run.
+// Default: tiles from this many bytes of values in their rows.  Two launches
+// more than the binned one, which has only its gathers to lose (binned | tiles,
+// float32 then float64; nnz): 1.07M 8.0 | 12.1 us and 8.8 | 10.9, 2.0M 16.0 |
+// 15.6 and 20.9 | 16.9, 2.8M 15.8 | 16.6 and 20.7 | 15.6, 7.7M 35 | 22 and 42 | 28.
+constexpr int64_t kTileBytesDefault = 10 << 20;
+// Tiles are built only when their partial sums cost at most
+// 1/kTileExtraShare of the long rows' own bytes per run.
 constexpr double kTileExtraShare = 5.0;
-constexpr int64_t kTileMinEntries = 16384;   // per tile workgroup, at least
-constexpr double kTileEntriesPerLane = 16.0;
+// Streams of the tiles read past the caches from this size on (the panels of x
+// and the partials stay in them): n = 700k float64, 1.8 GB, 468 -> 405 us; 81
+// MB of a float32 matrix that the Infinity Cache holds between runs, 50 -> 55.
+constexpr uint64_t kTileNtBytes = uint64_t(160) << 20;
+// Tile workgroups resident at once (two per compute unit), what a tile costs
+// besides its entries -- copying an 80 KB panel of x -- in entries, and the
+// fewest entries a tile is cut to.
+constexpr int64_t kTileResident = 512, kTileFixed = 8192, kTileShareMin = 4096;
+
+// Row blocks for `total` entries over NP panels: the fewest rounds of resident
+// workgroups, counting a round as long as its tiles.  A round too many is what
+// costs: n = 310k float32, 1.2e7 long-row entries in 732 tiles 54 us, in 488
+// tiles 46 us.
+int64_t tile_row_blocks(int64_t total, int64_t NP) {
+    double best = 1e300;
+    int64_t nb = 1;
+    for (int64_t k = 1; k * NP <= 16 * kTileResident || k == 1; ++k) {
+        if (k > 1 && total < k * NP * kTileShareMin) break;
+        const double rounds = (double)((k * NP + kTileResident - 1) / kTileResident);
+        const double cost = rounds * ((double)kTileFixed + (double)total / (double)(k * NP));
+        if (cost < best) {
+            best = cost;
+            nb = k;
+        }
+    }
+    return nb;
+}
 
 // Kernels that can hold this matrix (zero-fill rule, storage cap) and, when
 // `accuracy` is set, also keep every float64 summation chain short enough for
@@ -678,12 +714,6 @@ void raw_features(const spmv_features &F, int dtype, float out[12]) {
 
 // ------------------------------------------------------------------ conversion
 
-// Long rows by tiles (x panels of long_tile_width values per workgroup)
-// over the long rows already in V.long_rows, longest first, of lengths len.
-// Row blocks hold about four panels' worth of entries per workgroup (less
-// when the grid would have under 2048 workgroups); a block's lanes per row
-// (8 to 64) give about 16 entries per lane of its mean segment, raised for
-// float64 until its longest segment keeps the chain bound.  Leaves
 // Launch geometry of the length bins blo..bhi of a binned row order (the
 // other bins get no workgroups): bin 7 a workgroup per row, bins 6..0
 // 256 >> max(0, b - shift) rows per workgroup.
@@ -705,121 +735,83 @@ AdaptiveLaunch bins_launch(const unsigned bin_off[kAdaptiveBins + 1], int blo, i
     return a;
 }
 
-// V.long_tiles false (nothing built) when the partials and segment starts
-// would cost over 1/kTileExtraShare of the long rows' own bytes per run, or
-// no lane count keeps the float64 bound.
-spmv_status build_long_tiles(const spmv_plan_s &P, Variant &V, const std::vector<int64_t> &len,
-                             hipStream_t s) {
-    const int64_t n7 = (int64_t)len.size();
+// The long rows' entry count and their scanned lengths (lpos, n7 + 1 ints).
+spmv_status long_row_lengths(const spmv_plan_s &P, int64_t n7, const int32_t *rows, Dev &lpos,
+                             int64_t *total, hipStream_t s) {
+    Dev len, scan;
+    SMAT_TRY(len.alloc(sizeof(int32_t) * (size_t)n7));
+    SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(n7 / 4096 + 2)));
+    SMAT_TRY(lpos.alloc(sizeof(int32_t) * (size_t)(n7 + 1)));
+    SMAT_TRY(launch_binned_scan(n7, rows, P.rp.as<int32_t>(), len.as<int32_t>(),
+                                scan.as<unsigned>(), lpos.as<int32_t>(), s));
+    int32_t t = 0;
+    SMAT_HIP(hipMemcpyAsync(&t, lpos.as<int32_t>() + n7, sizeof(int32_t), hipMemcpyDeviceToHost,
+                            s));
+    SMAT_HIP(hipStreamSynchronize(s));
+    *total = t;
+    return SPMV_OK;
+}
+
+// Long rows by tiles (x panels of long_tile_width values per workgroup) over
+// the n7 rows of V.long_rows holding `total` entries.
+// V.long_tiles stays false (nothing built) when the partials would cost over
+// 1/kTileExtraShare of the long rows' own bytes per run, or the panels are too
+// many for the float64 chain.
+spmv_status build_long_tiles(const spmv_plan_s &P, Variant &V, int64_t n7, const Dev &lpos,
+                             int64_t total, hipStream_t s) {
     const int64_t W = long_tile_width(P.elt);
     const int64_t NP = (P.n + W - 1) / W;
-    if (n7 == 0 || NP < 1 || NP > 65535) return SPMV_OK;
-    int64_t total = 0;
-    for (int64_t l : len) total += l;
-    const double extra = 16.0 * (double)NP * n7 + 8.0 * (double)(NP + 1) * n7;
-    if (extra * kTileExtraShare > (double)total * (P.elt + 4)) return SPMV_OK;
-    const size_t nseg = (size_t)(n7 * (NP + 1));
+    if (n7 == 0 || NP < 1 || NP > kFp64MaxDepth - 64) return SPMV_OK;
+    if (16.0 * (double)NP * n7 * kTileExtraShare > (double)total * (P.elt + 4)) return SPMV_OK;
+    const int32_t *rows = V.long_rows.as<int32_t>();
     SMAT_TRY(long_tiles_prepare());
-    SMAT_TRY(V.tile_seg.alloc(sizeof(int32_t) * nseg));
-    SMAT_TRY(launch_long_tile_seg(n7, NP, W, V.long_rows.as<int32_t>(), P.rp.as<int32_t>(),
-                                  P.col.as<int32_t>(), V.tile_seg.as<int32_t>(), s));
-    std::vector<int32_t> h(nseg);
-    SMAT_HIP(hipMemcpyAsync(h.data(), V.tile_seg.p, sizeof(int32_t) * nseg,
+    const int64_t want = tile_row_blocks(total, NP);
+    const int64_t step = (total + want - 1) / want, nb = (total + step - 1) / step;
+    Dev seg, cnt, scan;
+    SMAT_TRY(seg.alloc(sizeof(int32_t) * (size_t)(n7 * (NP + 1))));
+    SMAT_TRY(cnt.alloc(sizeof(int32_t) * (size_t)(nb * NP)));
+    SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(nb * NP / 4096 + 2)));
+    SMAT_TRY(V.tile_blocks.alloc(sizeof(TileBlock) * (size_t)nb));
+    SMAT_TRY(V.tile_start.alloc(sizeof(int32_t) * (size_t)(nb * NP + 1)));
+    SMAT_TRY(launch_long_tile_seg(n7, NP, W, rows, P.rp.as<int32_t>(), P.col.as<int32_t>(),
+                                  seg.as<int32_t>(), s));
+    SMAT_TRY(launch_tile_blocks(n7, nb, step, lpos.as<int32_t>(), V.tile_blocks.as<TileBlock>(),
+                                s));
+    SMAT_TRY(launch_tile_count(P.elt, n7, nb, NP, V.tile_blocks.as<TileBlock>(),
+                               seg.as<int32_t>(), cnt.as<int32_t>(), s));
+    SMAT_TRY(launch_exclusive_scan_rows(nb * NP, cnt.as<int32_t>(), V.tile_start.as<int32_t>(),
+                                        scan.as<unsigned>(), s));
+    int32_t units = 0;
+    SMAT_HIP(hipMemcpyAsync(&units, V.tile_start.as<int32_t>() + nb * NP, sizeof(int32_t),
                             hipMemcpyDeviceToHost, s));
     SMAT_HIP(hipStreamSynchronize(s));
-    // entries per row block (over all its panels): about four panels' worth,
-    // fewer so that the grid has about 2048 workgroups, but no fewer than
-    // kTileMinEntries per workgroup -- each workgroup reads a whole x panel,
-    // which small blocks would not repay (measured: 5-14% faster than 2048
-    // workgroups on Zipf matrices of 1.1-2.6e7 long-row entries)
-    const int64_t target = std::max<int64_t>(
-        1, std::min<int64_t>(4 * W * NP,
-                             std::max<int64_t>(total * NP / 2048, kTileMinEntries * NP)));
-    std::vector<int32_t> blocks;
-    int max_tpr = 0;
-    for (int64_t r0 = 0; r0 < n7;) {
-        int64_t r1 = r0, acc = 0;
-        while (r1 < n7 && (r1 == r0 || acc < target)) acc += len[r1++];
-        int64_t maxseg = 0;
-        for (int64_t p = 0; p < NP; ++p)
-            for (int64_t r = r0; r < r1; ++r)
-                maxseg = std::max<int64_t>(maxseg, (int64_t)h[(p + 1) * n7 + r] - h[p * n7 + r]);
-        const double mean = (double)acc / ((double)(r1 - r0) * (double)NP);
-        int lg = kTileLanesLog2Min;
-        while (lg < 6 && kTileEntriesPerLane * (double)(1 << lg) < mean) ++lg;
-        auto depth = [&](int l) { return (maxseg + (1 << l) - 1) / (1 << l) + l + NP; };
-        if (P.dtype == SPMV_F64) {
-            while (lg < 6 && depth(lg) > kFp64MaxDepth) ++lg;
-            if (depth(lg) > kFp64MaxDepth) {
-                V.tile_seg.release();
-                return SPMV_OK;
-            }
-        }
-        blocks.push_back((int32_t)r0);
-        blocks.push_back((int32_t)r1);
-        blocks.push_back(lg);
-        max_tpr = std::max(max_tpr, 1 << lg);
-        r0 = r1;
-    }
-    SMAT_TRY(V.tile_blocks.alloc(sizeof(int32_t) * blocks.size()));
-    SMAT_HIP(hipMemcpyAsync(V.tile_blocks.p, blocks.data(), sizeof(int32_t) * blocks.size(),
-                            hipMemcpyHostToDevice, s));
+    const size_t entries = (size_t)units * kWave * (size_t)long_tile_per(P.elt);
     SMAT_TRY(V.tile_part.alloc(sizeof(double) * (size_t)(NP * n7)));
-    // The long rows' entries packed in workgroup order -- row block, panel,
-    // row -- so that each workgroup streams one contiguous range: pk[k] is
-    // the first packed entry of row r in panel p, k = NP r0 + p (r1 - r0) +
-    // (r - r0) for the block [r0, r1) holding r, and pk[k + 1] its end.
-    // NP n7 stays below total / 10 (the partials' share above), so int32.
-    std::vector<int32_t> pk((size_t)(NP * n7 + 1)), kb(2 * (size_t)n7);
-    int64_t pos = 0;
-    for (size_t bi = 0; bi < blocks.size(); bi += 3) {
-        const int64_t r0 = blocks[bi], r1 = blocks[bi + 1];
-        for (int64_t p = 0; p < NP; ++p)
-            for (int64_t r = r0; r < r1; ++r) {
-                pk[(size_t)(NP * r0 + p * (r1 - r0) + (r - r0))] = (int32_t)pos;
-                pos += (int64_t)h[(p + 1) * n7 + r] - h[p * n7 + r];
-            }
-        for (int64_t r = r0; r < r1; ++r) {
-            kb[2 * r] = (int32_t)(NP * r0 + (r - r0));
-            kb[2 * r + 1] = (int32_t)(r1 - r0);
-        }
-    }
-    pk[(size_t)(NP * n7)] = (int32_t)pos;
-    if (pos != total) {
-        set_error("long-row tiles: %lld packed entries for %lld", (long long)pos,
-                  (long long)total);
-        return SPMV_EINVAL;
-    }
-    {
-        Dev kbd;
-        SMAT_TRY(kbd.alloc(sizeof(int32_t) * kb.size()));
-        SMAT_TRY(V.tile_pk.alloc(sizeof(int32_t) * pk.size()));
-        SMAT_TRY(V.tile_off.alloc(sizeof(uint16_t) * (size_t)std::max<int64_t>(1, total)));
-        SMAT_TRY(V.tile_val.alloc((size_t)P.elt * (size_t)std::max<int64_t>(1, total)));
-        SMAT_HIP(hipMemcpyAsync(kbd.p, kb.data(), sizeof(int32_t) * kb.size(),
-                                hipMemcpyHostToDevice, s));
-        SMAT_HIP(hipMemcpyAsync(V.tile_pk.p, pk.data(), sizeof(int32_t) * pk.size(),
-                                hipMemcpyHostToDevice, s));
-        SMAT_TRY(launch_long_tile_pack(n7, NP, W, V.long_rows.as<int32_t>(), P.rp.as<int32_t>(),
-                                       P.col.as<int32_t>(), P.val.p, P.elt,
-                                       V.tile_seg.as<int32_t>(), kbd.as<int32_t>(),
-                                       V.tile_pk.as<int32_t>(), V.tile_off.as<uint16_t>(),
-                                       V.tile_val.p, s));
-        SMAT_HIP(hipStreamSynchronize(s));
-    }
-    V.tile_seg.release();   // the CSR-position segment starts are not needed to run
+    SMAT_TRY(V.tile_meta.alloc(sizeof(uint32_t) * (size_t)units * kWave));
+    SMAT_TRY(V.tile_off.alloc(sizeof(uint16_t) * entries));
+    SMAT_TRY(V.tile_val.alloc((size_t)P.elt * entries));
+    SMAT_HIP(hipMemsetAsync(V.tile_meta.p, 0, V.tile_meta.bytes, s));
+    int lg = 0;   // lanes per segment of the packing pass
+    while (lg < 6 && (double)(2 << lg) * (double)NP * (double)n7 < (double)total) ++lg;
+    SMAT_TRY(launch_tile_fill(P.elt, n7, nb, NP, lg, rows, P.rp.as<int32_t>(),
+                              P.col.as<int32_t>(), P.val.p, seg.as<int32_t>(),
+                              V.tile_blocks.as<TileBlock>(), V.tile_start.as<int32_t>(),
+                              V.tile_meta.as<uint32_t>(), V.tile_off.as<uint16_t>(),
+                              V.tile_val.p, s));
+    SMAT_HIP(hipStreamSynchronize(s));
+    V.tile_nt = V.tile_off.bytes + V.tile_val.bytes > kTileNtBytes;
     V.tile_P = NP;
-    V.tile_nb = (int64_t)blocks.size() / 3;
+    V.tile_nb = nb;
     V.long_tiles = true;
-    V.long_tpr = max_tpr;
+    V.long_tpr = kWave;   // rows share the wave's lanes
     return SPMV_OK;
 }
 
 // Column panels in two steps (k_expand.hip) when no other form was asked for
 // (panel_xcd, panel_kib or panel_direct_max) and the matrix fits the form's
 // indices: a block of rows never has more pieces than LDS holds (its entries
-// plus one partly filled piece per panel), scanned positions fit 31 bits, and
-// a row of the blocks takes at most a quarter of one.  Beyond those sizes an
+// plus one partly filled piece per panel) and scanned positions fit 31 bits.
+// Beyond those sizes an
 // entry's piece of x would be almost alone in its 16 bytes, and the XCD panels
 // are the better form.
 int64_t expand_panels(int64_t n, int elt) {
@@ -837,13 +829,20 @@ constexpr int64_t kExpandResident = 512, kExpandShare = 32768, kExpandShareMin =
 // MB, 172 -> 141 us; float32 n = 730k, 326 MB, 89 -> 87 us; 60 MB of short rows
 // beside tiles, 47 -> 53 us).
 constexpr uint64_t kExpandNtBytes = uint64_t(128) << 20;
+// ... and the first step's offsets, once they and xe alone leave none (n =
+// 730k: float64, 241 MB, 144 -> 136 us; float32, 144 MB, 80 -> 84 us).
+constexpr uint64_t kExpandNt1Bytes = uint64_t(192) << 20;
+// Longest row of the blocks where no tiles take the longer ones (a block is
+// filled only up to the last row that still fits: at most half is lost at
+// kTileRowMinMax, a sixteenth to an eighth here).
+constexpr int kExpandRowMax = 1024;
 
-bool expand_fits(const spmv_plan_s &P, const spmv_params &prm, int64_t lmax) {
+bool expand_fits(const spmv_plan_s &P, const spmv_params &prm) {
     const int G = 16 / P.elt;
     const int64_t E = expand_block_entries(P.elt), NP = expand_panels(P.n, P.elt);
     return prm.panel_xcd == 0 && prm.panel_kib == 4096 && prm.panel_direct_max <= 0 && P.m > 0 &&
            P.n > 0 && P.nnz > 0 && NP <= kExpandMaxPanels && E / G + NP <= expand_max_pieces() &&
-           lmax <= E / 4 && P.nnz + P.m < (1ll << 31) - 2 * E;
+           P.nnz + P.m < (1ll << 31) - 2 * E;
 }
 
 // Both steps' arrays from the plan's CSR copy; rows longer than lmax are left
@@ -1114,12 +1113,14 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         // restored below when they are not used
         const bool try_tiles = prm.long_lds == 0 || prm.long_lds == 3;
         int wg = try_tiles ? std::min(prm.adaptive_wg_min, prm.tile_row_min) : prm.adaptive_wg_min;
-        // panels in two steps: the longest bin (never in row blocks, which are
-        // cut between rows) starts at the tiles' row length at most
-        const int32_t expand_lmax =
-            std::max(std::min(wg, prm.tile_row_min), prm.adaptive_rows_per_lane << 5);
-        const bool expand = panels && expand_fits(P, prm, expand_lmax);
-        if (expand) wg = std::min(wg, prm.tile_row_min);
+        // panels in two steps: row blocks, cut between rows, take rows of a
+        // limited length; the longest bin starts there
+        const bool expand = panels && expand_fits(P, prm);
+        int wg_plain = prm.adaptive_wg_min;   // without tiles
+        if (expand) {
+            wg_plain = std::min(wg_plain, kExpandRowMax);
+            wg = std::min(wg, try_tiles ? kTileRowMinMax : wg_plain);
+        }
         SMAT_TRY(bin(wg));
         // split rows: segment table on the host from their row_ptr entries
         int64_t ns = V.bin_off[9] - V.bin_off[8];
@@ -1169,54 +1170,65 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         int ll = prm.long_lds;
         for (;;) {
             const int64_t n7 = (int64_t)V.bin_off[8] - V.bin_off[7];
-            if (ll == 0) ll = n7 >= kTileRowsDefault ? 3 : 2;
+            const int32_t *r7 = V.bin_rows.as<int32_t>() + V.bin_off[7];
+            Dev lpos;
+            int64_t total7 = 0;
+            if (n7 > 0 && (ll == 0 || ll == 3))
+                SMAT_TRY(long_row_lengths(P, n7, r7, lpos, &total7, s));
+            if (ll == 0)
+                ll = total7 * elt >= kTileBytesDefault ? 3 : 2;
             int tpr = n7 >= 8192 ? 32 : 64;
             if ((F.max_rd + tpr - 1) / tpr + ilog2(tpr) > kFp64MaxDepth) tpr = 64;
             const bool chunks_ok = P.dtype == SPMV_F64 &&
                                    (F.max_rd + tpr - 1) / tpr + ilog2(tpr) <= kFp64MaxDepth;
             if (n7 == 0 || (ll == 1 && !chunks_ok)) ll = 2;
-            if (ll != 2) {
+            if (ll == 3) {
+                SMAT_TRY(V.long_rows.alloc(sizeof(int32_t) * (size_t)n7));
+                SMAT_HIP(hipMemcpyAsync(V.long_rows.p, r7, sizeof(int32_t) * n7,
+                                        hipMemcpyDeviceToDevice, s));
+                SMAT_TRY(build_long_tiles(P, V, n7, lpos, total7, s));
+                if (!V.long_tiles && prm_in.tile_row_min == 0 && wg < kTileRowMinMax &&
+                    wg < prm.adaptive_wg_min) {
+                    // rows too short for so many panels: only longer ones
+                    V.prm.tile_row_min = wg = std::min(2 * wg, prm.adaptive_wg_min);
+                    V.long_rows.release();
+                    SMAT_TRY(bin(wg));
+                    ll = prm.long_lds;
+                    continue;
+                }
+                if (!V.long_tiles) ll = chunks_ok ? 1 : 2;
+            }
+            if (ll == 1) {
                 // the long rows longest first, so that the rows of one
                 // workgroup (which waits for its longest) are alike
-                std::vector<int64_t> len(n7);
-                {
-                    Dev be;
-                    SMAT_TRY(be.alloc(sizeof(int64_t) * 2 * (size_t)n7));
-                    const int32_t *r7 = V.bin_rows.as<int32_t>() + V.bin_off[7];
-                    k_gather_rowptr<<<(unsigned)((n7 + 255) / 256), 256, 0, s>>>(
-                        n7, r7, P.rp.as<int32_t>(), be.as<int64_t>());
-                    SMAT_LAUNCHED("gather_rowptr");
-                    std::vector<int64_t> h(2 * (size_t)n7);
-                    std::vector<int32_t> rows(n7);
-                    SMAT_HIP(hipMemcpyAsync(h.data(), be.p, sizeof(int64_t) * 2 * n7,
-                                            hipMemcpyDeviceToHost, s));
-                    SMAT_HIP(hipMemcpyAsync(rows.data(), r7, sizeof(int32_t) * n7,
-                                            hipMemcpyDeviceToHost, s));
-                    SMAT_HIP(hipStreamSynchronize(s));
-                    std::vector<int64_t> ord(n7);
-                    for (int64_t i = 0; i < n7; ++i) ord[i] = i;
-                    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
-                        return h[2 * a + 1] - h[2 * a] > h[2 * b + 1] - h[2 * b];
-                    });
-                    std::vector<int32_t> sorted(n7);
-                    for (int64_t i = 0; i < n7; ++i) {
-                        sorted[i] = rows[ord[i]];
-                        len[i] = h[2 * ord[i] + 1] - h[2 * ord[i]];
-                    }
-                    SMAT_TRY(V.long_rows.alloc(sizeof(int32_t) * (size_t)n7));
-                    SMAT_HIP(hipMemcpyAsync(V.long_rows.p, sorted.data(), sizeof(int32_t) * n7,
-                                            hipMemcpyHostToDevice, s));
-                    SMAT_HIP(hipStreamSynchronize(s));
-                }
-                if (ll == 3) {
-                    SMAT_TRY(build_long_tiles(P, V, len, s));
-                    if (!V.long_tiles) ll = chunks_ok ? 1 : 2;
-                }
+                Dev be;
+                SMAT_TRY(be.alloc(sizeof(int64_t) * 2 * (size_t)n7));
+                k_gather_rowptr<<<(unsigned)((n7 + 255) / 256), 256, 0, s>>>(
+                    n7, r7, P.rp.as<int32_t>(), be.as<int64_t>());
+                SMAT_LAUNCHED("gather_rowptr");
+                std::vector<int64_t> h(2 * (size_t)n7);
+                std::vector<int32_t> rows(n7);
+                SMAT_HIP(hipMemcpyAsync(h.data(), be.p, sizeof(int64_t) * 2 * n7,
+                                        hipMemcpyDeviceToHost, s));
+                SMAT_HIP(hipMemcpyAsync(rows.data(), r7, sizeof(int32_t) * n7,
+                                        hipMemcpyDeviceToHost, s));
+                SMAT_HIP(hipStreamSynchronize(s));
+                std::vector<int64_t> ord(n7);
+                for (int64_t i = 0; i < n7; ++i) ord[i] = i;
+                std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
+                    return h[2 * a + 1] - h[2 * a] > h[2 * b + 1] - h[2 * b];
+                });
+                std::vector<int32_t> sorted(n7);
+                for (int64_t i = 0; i < n7; ++i) sorted[i] = rows[ord[i]];
+                SMAT_TRY(V.long_rows.alloc(sizeof(int32_t) * (size_t)n7));
+                SMAT_HIP(hipMemcpyAsync(V.long_rows.p, sorted.data(), sizeof(int32_t) * n7,
+                                        hipMemcpyHostToDevice, s));
+                SMAT_HIP(hipStreamSynchronize(s));
             }
-            if (ll != 3 && wg != prm.adaptive_wg_min && n7 > 0 && !expand) {
+            if (ll != 3 && wg != wg_plain && n7 > 0) {
                 // no tiles: bins with the binned launch's own threshold
                 V.long_rows.release();
-                wg = prm.adaptive_wg_min;
+                wg = wg_plain;
                 SMAT_TRY(bin(wg));
                 continue;
             }
@@ -1282,7 +1294,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             if (expand) {
                 V.along = bins_launch(V.bin_off, 7, 7, 0);
                 V.prm.panel_xcd = 0;
-                SMAT_TRY(build_expand(P, F, V, expand_lmax, s));
+                SMAT_TRY(build_expand(P, F, V, spec.upper[6], s));
                 // streams that leave no room in the 256 MB Infinity Cache for
                 // xe between the two steps are read past it
                 if (prm_in.stream_nt == 0)
@@ -1321,14 +1333,17 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
     }
 }
 
+TileRun tile_run(const Variant &V) {
+    return TileRun{V.n_long, V.tile_P, V.tile_nb, V.tile_blocks.as<TileBlock>(),
+                   V.tile_start.as<int32_t>(), V.tile_meta.as<uint32_t>(),
+                   V.long_rows.as<int32_t>(), V.tile_off.as<uint16_t>(), V.tile_val.p,
+                   V.tile_part.as<double>(), V.tile_nt};
+}
+
 // The long rows taken out of the binned launch: x chunks or tiles.
 spmv_status run_long_rows(const spmv_plan_s &P, const Variant &V, const void *x, void *y,
                           hipStream_t s) {
-    if (V.long_tiles)
-        return run_long_tiles(P.elt, V.n_long, V.tile_P, V.tile_nb, V.tile_blocks.as<int32_t>(),
-                              V.tile_pk.as<int32_t>(), V.long_rows.as<int32_t>(),
-                              V.tile_off.as<uint16_t>(), V.tile_val.p, x, P.n,
-                              V.tile_part.as<double>(), y, s);
+    if (V.long_tiles) return run_long_tiles(P.elt, tile_run(V), x, P.n, y, s);
     return run_long_rows_lds(V.long_tpr, V.n_long, V.long_rows.as<int32_t>(), P.rp.as<int32_t>(),
                              P.col.as<int32_t>(), P.val.as<double>(), (const double *)x, P.n,
                              (double *)y, s);
@@ -1351,10 +1366,7 @@ spmv_status run_variant(const spmv_plan_s &P, const Variant &V, const void *x, v
         if (V.long_tiles) {
             // the tiles first, then the short rows and the tiles' sums in
             // one launch
-            SMAT_TRY(run_long_tiles(elt, V.n_long, V.tile_P, V.tile_nb,
-                                    V.tile_blocks.as<int32_t>(), V.tile_pk.as<int32_t>(),
-                                    V.long_rows.as<int32_t>(), V.tile_off.as<uint16_t>(),
-                                    V.tile_val.p, x, P.n, V.tile_part.as<double>(), y, s, false));
+            SMAT_TRY(run_long_tiles(elt, tile_run(V), x, P.n, y, s, false));
             SMAT_TRY(run_csr_adaptive_tiles(elt, nt, V.arest, V.bin_rows.as<int32_t>(),
                                             V.binned_rp.as<int32_t>(), V.binned_col.as<int32_t>(),
                                             V.binned_val.p, x, y, V.n_long, V.tile_P,
@@ -1377,11 +1389,15 @@ spmv_status run_variant(const spmv_plan_s &P, const Variant &V, const void *x, v
         // binned positions [lo, hi) go through the panels: all rows but the
         // short bins (summed directly) and the longest bin (long-row kernel)
         if (V.expand) {
-            SMAT_TRY(run_expand(elt, nt, V.ex_nchunks, V.ex_chunks.as<ExpandChunk>(),
-                                V.ex_starts.as<int32_t>(), V.ex_off.as<uint16_t>(), x, P.n, V.ex_xe.p, V.ex_nb,
-                                V.ex_blocks.as<ExpandBlock>(), V.ex_meta.as<uint32_t>(),
-                                V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
-                                V.ex_stride, y, s));
+            const ExpandRun r{V.ex_nchunks, V.ex_nb, V.ex_chunks.as<ExpandChunk>(),
+                              V.ex_starts.as<int32_t>(), V.ex_off.as<uint16_t>(), V.ex_xe.p,
+                              V.ex_blocks.as<ExpandBlock>(), V.ex_meta.as<uint32_t>(),
+                              V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
+                              V.ex_stride, nt && V.ex_off.bytes + V.ex_xe.bytes > kExpandNt1Bytes,
+                              nt};
+            const TileRun t = tile_run(V);
+            SMAT_TRY(run_expand(elt, r, V.long_tiles ? &t : nullptr, x, P.n, y, s));
+            if (V.long_tiles) return SPMV_OK;
             if (V.long_tpr) return run_long_rows(P, V, x, y, s);
             return run_csr_adaptive(elt, nt, true, V.along, V.bin_rows.as<int32_t>(),
                                     P.rp.as<int32_t>(), P.col.as<int32_t>(), P.val.p, x, y, s);
@@ -1517,7 +1533,7 @@ std::vector<spmv_params> tune_grid(int kernel, const spmv_params &b, const spmv_
                 }
         // tiles for more or only the longer rows, the other parameters at
         // their defaults
-        for (int r : {256, 4096, 16384}) {
+        for (int r : {256, 1024, 4096, 16384}) {
             spmv_params p = b;
             p.long_lds = 3;
             p.tile_row_min = r;
@@ -1602,7 +1618,7 @@ std::vector<spmv_params> tune_grid(int kernel, const spmv_params &b, const spmv_
             p.panel_direct_max = d;
             add(p);
         }
-        for (int r : {256, 4096, 16384}) {
+        for (int r : {256, 1024, 4096, 16384}) {
             spmv_params p = b;
             p.long_lds = 3;
             p.tile_row_min = r;

@@ -173,31 +173,61 @@ spmv_status run_long_rows_lds(int tpr, int64_t nrows, const int32_t *rows, const
                               double *y, hipStream_t s);
 // Long rows by tiles: x panels of long_tile_width(elt) values, workgroup
 // (row block, panel).  seg: (P + 1) * n7 segment starts in CSR positions,
-// filled by launch_long_tile_seg from the rows (ascending columns); blocks:
-// nblocks triples (first row, end row, log2 lanes per row) over the rows'
-// order.  The entries are packed by launch_long_tile_pack in (row block,
-// panel, row) order: pk[k], k = P r0 + p (r1 - r0) + (r - r0) for the block
-// [r0, r1) holding r, is row r's first entry in panel p and pk[k + 1] its
-// end (P n7 + 1 ints); off (16-bit column - p W) and val hold the packed
-// entries, kb two ints per row (k at p = 0, r1 - r0).  part: P * n7 float64
-// partials.  y receives the rows rows[0 .. n7).
+// filled by launch_long_tile_seg from the rows (ascending columns).  A tile's
+// entries lie in wave units of 64 * PER entries, lane l of a unit holding
+// entries l PER .. l PER + PER - 1 of it (interleaved over the wave in 16-byte
+// vectors); start: the tiles' first units, b P + p (and the end).  meta, one
+// word a lane: row starts (low half), rows started before the lane in its
+// pass of 16 units (high half).  part: P * n7 float64 partials.  y receives
+// the rows rows[0 .. n7).
+template <typename T> struct TileShape {
+    static constexpr int PER = 64 / (int)sizeof(T);   // 64 bytes of values a thread
+};
+struct TileBlock { int32_t row0, rows; };
 int64_t long_tile_width(int elt);
+int long_tile_per(int elt);
 // Raises the tile kernels' dynamic LDS limit (before the first launch,
 // outside graph capture).
 spmv_status long_tiles_prepare();
 spmv_status launch_long_tile_seg(int64_t n7, int64_t P, int64_t W, const int32_t *rows,
                                  const int32_t *rp, const int32_t *col, int32_t *seg,
                                  hipStream_t s);
-spmv_status launch_long_tile_pack(int64_t n7, int64_t P, int64_t W, const int32_t *rows,
-                                  const int32_t *rp, const int32_t *col, const void *val, int elt,
-                                  const int32_t *seg, const int32_t *kb, const int32_t *pk,
-                                  uint16_t *off, void *pval, hipStream_t s);
+// Row blocks of `step` entries (lpos: the rows' lengths scanned), the wave
+// units per tile, the packed entries (2^lg lanes share a segment).
+spmv_status launch_tile_blocks(int64_t n7, int64_t nb, int64_t step, const int32_t *lpos,
+                               TileBlock *blocks, hipStream_t s);
+spmv_status launch_tile_count(int elt, int64_t n7, int64_t nb, int64_t P, const TileBlock *blocks,
+                              const int32_t *seg, int32_t *cnt, hipStream_t s);
+spmv_status launch_tile_fill(int elt, int64_t n7, int64_t nb, int64_t P, int lg,
+                             const int32_t *rows, const int32_t *rp, const int32_t *col,
+                             const void *val, const int32_t *seg, const TileBlock *blocks,
+                             const int32_t *start, uint32_t *meta, uint16_t *off, void *oval,
+                             hipStream_t s);
+// What a run of the tiles needs; nt: the entries are read past the caches.
+struct TileRun {
+    int64_t n7, P, nblocks;
+    const TileBlock *blocks;
+    const int32_t *start;
+    const uint32_t *meta;
+    const int32_t *rows;
+    const uint16_t *off;
+    const void *val;
+    double *part;
+    bool nt;
+};
+#define SMAT_TILES_OK(t, elt)                                                              \
+    do {                                                                                   \
+        if ((t).P < 1 || (t).P > 65535 || (t).nblocks < 1 ||                               \
+            (t).P * (t).nblocks > INT32_MAX || ((elt) != 4 && (elt) != 8)) {               \
+            set_error("long-row tiles: %lld panels, %lld row blocks", (long long)(t).P,    \
+                      (long long)(t).nblocks);                                             \
+            return SPMV_EINVAL;                                                            \
+        }                                                                                  \
+    } while (0)
 // reduce false: the tiles' partials only, added later by
 // run_csr_adaptive_tiles.
-spmv_status run_long_tiles(int elt, int64_t n7, int64_t P, int64_t nblocks,
-                           const int32_t *blocks, const int32_t *pk, const int32_t *rows,
-                           const uint16_t *off, const void *val, const void *x, int64_t n,
-                           double *part, void *y, hipStream_t s, bool reduce = true);
+spmv_status run_long_tiles(int elt, const TileRun &t, const void *x, int64_t n, void *y,
+                           hipStream_t s, bool reduce = true);
 // After run_long_tiles(..., reduce = false): the binned launch `a` of the
 // short rows (entries from the binned-order copy) and the sums of the n7
 // long rows' P panel partials `part` into y[lrows[r]], in one launch.
@@ -251,12 +281,25 @@ spmv_status launch_expand_to_csr(int elt, int64_t nb, int P, int32_t lmax, const
                                  const uint16_t *off, const uint16_t *slot, const void *oval,
                                  const int32_t *piece, int pieces_stride, int32_t *col, void *val,
                                  hipStream_t s);
-// Both steps: every row of the blocks but those longer than lmax.
-spmv_status run_expand(int elt, bool nt, int64_t nchunks, const ExpandChunk *chunks,
-                       const int32_t *starts, const uint16_t *off, const void *x, int64_t n, void *xe, int64_t nb,
-                       const ExpandBlock *blocks, const uint32_t *meta, const uint16_t *slot,
-                       const void *val, const int32_t *piece, int pieces_stride, void *y,
-                       hipStream_t s);
+// Both steps: every row of the blocks but those longer than lmax, which the
+// tiles `t`, if given, take in the same two launches.  nt1, nt: the first and
+// second step's streams are read past the caches.
+struct ExpandRun {
+    int64_t nchunks, nb;
+    const ExpandChunk *chunks;
+    const int32_t *starts;
+    const uint16_t *off;
+    void *xe;
+    const ExpandBlock *blocks;
+    const uint32_t *meta;
+    const uint16_t *slot;
+    const void *val;
+    const int32_t *piece;
+    int stride;
+    bool nt1, nt;
+};
+spmv_status run_expand(int elt, const ExpandRun &r, const TileRun *t, const void *x, int64_t n,
+                       void *y, hipStream_t s);
 // split rows: segments (row, begin, end) reduce into partials, then fix-up
 spmv_status run_csr_split(int elt, int64_t nseg, const int64_t *segs, double *partials,
                           int64_t nrows, const int64_t *row_seg_begin, const int32_t *rows,

@@ -19,14 +19,19 @@
 // streamed.  x is only copied in between, so a row is summed in float64 from
 // the same products as in any other CSR kernel.
 //
-// Measured (MI355X; expand + rows): uniform 33 a row, n = 730k, float32 32 +
-// 52 us (5.3 and 5.2 TB/s), float64 55 + 84 us, where slot-major ELL takes 118
-// and 190 us and the XCD panels 143 and 222 us; the 7.98M rows of up to 1024
-// entries of a Zipf matrix with n = 8M, float32, 117 + 252 us for 968 + 102 us
-// by XCD panels (the whole product 1425 -> 728 us).  Rows as plain blocks of
-// 16384 (8192 float64) entries: shrinking the blocks so that their number
-// fills the last round of resident workgroups was no faster (n = 300k float32
-// 39 -> 44 us: a block's fixed cost outweighs the half-empty round).
+// Measured (MI355X): uniform 33 a row, n = 730k, float32 32 + 52 us (5.3 and
+// 5.2 TB/s), float64 55 + 84 us, where slot-major ELL takes 118 and 190 us and
+// the XCD panels 143 and 222 us; the 7.98M rows of up to 1024 entries of a Zipf
+// matrix with n = 8M, float32, 117 + 252 us for 968 + 102 us by XCD panels.
+// Rows as plain blocks of 16384 (8192 float64) entries: shrinking the blocks
+// so that their number fills the last round of resident workgroups was no
+// faster (n = 300k float32 39 -> 44 us: a block's fixed cost outweighs the
+// half-empty round).
+//
+// Long rows by tiles (tiles_device.hpp) run in the same two launches: their
+// workgroups hold a panel of x as well, and their sums run beside the row
+// blocks.  Two launches instead of four: n = 310k float32 41 -> 37 us, n =
+// 700k float64 404 -> 391 us, n = 1M float64 with 5M entries 45 -> 39 us.
 //
 // Row sums: a thread takes PER consecutive entries whatever their rows, with
 // a bit per entry marking where a row starts; the piece of a row that
@@ -34,22 +39,23 @@
 // LDS, over the workgroup, in a fixed order.  A block is cut between rows, so
 // no sum leaves it.  The float64 chain of a row is at most PER + 6 + 16 + its
 // share of threads.
-#include "spmv_device.hpp"
+#include "tiles_device.hpp"
 
 #include <algorithm>
+#include <climits>
 
 namespace smat {
 namespace {
 
-constexpr int kExpandThreads = 1024;
-constexpr int kExpandBytes = 81920;   // x per panel: two workgroups fill a CU's LDS
+constexpr int kExpandThreads = kTileThreads;
+constexpr int kExpandBytes = kTileBytes;   // x per panel: two workgroups fill a CU's LDS
 constexpr int kRowsThreads = 1024;
 constexpr int kRowsPieces = 5100;     // 16-byte pieces of xe per row block, at most
-// slot of an entry that stands for a row the block skips (another kernel
-// writes it), and the most slots a block can have
-constexpr unsigned kSkipSlot = 0xFFFF;
+// Behind a block's pieces lies one of zeros: its first value is the slot of an
+// entry that adds zero, its second that of the entry standing for a row which
+// another kernel writes.
 static_assert((kRowsPieces + 1) * 16 + 256 <= 81920, "two row workgroups fill a CU's LDS");
-static_assert((kRowsPieces + 1) * 4 < kSkipSlot, "slots must fit 16 bits");
+static_assert((kRowsPieces + 1) * 4 < 65536, "slots must fit 16 bits");
 
 // G: values per 16-byte piece.
 template <typename T> constexpr int kPiece = 16 / (int)sizeof(T);
@@ -69,40 +75,33 @@ constexpr int kSlotVec = 8;   // 16-bit slots per 16 bytes
 // in, G values of x out per lane and piece, kExpandAhead pieces in flight.
 constexpr int kExpandAhead = 4;
 
+template <typename T> struct ExpandArgs {
+    const ExpandChunk *__restrict__ chunks;
+    const int32_t *__restrict__ starts;
+    const uint16_t *__restrict__ off;
+    const T *__restrict__ x;
+    int64_t n;
+    T *__restrict__ xe;
+};
+
 template <typename T, bool NT>
-__global__ __launch_bounds__(kExpandThreads) void k_panel_expand(
-    const ExpandChunk *__restrict__ chunks, const int32_t *__restrict__ starts,
-    const uint16_t *__restrict__ off, const T *__restrict__ x, int64_t n, T *__restrict__ xe) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void expand_block(const ExpandArgs<T> &a, unsigned bid,
+                                             unsigned char *smem) {
     constexpr int G = kPiece<T>;
     typedef T vec __attribute__((ext_vector_type(G)));
     typedef uint16_t ovec __attribute__((ext_vector_type(G)));
-    constexpr int PER = kExpandBytes / 16 / kExpandThreads;
-    static_assert(kExpandBytes % (16 * kExpandThreads) == 0, "panel must split evenly");
-    const ExpandChunk ch = chunks[blockIdx.x];
-    const ovec *ov = reinterpret_cast<const ovec *>(off);
-    vec *out = reinterpret_cast<vec *>(xe);
+    const ExpandChunk ch = a.chunks[bid];
+    const ovec *ov = reinterpret_cast<const ovec *>(a.off);
+    vec *out = reinterpret_cast<vec *>(a.xe);
     vec *xv = reinterpret_cast<vec *>(smem);
     const T *xs = reinterpret_cast<const T *>(smem);
     int64_t begin = ch.begin;
     for (int p = ch.panel; begin < ch.end; ++p) {
-        const int64_t stop = starts[p + 1], end = stop < ch.end ? stop : ch.end;
+        const int64_t stop = a.starts[p + 1], end = stop < ch.end ? stop : ch.end;
         if (begin >= end) continue;   // a panel without entries
         const int64_t c0 = (int64_t)p * (kExpandBytes / (int)sizeof(T));
         if (p != ch.panel) __syncthreads();   // the panel before is done with
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int k = q * kExpandThreads + threadIdx.x;
-            const int64_t j0 = c0 + (int64_t)k * G;
-            vec w;
-            if (j0 + G <= n) {
-                __builtin_memcpy(&w, x + j0, sizeof(w));
-            } else {
-#pragma unroll
-                for (int e = 0; e < G; ++e) w[e] = j0 + e < n ? x[j0 + e] : T(0);
-            }
-            xv[k] = w;
-        }
+        copy_panel<T>(a.x, a.n, c0, xv);
         __syncthreads();
         constexpr int U = kExpandAhead;
         int64_t v = begin + (int)threadIdx.x;
@@ -129,23 +128,50 @@ __global__ __launch_bounds__(kExpandThreads) void k_panel_expand(
     }
 }
 
+// First launch: workgroups [0, tiles) take the long rows' tiles, if the plan
+// has any, the others the first step; both hold a panel of x, and the second
+// kind fills the compute units that the last round of tiles leaves.
+template <typename T, bool NT>
+__global__ __launch_bounds__(kExpandThreads, 8) void k_panel_expand(ExpandArgs<T> a,
+                                                                    unsigned tiles,
+                                                                    TileArgs<T> ta) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ TileLds lds;
+    if (blockIdx.x < tiles)
+        tile_block<T, NT>(ta, blockIdx.x, smem, lds);
+    else
+        expand_block<T, NT>(a, blockIdx.x - tiles, smem);
+}
+
 // Row block b of the second step.  meta[b * threads + t]: bit j of the low
 // half set when entry j of thread t starts a row, the high half the rows
-// started before the thread's first entry.
+// started before the thread's first entry.  The workgroups from `sums` on add
+// the long rows' panel partials, kRowsThreads / 256 groups of kReduceRows rows
+// each.
 template <typename T, int PER, bool NT>
 __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
     const ExpandBlock *__restrict__ blocks, const uint32_t *__restrict__ meta,
     const uint16_t *__restrict__ slot, const T *__restrict__ val,
     const int32_t *__restrict__ piece, int pieces_stride, const T *__restrict__ xe,
-    T *__restrict__ y) {
+    T *__restrict__ y, unsigned sums, int64_t n7, int64_t P, const int32_t *__restrict__ lrows,
+    const double *__restrict__ part) {
     extern __shared__ __align__(16) unsigned char smem[];
+    if (blockIdx.x >= sums) {
+        constexpr int kThreads = kReduceRows * kReduceGroups, kParts = kRowsThreads / kThreads;
+        typedef double gs_t[kReduceGroups][kReduceRows];
+        const unsigned sub = threadIdx.x / kThreads;
+        tiles_reduce_block<T>((blockIdx.x - sums) * kParts + sub, threadIdx.x % kThreads, n7, P,
+                              lrows, part, y, reinterpret_cast<gs_t *>(smem)[sub]);
+        return;
+    }
     __shared__ double wtail[kRowsThreads / kWave];
     __shared__ unsigned wflag[kRowsThreads / kWave];
     constexpr int G = kPiece<T>;
     typedef T vec __attribute__((ext_vector_type(G)));
     constexpr int SV = kSlotVec;
-    typedef uint16_t svec __attribute__((ext_vector_type(SV)));
-    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+    typedef uint32_t svec __attribute__((ext_vector_type(SV / 2)));   // two slots a word
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const int64_t b = blockIdx.x;
     const ExpandBlock blk = blocks[b];
     const int zero = pieces_stride * G;   // slot holding +0.0
@@ -159,7 +185,7 @@ __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
 #pragma unroll
     for (int q = 0; q < PER / SV; ++q)
 #pragma unroll
-        for (int e = 0; e < SV; ++e) sl[q][e] = (uint16_t)zero;
+        for (int e = 0; e < SV / 2; ++e) sl[q][e] = (unsigned)zero * 0x10001u;
 #pragma unroll
     for (int q = 0; q < PER / G; ++q)
 #pragma unroll
@@ -204,7 +230,7 @@ __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
     bool skip = false;                    // it is a row another kernel writes
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const unsigned s = sl[j / SV][j % SV];
+        const unsigned s = sl[j / SV][j % SV / 2] >> (j % 2 * 16) & 0xFFFFu;
         if (flags >> j & 1u) {
             if (r < before)
                 head = acc;
@@ -212,28 +238,19 @@ __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
                 yb[r] = (T)acc;
             acc = 0.0;
             ++r;
-            skip = s == kSkipSlot;
+            skip = s == (unsigned)zero + 1u;
         }
-        const T xj = xs[s == kSkipSlot ? (unsigned)zero : s];
-        acc = fma((double)vv[j / G][j % G], (double)xj, acc);
+        acc = fma((double)vv[j / G][j % G], (double)xs[s], acc);
     }
     // rows across threads: acc is the sum of the row still open (of all
     // entries if the thread starts no row)
     const bool any = flags != 0;
     const unsigned long long bal = __ballot(any);
-    const unsigned long long upto = bal & (~0ull >> (kWave - 1 - lane));
-    const int start = upto ? 63 - __clzll(upto) : 0;
-    double v = acc;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const double u = __shfl_up(v, off, kWave);
-        if (lane - off >= start) v += u;
-    }
-    double carry = __shfl_up(v, 1, kWave);
+    double tail;
+    double carry = wave_carry(acc, bal, lane, &tail);
     const int sk = __shfl_up((int)skip, 1, kWave);
-    if (lane == 0) carry = 0.0;
     if (lane == kWave - 1) {
-        wtail[wave] = v;
+        wtail[wave] = tail;
         wflag[wave] = (bal ? 1u : 0u) | (skip ? 2u : 0u);
     }
     __syncthreads();
@@ -384,7 +401,7 @@ __global__ __launch_bounds__(1024) void k_expand_fill(
         if (lane == 0) {
             atomicOr(&bits[pos / 32], 1u << (pos % 32));
             if (e1 == e0 || e1 - e0 > lmax) {
-                slot[expand_at<PER, kSlotVec>(b, pos)] = e1 == e0 ? zero : (uint16_t)kSkipSlot;
+                slot[expand_at<PER, kSlotVec>(b, pos)] = e1 == e0 ? zero : (uint16_t)(zero + 1);
                 oval[expand_at<PER, G>(b, pos)] = 0;
             }
         }
@@ -473,10 +490,10 @@ spmv_status expand_prepare() {
 #define ATTR(F, BYTES)                                                                      \
     SMAT_HIP(hipFuncSetAttribute((const void *)(F), hipFuncAttributeMaxDynamicSharedMemorySize, \
                                  (int)(BYTES)))
-    ATTR((k_panel_expand<float, false>), kExpandBytes);
-    ATTR((k_panel_expand<float, true>), kExpandBytes);
-    ATTR((k_panel_expand<double, false>), kExpandBytes);
-    ATTR((k_panel_expand<double, true>), kExpandBytes);
+    ATTR((k_panel_expand<float, false>), kTileLds);
+    ATTR((k_panel_expand<float, true>), kTileLds);
+    ATTR((k_panel_expand<double, false>), kTileLds);
+    ATTR((k_panel_expand<double, true>), kTileLds);
     ATTR((k_panel_rows<float, 16, false>), (kRowsPieces + 1) * 16);
     ATTR((k_panel_rows<float, 16, true>), (kRowsPieces + 1) * 16);
     ATTR((k_panel_rows<double, 8, false>), (kRowsPieces + 1) * 16);
@@ -552,42 +569,58 @@ spmv_status launch_expand_to_csr(int elt, int64_t nb, int P, int32_t lmax, const
     return SPMV_OK;
 }
 
-template <typename T, int PER, bool NT>
-static spmv_status expand_dispatch(int64_t nchunks, const ExpandChunk *chunks, const int32_t *starts,
-                                   const uint16_t *off,
-                                   const T *x, int64_t n, T *xe, int64_t nb,
-                                   const ExpandBlock *blocks, const uint32_t *meta,
-                                   const uint16_t *slot, const T *val, const int32_t *piece,
-                                   int pieces_stride, T *y, hipStream_t s) {
-    if (nchunks > 0) {
-        k_panel_expand<T, NT><<<(unsigned)nchunks, kExpandThreads, kExpandBytes, s>>>(
-            chunks, starts, off, x, n, xe);
+template <typename T, int PER>
+static spmv_status expand_dispatch(const ExpandRun &r, const TileRun *t, const T *x, int64_t n,
+                                   T *y, hipStream_t s) {
+    const ExpandArgs<T> a{r.chunks, r.starts, r.off, x, n, (T *)r.xe};
+    TileArgs<T> ta{};
+    unsigned tiles = 0, sum_blocks = 0;
+    if (t) {
+        ta = TileArgs<T>{t->n7, t->P, t->blocks, t->start, t->meta, t->off, (const T *)t->val, x,
+                         n, t->part};
+        tiles = (unsigned)(t->P * t->nblocks);
+        constexpr int kPer = kReduceRows * (kRowsThreads / (kReduceRows * kReduceGroups));
+        sum_blocks = (unsigned)((t->n7 + kPer - 1) / kPer);
+    }
+    const unsigned first = tiles + (unsigned)r.nchunks;
+    if (first > 0) {
+        if (r.nt1 || (t && t->nt))
+            k_panel_expand<T, true><<<first, kExpandThreads, kTileLds, s>>>(a, tiles, ta);
+        else
+            k_panel_expand<T, false><<<first, kExpandThreads, kTileLds, s>>>(a, tiles, ta);
         SMAT_LAUNCHED("panel_expand");
     }
-    if (nb > 0) {
-        const size_t sh = ((size_t)pieces_stride + 1) * 16;
-        k_panel_rows<T, PER, NT><<<(unsigned)nb, kRowsThreads, sh, s>>>(
-            blocks, meta, slot, val, piece, pieces_stride, xe, y);
+    const unsigned second = (unsigned)r.nb + sum_blocks;
+    if (second > 0) {
+        const size_t sums_lds = sum_blocks ? sizeof(double) * kRowsThreads : 0;
+        const size_t sh = std::max(((size_t)r.stride + 1) * 16, sums_lds);
+#define ROWS(NT)                                                                             \
+    k_panel_rows<T, PER, NT><<<second, kRowsThreads, sh, s>>>(                               \
+        r.blocks, r.meta, r.slot, (const T *)r.val, r.piece, r.stride, (const T *)r.xe, y,   \
+        (unsigned)r.nb, t ? t->n7 : 0, t ? t->P : 0, t ? t->rows : nullptr, t ? t->part : nullptr)
+        if (r.nt)
+            ROWS(true);
+        else
+            ROWS(false);
+#undef ROWS
         SMAT_LAUNCHED("panel_rows");
     }
     return SPMV_OK;
 }
 
-spmv_status run_expand(int elt, bool nt, int64_t nchunks, const ExpandChunk *chunks,
-                       const int32_t *starts, const uint16_t *off, const void *x, int64_t n, void *xe, int64_t nb,
-                       const ExpandBlock *blocks, const uint32_t *meta, const uint16_t *slot,
-                       const void *val, const int32_t *piece, int pieces_stride, void *y,
-                       hipStream_t s) {
-    if (pieces_stride < 0 || pieces_stride > kRowsPieces || nb > INT32_MAX || nchunks > INT32_MAX) {
-        set_error("expanded panels: %d pieces per row block", pieces_stride);
+spmv_status run_expand(int elt, const ExpandRun &r, const TileRun *t, const void *x, int64_t n,
+                       void *y, hipStream_t s) {
+    if (r.stride < 0 || r.stride > kRowsPieces || r.nb > INT32_MAX || r.nchunks > INT32_MAX) {
+        set_error("expanded panels: %d pieces per row block", r.stride);
         return SPMV_EINVAL;
     }
-#define CALL(T, PER, NT)                                                                       \
-    expand_dispatch<T, PER, NT>(nchunks, chunks, starts, off, (const T *)x, n, (T *)xe, nb, blocks, meta, \
-                                slot, (const T *)val, piece, pieces_stride, (T *)y, s)
-    return elt == 8 ? (nt ? CALL(double, 8, true) : CALL(double, 8, false))
-                    : (nt ? CALL(float, 16, true) : CALL(float, 16, false));
-#undef CALL
+    if (t) SMAT_TILES_OK(*t, elt);
+    if ((t ? t->P * t->nblocks : 0) + r.nchunks > INT32_MAX) {
+        set_error("expanded panels: too many workgroups");
+        return SPMV_EINVAL;
+    }
+    return elt == 8 ? expand_dispatch<double, 8>(r, t, (const double *)x, n, (double *)y, s)
+                    : expand_dispatch<float, 16>(r, t, (const float *)x, n, (float *)y, s);
 }
 
 }  // namespace smat

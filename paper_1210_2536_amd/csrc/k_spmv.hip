@@ -13,6 +13,7 @@
 // sums that cross workgroups are combined by a second kernel in a fixed
 // order.
 #include "spmv_device.hpp"
+#include "tiles_device.hpp"
 
 #include <climits>
 
@@ -466,163 +467,12 @@ __global__ __launch_bounds__(kLongThreads) void k_long_rows_lds(
 }
 
 // ---------------------------------------------------------------- long rows, x panels per workgroup
-// The long rows (longest first) are cut into row blocks of about equal entry
-// counts and x into panels of kTileBytes.  Workgroup (b, p) copies x panel p
-// into LDS once, then adds for every row of block b the row's entries whose
-// columns fall in the panel, the segment [seg[p][r], seg[p + 1][r]) of row r:
-// lane t of the row's TPR lanes takes the segment's entries t, t + TPR, ...
-// in order, TPR being set per block so that short and long segments both
-// keep the lanes busy.  The lane sums are added by xor shuffles into one
-// float64 partial per (row, panel), and k_long_tiles_reduce (or, in binned
-// CSR, the first workgroups of k_csr_adaptive_tiles) adds a row's partials
-// in panel order and rounds once.  A row's float64 chain is at most
-// (longest segment) / TPR + log2 TPR + panels long.
-//
-// The entries come packed in workgroup order (row block, panel, row; see
-// k_long_tile_pack), so a workgroup streams one contiguous range, and their
-// columns as 16-bit offsets into the panel (col - p W): a panel holds at
-// most 20480 values, and the entry stream shrinks from 4 + sizeof(T) to
-// 2 + sizeof(T) bytes per entry.
-constexpr int kTileThreads = 1024;
-constexpr int kTileBytes = 81920;   // x per workgroup: two workgroups fill a CU's LDS
-constexpr int kTileUnroll = 4;      // entries per lane loaded ahead
-static_assert(kTileBytes / 4 <= 65536, "panel offsets must fit 16 bits");
-
-//
-// Dispatch order: panels fastest (workgroup w serves panel w mod P of row
-// block w / P).  The workgroups in flight then cover a few row blocks across
-// all panels: each row's entries are read front to back by neighbouring
-// workgroups and the GPU streams a small part of the matrix at a time
-// (measured 6% faster on the largest Zipf matrices than row blocks
-// fastest; padding P to a multiple of 8, so that panel p always runs on XCD
-// p mod 8, was 1-2% slower again).
-template <typename T>
-__global__ __launch_bounds__(kTileThreads) void k_long_tiles(
-    int64_t n7, int64_t W, int64_t P, const int32_t *__restrict__ blocks,
-    const int32_t *__restrict__ pk, const uint16_t *__restrict__ off,
-    const T *__restrict__ val, const T *__restrict__ x, int64_t n, double *__restrict__ part) {
+// Long rows by tiles (tiles_device.hpp) in a launch of their own.
+template <typename T, bool NT>
+__global__ __launch_bounds__(kTileThreads, 8) void k_long_tiles(TileArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int V = 16 / (int)sizeof(T);      // values per 16-byte piece
-    typedef T vec __attribute__((ext_vector_type(V)));
-    constexpr int PIECES = kTileBytes / 16;
-    constexpr int PER = PIECES / kTileThreads;
-    static_assert(PIECES % kTileThreads == 0, "panel must split evenly");
-    const int64_t p = (int64_t)blockIdx.x % P, b = (int64_t)blockIdx.x / P;
-    const int64_t c0 = p * W;
-    vec *xv = reinterpret_cast<vec *>(smem);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int k = q * kTileThreads + threadIdx.x;
-        const int64_t j0 = c0 + (int64_t)k * V;
-        vec w;
-        if (j0 + V <= n) {
-            __builtin_memcpy(&w, x + j0, sizeof(w));
-        } else {
-#pragma unroll
-            for (int e = 0; e < V; ++e) w[e] = j0 + e < n ? x[j0 + e] : T(0);
-        }
-        xv[k] = w;
-    }
-    __syncthreads();
-    const T *xs = reinterpret_cast<const T *>(smem);
-    const int64_t r0 = blocks[3 * b], r1 = blocks[3 * b + 1];
-    const int lg = blocks[3 * b + 2];
-    const int tpr = 1 << lg;
-    const int t = threadIdx.x & (tpr - 1);
-    const int grp = threadIdx.x >> lg;
-    const int G = kTileThreads >> lg;
-    // row r's packed range in panel p: [sb[r], se[r])
-    const int32_t *sb = pk + (P * r0 + p * (r1 - r0) - r0), *se = sb + 1;
-    double *pp = part + p * n7;
-    // every lane of a wave runs the same iterations (the shuffles need them);
-    // the next group's segment bounds are loaded before the current group's
-    // entries, so blocks of many short segments do not wait on them
-    int64_t r = r0 + grp;
-    bool act = r < r1;
-    int64_t qb = act ? (int64_t)sb[r] : 0, qe = act ? (int64_t)se[r] : 0;
-    for (int64_t base = r0; base < r1; base += G) {
-        const int64_t rn = base + G + grp;
-        const bool actn = rn < r1;
-        const int64_t nb = actn ? (int64_t)sb[rn] : 0, ne = actn ? (int64_t)se[rn] : 0;
-        const int64_t e = qe;
-        int64_t q = qb + t;
-        double acc = 0.0;
-        // kTileUnroll entries per lane and trip, all loads issued before any
-        // is used; the remainder in one more trip whose loads past the
-        // segment's end are skipped and whose products there are left out
-        // (the same additions, in the same order, as one entry at a time)
-        for (; q + (kTileUnroll - 1) * tpr < e; q += kTileUnroll * tpr) {
-            uint32_t cc[kTileUnroll];
-            T vv[kTileUnroll];
-#pragma unroll
-            for (int u = 0; u < kTileUnroll; ++u) cc[u] = off[q + u * tpr];
-#pragma unroll
-            for (int u = 0; u < kTileUnroll; ++u) vv[u] = val[q + u * tpr];
-#pragma unroll
-            for (int u = 0; u < kTileUnroll; ++u)
-                acc = fma((double)vv[u], (double)xs[cc[u]], acc);
-        }
-        if (q < e) {
-            const int k = (int)((e - q + tpr - 1) / tpr);   // 1 .. kTileUnroll - 1
-            uint32_t cc[kTileUnroll - 1];
-            T vv[kTileUnroll - 1];
-#pragma unroll
-            for (int u = 0; u < kTileUnroll - 1; ++u) cc[u] = u < k ? off[q + u * tpr] : 0u;
-#pragma unroll
-            for (int u = 0; u < kTileUnroll - 1; ++u) vv[u] = u < k ? val[q + u * tpr] : T(0);
-#pragma unroll
-            for (int u = 0; u < kTileUnroll - 1; ++u) {
-                const double v = fma((double)vv[u], (double)xs[cc[u]], acc);
-                acc = u < k ? v : acc;
-            }
-        }
-        for (int off = tpr >> 1; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if (t == 0 && act) pp[r] = acc;
-        r = rn;
-        act = actn;
-        qb = nb;
-        qe = ne;
-    }
-}
-
-// A long row's result: its panel partials added in a fixed order, rounded
-// once.  A workgroup takes 32 rows; thread (g, i) adds the partials of panels
-// g, g + 8, g + 16, ... of row i in that order (32 neighbouring rows per
-// load, four of a thread's loads issued before their additions), and the
-// eight group sums are added in group order.  Workgroup `bid` of such a
-// reduction; every thread of the 256 calls it.
-constexpr int kReduceRows = 32, kReduceGroups = 8;
-
-template <typename T>
-__device__ __forceinline__ void tiles_reduce_block(unsigned bid, int64_t n7, int64_t P,
-                                                   const int32_t *__restrict__ rows,
-                                                   const double *__restrict__ part,
-                                                   T *__restrict__ y,
-                                                   double (*gs)[kReduceRows]) {
-    const int i = threadIdx.x % kReduceRows, g = threadIdx.x / kReduceRows;
-    const int64_t r = (int64_t)bid * kReduceRows + i;
-    double acc = 0.0;
-    if (r < n7) {
-        constexpr int G = kReduceGroups;
-        int64_t p = g;
-        for (; p + 3 * G < P; p += 4 * G) {
-            const double v0 = part[p * n7 + r], v1 = part[(p + G) * n7 + r];
-            const double v2 = part[(p + 2 * G) * n7 + r], v3 = part[(p + 3 * G) * n7 + r];
-            acc += v0;
-            acc += v1;
-            acc += v2;
-            acc += v3;
-        }
-        for (; p < P; p += G) acc += part[p * n7 + r];
-    }
-    gs[g][i] = acc;
-    __syncthreads();
-    if (g == 0 && r < n7) {
-        double s = gs[0][i];
-#pragma unroll
-        for (int k = 1; k < kReduceGroups; ++k) s += gs[k][i];
-        y[rows[r]] = (T)s;
-    }
+    __shared__ TileLds lds;
+    tile_block<T, NT>(a, blockIdx.x, smem, lds);
 }
 
 template <typename T>
@@ -630,7 +480,7 @@ __global__ __launch_bounds__(kReduceRows * kReduceGroups) void k_long_tiles_redu
     int64_t n7, int64_t P, const int32_t *__restrict__ rows, const double *__restrict__ part,
     T *__restrict__ y) {
     __shared__ double gs[kReduceGroups][kReduceRows];
-    tiles_reduce_block<T>(blockIdx.x, n7, P, rows, part, y, gs);
+    tiles_reduce_block<T>(blockIdx.x, threadIdx.x, n7, P, rows, part, y, gs);
 }
 
 // The short rows of a binned-CSR plan whose long rows are in tiles, launched
@@ -649,7 +499,7 @@ __global__ __launch_bounds__(kAdaptBlock) void k_csr_adaptive_tiles(
     __shared__ double sp[kAdaptBlock / kWave];
     __shared__ double gs[kReduceGroups][kReduceRows];
     if (blockIdx.x < rg) {
-        tiles_reduce_block<T>(blockIdx.x, n7, P, lrows, part, y, gs);
+        tiles_reduce_block<T>(blockIdx.x, threadIdx.x, n7, P, lrows, part, y, gs);
         return;
     }
     adaptive_block<T, NT, PK>(a, blockIdx.x - rg, rows, rp, col, val, x, y, sp);
@@ -679,27 +529,128 @@ __global__ __launch_bounds__(256) void k_long_tile_seg(int64_t n7, int64_t P, in
     seg[i] = (int32_t)lo;
 }
 
-// Packing of the long rows' entries for the tiles: entry e of row rows[r],
-// in panel p = col / W, goes to pk[kb[2r] + p kb[2r+1]] + (e - seg[p n7 +
-// r]) with its column as col - p W (16 bits) and its value's bits.
-// Workgroups take rows in turn, threads the row's entries.
-template <typename U>
-__global__ __launch_bounds__(256) void k_long_tile_pack(
-    int64_t n7, int32_t W, const int32_t *__restrict__ rows, const int32_t *__restrict__ rp,
-    const int32_t *__restrict__ col, const U *__restrict__ val, const int32_t *__restrict__ seg,
-    const int32_t *__restrict__ kb, const int32_t *__restrict__ pk, uint16_t *__restrict__ off,
-    U *__restrict__ pval) {
-    for (int64_t r = blockIdx.x; r < n7; r += gridDim.x) {
-        const int32_t row = rows[r];
-        const int64_t k0 = kb[2 * r], ks = kb[2 * r + 1];
-        const int64_t e1 = rp[row + 1];
-        for (int64_t e = rp[row] + threadIdx.x; e < e1; e += blockDim.x) {
-            const int32_t c = col[e];
-            const int64_t p = c / W;
-            const int64_t dst = (int64_t)pk[k0 + p * ks] + (e - seg[p * n7 + r]);
-            off[dst] = (uint16_t)(c - p * W);
-            pval[dst] = val[e];
+// Rows and entries of the tiles' row blocks: block b holds the long rows
+// whose entries (lpos, scanned lengths) start in [b step, (b + 1) step).
+__global__ __launch_bounds__(256) void k_tile_blocks(int64_t n7, int64_t nb, int64_t step,
+                                                     const int32_t *__restrict__ lpos,
+                                                     TileBlock *__restrict__ blocks) {
+    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (b >= nb) return;
+    int64_t r[2];
+    for (int k = 0; k < 2; ++k) {
+        int64_t lo = 0, hi = n7;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (lpos[mid] < (b + k) * step)
+                lo = mid + 1;
+            else
+                hi = mid;
         }
+        r[k] = lo;
+    }
+    blocks[b] = TileBlock{(int32_t)r[0], (int32_t)(r[1] - r[0])};
+}
+
+// Wave units of tile (b, p), one wave per tile.
+template <int UNIT>
+__global__ __launch_bounds__(256) void k_tile_count(int64_t n7, int64_t nb, int64_t P,
+                                                    const TileBlock *__restrict__ blocks,
+                                                    const int32_t *__restrict__ seg,
+                                                    int32_t *__restrict__ cnt) {
+    const int64_t w = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (w >= nb * P) return;
+    const int64_t b = w / P, p = w - b * P;
+    const int32_t *s0 = seg + p * n7 + blocks[b].row0, *s1 = s0 + n7;
+    int64_t sum = 0;
+    for (int i = lane; i < blocks[b].rows; i += kWave) sum += max(1, s1[i] - s0[i]);
+    for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (lane == 0) cnt[w] = (int32_t)((sum + UNIT - 1) / UNIT);
+}
+
+// The entries of tile (b, p) in the kernel's order; row starts into the low
+// halves of meta (zero before), padding after the last row starting a row
+// past the block's.
+template <typename U, int PER>
+__global__ __launch_bounds__(1024) void k_tile_fill(
+    int64_t n7, int64_t P, int32_t W, int lg, const int32_t *__restrict__ rows,
+    const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const U *__restrict__ val, const int32_t *__restrict__ seg,
+    const TileBlock *__restrict__ blocks, const int32_t *__restrict__ start,
+    uint32_t *__restrict__ meta, uint16_t *__restrict__ off, U *__restrict__ oval) {
+    constexpr int G = 16 / (int)sizeof(U), SV = 8, UNIT = kWave * PER;
+    __shared__ int scan[1024], at[1024];
+    const int t = threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x % P, b = (int64_t)blockIdx.x / P;
+    const int64_t u0 = start[blockIdx.x], u1 = start[blockIdx.x + 1];
+    const TileBlock blk = blocks[b];
+    const int32_t *s0 = seg + p * n7 + blk.row0, *s1 = s0 + n7;
+    const int lanes = 1 << lg, lane = t & (lanes - 1);
+    // entry i of the tile: wave unit, lane and place in the lane
+    auto put = [&](int64_t i, uint16_t o, U v) {
+        const int64_t u = u0 + i / UNIT;
+        const int l = (int)(i % UNIT) / PER, j = (int)(i % PER);
+        off[((u * (PER / SV) + j / SV) * kWave + l) * SV + j % SV] = o;
+        oval[((u * (PER / G) + j / G) * kWave + l) * G + j % G] = v;
+    };
+    auto mark = [&](int64_t i) {
+        atomicOr(&meta[(u0 + i / UNIT) * kWave + (i % UNIT) / PER], 1u << (i % PER));
+    };
+    int64_t base = 0;
+    for (int r0 = 0; r0 < blk.rows; r0 += 1024) {
+        const int r = r0 + t;
+        const int c = r < blk.rows ? max(1, s1[r] - s0[r]) : 0;
+        scan[t] = c;
+        __syncthreads();
+        for (int o = 1; o < 1024; o <<= 1) {
+            const int a = t >= o ? scan[t - o] : 0;
+            __syncthreads();
+            scan[t] += a;
+            __syncthreads();
+        }
+        at[t] = scan[t] - c;
+        const int total = scan[1023];
+        __syncthreads();
+        const int nr = min(1024, blk.rows - r0);
+        for (int i = t >> lg; i < nr; i += 1024 >> lg) {
+            const int32_t e0 = s0[r0 + i], e1 = s1[r0 + i];
+            const int64_t k = base + at[i];
+            if (lane == 0) {
+                mark(k);
+                if (e0 == e1) put(k, kTileEmpty<U>, U(0));
+            }
+            for (int32_t e = e0 + lane; e < e1; e += lanes)
+                put(k + (e - e0), (uint16_t)(col[e] - p * W), val[e]);
+        }
+        base += total;
+        __syncthreads();
+    }
+    const int64_t end = (u1 - u0) * UNIT;
+    for (int64_t i = base + t; i < end; i += 1024) put(i, kTileEmpty<U>, U(0));
+    if (t == 0 && base < end) mark(base);
+}
+
+// Rows started before each thread of a pass (kTileThreads / 64 wave units),
+// into the high halves of meta.
+__global__ __launch_bounds__(kTileThreads) void k_tile_ranks(const int32_t *__restrict__ start,
+                                                             uint32_t *__restrict__ meta) {
+    __shared__ int scan[kTileThreads];
+    const int t = threadIdx.x;
+    const int64_t m0 = (int64_t)start[blockIdx.x] * kWave;
+    const int64_t m1 = (int64_t)start[blockIdx.x + 1] * kWave;
+    for (int64_t m = m0; m < m1; m += kTileThreads) {
+        const uint32_t w = m + t < m1 ? meta[m + t] & 0xFFFFu : 0u;
+        const int c = __popc(w);
+        scan[t] = c;
+        __syncthreads();
+        for (int o = 1; o < kTileThreads; o <<= 1) {
+            const int a = t >= o ? scan[t - o] : 0;
+            __syncthreads();
+            scan[t] += a;
+            __syncthreads();
+        }
+        if (m + t < m1) meta[m + t] = w | (uint32_t)(scan[t] - c) << 16;
+        __syncthreads();
     }
 }
 
@@ -1218,10 +1169,14 @@ int64_t long_tile_width(int elt) { return kTileBytes / elt; }
 
 spmv_status long_tiles_prepare() {
     // the tile kernels use more than the default 64 KB of dynamic LDS
-    SMAT_HIP(hipFuncSetAttribute((const void *)k_long_tiles<double>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, kTileBytes));
-    SMAT_HIP(hipFuncSetAttribute((const void *)k_long_tiles<float>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, kTileBytes));
+#define ATTR(T, NT)                                                                        \
+    SMAT_HIP(hipFuncSetAttribute((const void *)(k_long_tiles<T, NT>),                      \
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds))
+    ATTR(double, false);
+    ATTR(double, true);
+    ATTR(float, false);
+    ATTR(float, true);
+#undef ATTR
     return SPMV_OK;
 }
 
@@ -1235,59 +1190,71 @@ spmv_status launch_long_tile_seg(int64_t n7, int64_t P, int64_t W, const int32_t
     return SPMV_OK;
 }
 
-spmv_status launch_long_tile_pack(int64_t n7, int64_t P, int64_t W, const int32_t *rows,
-                                  const int32_t *rp, const int32_t *col, const void *val, int elt,
-                                  const int32_t *seg, const int32_t *kb, const int32_t *pk,
-                                  uint16_t *off, void *pval, hipStream_t s) {
-    if (n7 == 0) return SPMV_OK;
-    if (W < 1 || W > 65536 || P < 1 || (elt != 4 && elt != 8)) {
-        set_error("long-row tiles: panel width %lld beyond 16-bit offsets", (long long)W);
-        return SPMV_EINVAL;
-    }
-    const unsigned grid = (unsigned)std::min<int64_t>(n7, 4096);
-    if (elt == 8)
-        k_long_tile_pack<uint64_t><<<grid, 256, 0, s>>>(n7, (int32_t)W, rows, rp, col,
-                                                        (const uint64_t *)val, seg, kb, pk, off,
-                                                        (uint64_t *)pval);
-    else
-        k_long_tile_pack<uint32_t><<<grid, 256, 0, s>>>(n7, (int32_t)W, rows, rp, col,
-                                                        (const uint32_t *)val, seg, kb, pk, off,
-                                                        (uint32_t *)pval);
-    SMAT_LAUNCHED("long_tile_pack");
+int long_tile_per(int elt) { return elt == 8 ? TileShape<double>::PER : TileShape<float>::PER; }
+
+spmv_status launch_tile_blocks(int64_t n7, int64_t nb, int64_t step, const int32_t *lpos,
+                               TileBlock *blocks, hipStream_t s) {
+    k_tile_blocks<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(n7, nb, step, lpos, blocks);
+    SMAT_LAUNCHED("tile_blocks");
     return SPMV_OK;
 }
 
-spmv_status run_long_tiles(int elt, int64_t n7, int64_t P, int64_t nblocks,
-                           const int32_t *blocks, const int32_t *pk, const int32_t *rows,
-                           const uint16_t *off, const void *val, const void *x, int64_t n,
-                           double *part, void *y, hipStream_t s, bool reduce) {
-    if (n7 == 0) return SPMV_OK;
-    if (P < 1 || P > 65535 || nblocks < 1 || nblocks > INT_MAX || (elt != 4 && elt != 8)) {
-        set_error("long-row tiles: %lld panels, %lld row blocks", (long long)P,
-                  (long long)nblocks);
-        return SPMV_EINVAL;
-    }
-    const int64_t W = kTileBytes / elt;
-    if (P * nblocks > INT_MAX) {
-        set_error("long-row tiles: %lld workgroups", (long long)(P * nblocks));
-        return SPMV_EINVAL;
-    }
-    const unsigned grid = (unsigned)(P * nblocks);
-    const unsigned rg = (unsigned)((n7 + kReduceRows - 1) / kReduceRows);
+spmv_status launch_tile_count(int elt, int64_t n7, int64_t nb, int64_t P, const TileBlock *blocks,
+                              const int32_t *seg, int32_t *cnt, hipStream_t s) {
+    const unsigned g = (unsigned)((nb * P + 3) / 4);
     if (elt == 8)
-        k_long_tiles<double><<<grid, kTileThreads, kTileBytes, s>>>(
-            n7, W, P, blocks, pk, off, (const double *)val, (const double *)x, n, part);
+        k_tile_count<kWave * TileShape<double>::PER><<<g, 256, 0, s>>>(n7, nb, P, blocks, seg, cnt);
     else
-        k_long_tiles<float><<<grid, kTileThreads, kTileBytes, s>>>(
-            n7, W, P, blocks, pk, off, (const float *)val, (const float *)x, n, part);
+        k_tile_count<kWave * TileShape<float>::PER><<<g, 256, 0, s>>>(n7, nb, P, blocks, seg, cnt);
+    SMAT_LAUNCHED("tile_count");
+    return SPMV_OK;
+}
+
+spmv_status launch_tile_fill(int elt, int64_t n7, int64_t nb, int64_t P, int lg,
+                             const int32_t *rows, const int32_t *rp, const int32_t *col,
+                             const void *val, const int32_t *seg, const TileBlock *blocks,
+                             const int32_t *start, uint32_t *meta, uint16_t *off, void *oval,
+                             hipStream_t s) {
+    const unsigned g = (unsigned)(nb * P);
+    const int32_t W = kTileBytes / elt;
+    if (elt == 8)
+        k_tile_fill<uint64_t, TileShape<double>::PER><<<g, 1024, 0, s>>>(
+            n7, P, W, lg, rows, rp, col, (const uint64_t *)val, seg, blocks, start, meta, off,
+            (uint64_t *)oval);
+    else
+        k_tile_fill<uint32_t, TileShape<float>::PER><<<g, 1024, 0, s>>>(
+            n7, P, W, lg, rows, rp, col, (const uint32_t *)val, seg, blocks, start, meta, off,
+            (uint32_t *)oval);
+    SMAT_LAUNCHED("tile_fill");
+    k_tile_ranks<<<g, kTileThreads, 0, s>>>(start, meta);
+    SMAT_LAUNCHED("tile_ranks");
+    return SPMV_OK;
+}
+
+spmv_status run_long_tiles(int elt, const TileRun &t, const void *x, int64_t n, void *y,
+                           hipStream_t s, bool reduce) {
+    if (t.n7 == 0) return SPMV_OK;
+    SMAT_TILES_OK(t, elt);
+    const unsigned grid = (unsigned)(t.P * t.nblocks);
+    const unsigned rg = (unsigned)((t.n7 + kReduceRows - 1) / kReduceRows);
+#define TILES(T, NT)                                                                           \
+    k_long_tiles<T, NT><<<grid, kTileThreads, kTileLds, s>>>(                                \
+        TileArgs<T>{t.n7, t.P, t.blocks, t.start, t.meta, t.off, (const T *)t.val, (const T *)x, \
+                    n, t.part})
+    if (elt == 8) {
+        if (t.nt) TILES(double, true); else TILES(double, false);
+    } else {
+        if (t.nt) TILES(float, true); else TILES(float, false);
+    }
+#undef TILES
     SMAT_LAUNCHED("long_tiles");
     if (!reduce) return SPMV_OK;
     if (elt == 8)
-        k_long_tiles_reduce<double><<<rg, kReduceRows * kReduceGroups, 0, s>>>(n7, P, rows, part,
-                                                                              (double *)y);
+        k_long_tiles_reduce<double><<<rg, kReduceRows * kReduceGroups, 0, s>>>(
+            t.n7, t.P, t.rows, t.part, (double *)y);
     else
-        k_long_tiles_reduce<float><<<rg, kReduceRows * kReduceGroups, 0, s>>>(n7, P, rows, part,
-                                                                             (float *)y);
+        k_long_tiles_reduce<float><<<rg, kReduceRows * kReduceGroups, 0, s>>>(
+            t.n7, t.P, t.rows, t.part, (float *)y);
     SMAT_LAUNCHED("long_tiles_reduce");
     return SPMV_OK;
 }

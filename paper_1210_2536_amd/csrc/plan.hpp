@@ -114,9 +114,9 @@ struct Variant {
     AdaptiveLaunch arest{};
     Dev long_rows;   // the long rows, longest first
     // long rows by tiles (x panel per workgroup) instead of x chunks
-    bool long_tiles = false;
+    bool long_tiles = false, tile_nt = false;
     int64_t tile_P = 0, tile_nb = 0;
-    Dev tile_seg, tile_blocks, tile_part, tile_off, tile_pk, tile_val;
+    Dev tile_blocks, tile_start, tile_meta, tile_part, tile_off, tile_val;
     // column panels in two steps: rows of at most ex_lmax entries
     bool expand = false;
     int ex_P = 0, ex_stride = 0;
@@ -133,8 +133,8 @@ struct Variant {
                bin_rows.bytes + bin_scratch.bytes + split_segs.bytes + split_partials.bytes +
                split_begin.bytes + split_rows.bytes + prow.bytes + pcol.bytes + pval.bytes +
                ppart.bytes + brp.bytes + bcol.bytes + bval.bytes + bpres.bytes + long_rows.bytes +
-               tile_seg.bytes + tile_blocks.bytes + tile_part.bytes + tile_off.bytes +
-               tile_pk.bytes + tile_val.bytes + binned_rp.bytes + binned_col.bytes +
+               tile_blocks.bytes + tile_start.bytes + tile_meta.bytes + tile_part.bytes +
+               tile_off.bytes + tile_val.bytes + binned_rp.bytes + binned_col.bytes +
                binned_val.bytes + ex_rp.bytes + ex_off.bytes + ex_xe.bytes + ex_chunks.bytes +
                ex_blocks.bytes + ex_meta.bytes + ex_slot.bytes + ex_val.bytes + ex_piece.bytes +
                ex_starts.bytes;

@@ -321,6 +321,27 @@ __device__ __forceinline__ void dia_tile_direct(int64_t r0, int64_t m, int64_t n
     }
 }
 
+// Row sums over threads that take consecutive entries whatever their rows:
+// `acc` is the thread's sum of the row still open at its end (of all its
+// entries if no row starts in it), `bal` the ballot of the threads in which a
+// row starts.  Returns what the wave's earlier threads carry into the row open
+// at this thread's start; *tail (last lane) is the sum of the row open at the
+// wave's end.
+__device__ __forceinline__ double wave_carry(double acc, unsigned long long bal, int lane,
+                                             double *tail) {
+    const unsigned long long upto = bal & (~0ull >> (kWave - 1 - lane));
+    const int start = upto ? 63 - __clzll(upto) : 0;
+    double v = acc;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const double u = __shfl_up(v, off, kWave);
+        if (lane - off >= start) v += u;
+    }
+    *tail = v;
+    const double carry = __shfl_up(v, 1, kWave);
+    return lane == 0 ? 0.0 : carry;
+}
+
 // ---------------------------------------------------------------- BCSR 4x4
 // Block row R (rows 4R .. 4R+3) by L lanes; every lane of the wave must
 // call (the lane sums are added by shuffles), R >= mb contributing nothing.

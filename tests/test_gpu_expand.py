@@ -8,7 +8,7 @@ from oracle import spmv as O
 
 pytestmark = pytest.mark.gpu
 
-PANEL = {np.float32: 20480, np.float64: 10240}    # columns of an 80 KiB panel
+PANEL = {np.float32: 20352, np.float64: 10176}    # columns of a panel (81408 bytes of x)
 BLOCK = {np.float32: 16384, np.float64: 8192}     # entries of a row block
 
 
