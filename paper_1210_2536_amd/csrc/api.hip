@@ -117,6 +117,7 @@ struct FeatureWork {
     Dev scratch;   // RowStats + EntryStats + DiagStats + flags + fit sums
     Dev row_hist;
     Dev diag_hist; // m + n - 1 bins; later the diagonal -> slot map
+    Dev diag_maps; // bitmap census (none in allocation-free mode)
     bool census = false;       // the census was taken (DIA could be feasible)
     bool census_done = false;  // the census question is settled
     // Allocation-free mode: the three buffers are carved out of a device
@@ -167,6 +168,7 @@ struct Scratch {
     DiagStats ds;
     uint32_t flags;    // row_ptr check
     uint32_t flags2;   // column checks
+    uint32_t spill;    // the census left its table for bitmaps
     double fit[5];
 };
 static_assert(sizeof(Scratch) <= FeatureArena::kDiagOffset, "scratch block fits its slot");
@@ -227,6 +229,26 @@ void set_census(spmv_features &F, const DiagStats &ds, int64_t m, int64_t nnz, F
     F.dia_feasible = (__int128)F.ndiags * m <= (__int128)20 * nnz;
 }
 
+// The diagonal census with the 4x4 block count or without: through tables,
+// and where those spill through bitmaps.  gated: only if the checks passed
+// and DIA can still be feasible.
+spmv_status launch_census(const spmv_csr &A, hipStream_t s, FeatureWork &W, Scratch *d,
+                          bool blocks, bool gated) {
+    const int64_t m = A.m, n = A.n, nnz = A.nnz;
+    SMAT_TRY(W.take(1, sizeof(unsigned) * (size_t)(m + n - 1)));
+    SMAT_HIP(hipMemsetAsync(W.diag_hist.p, 0, W.diag_hist.bytes, s));
+    size_t maps = W.arena ? 0 : diag_bitmap_bytes(m, n, nnz);
+    if (maps && W.diag_maps.alloc(maps) != SPMV_OK) maps = 0;   // the tables alone, slower
+    uint32_t *spill = maps ? &d->spill : nullptr;
+    unsigned *hist = W.diag_hist.as<unsigned>();
+    SMAT_TRY(launch_entry_stats(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->es, hist, blocks, s,
+                                gated ? &d->flags : nullptr, gated ? &d->rs : nullptr, spill));
+    if (maps)
+        SMAT_TRY(launch_diag_bitmap(m, n, nnz, A.row_ptr_dev, A.col_dev, spill, W.diag_maps.p,
+                                    hist, s));
+    return launch_diag_stats(m, n, hist, &d->ds, s, spill, W.diag_maps.p);
+}
+
 spmv_status extract_rows(const spmv_csr &A, hipStream_t s, spmv_features &F, FeatureWork &W) {
     const int64_t m = A.m, n = A.n, nnz = A.nnz;
     SMAT_TRY(W.take(0, sizeof(Scratch)));
@@ -235,23 +257,15 @@ spmv_status extract_rows(const spmv_csr &A, hipStream_t s, spmv_features &F, Fea
     k_init_scratch<<<1, 64, 0, s>>>(d);
     SMAT_LAUNCHED("init_scratch");
     // the row_ptr check, the column checks (with the bandwidth) and the row
-    // pass share one synchronisation: the column and row passes stay in
-    // bounds whatever row_ptr holds, and their results are only used when
-    // the row_ptr check passes
-    SMAT_TRY(launch_validate_rows(m, nnz, A.row_ptr_dev, &d->flags, s));
-    SMAT_TRY(launch_validate_entries(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->flags2,
-                                     &d->es.bandwidth, s));
-    SMAT_TRY(launch_row_stats(m, A.row_ptr_dev, &d->rs, s));
+    // pass in one launch: the column and row passes stay in bounds whatever
+    // row_ptr holds, and their results are only used when the row_ptr check
+    // passes
+    SMAT_TRY(launch_check(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->flags, &d->flags2, &d->rs,
+                          &d->es.bandwidth, s));
     // small matrices: the census too, run on the device only if the checks
     // pass and DIA can still be feasible
     const bool with_census = nnz > 0 && m + n - 1 <= kCensusWithChecksBins;
-    if (with_census) {
-        SMAT_TRY(W.take(1, sizeof(unsigned) * (size_t)(m + n - 1)));
-        SMAT_HIP(hipMemsetAsync(W.diag_hist.p, 0, W.diag_hist.bytes, s));
-        SMAT_TRY(launch_entry_stats(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->es,
-                                    W.diag_hist.as<unsigned>(), false, s, &d->flags, &d->rs));
-        SMAT_TRY(launch_diag_stats(m, n, W.diag_hist.as<unsigned>(), &d->ds, s));
-    }
+    if (with_census) SMAT_TRY(launch_census(A, s, W, d, false, true));
     SMAT_TRY(read_scratch(d, h, s, W.arena == nullptr));
     if (h.flags) {
         set_error("invalid CSR row_ptr (flags 0x%x: %s%s%s)", h.flags,
@@ -289,6 +303,7 @@ spmv_status extract_rows(const spmv_csr &A, hipStream_t s, spmv_features &F, Fea
     F.blocks4 = -1;
     F.block_fill = -1.0;
     F.R = std::numeric_limits<double>::quiet_NaN();
+    W.diag_maps.release();
     if (with_census) {
         W.census_done = true;
         if (F.ell_feasible) set_census(F, h.ds, m, nnz, W);
@@ -312,16 +327,13 @@ spmv_status extract_entries(const spmv_csr &A, hipStream_t s, spmv_features &F, 
     // ---- entry pass: diagonal census (while DIA may still be feasible,
     // since Ndiags >= max_RD) and / or the 4x4 block count
     const bool census = (what & kStageCensus) && !W.census_done && F.ell_feasible && nnz > 0;
-    if (census) {
-        SMAT_TRY(W.take(1, sizeof(unsigned) * (size_t)(m + n - 1)));
-        SMAT_HIP(hipMemsetAsync(W.diag_hist.p, 0, W.diag_hist.bytes, s));
-    }
-    if (census || rest)
-        SMAT_TRY(launch_entry_stats(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->es,
-                                    census ? W.diag_hist.as<unsigned>() : nullptr, rest, s));
-    if (census) SMAT_TRY(launch_diag_stats(m, n, W.diag_hist.as<unsigned>(), &d->ds, s));
+    if (census)
+        SMAT_TRY(launch_census(A, s, W, d, rest, false));
+    else if (rest)
+        SMAT_TRY(launch_entry_stats(m, n, nnz, A.row_ptr_dev, A.col_dev, &d->es, nullptr, true, s));
     Scratch h{};
     SMAT_TRY(read_scratch(d, h, s, W.arena == nullptr));
+    W.diag_maps.release();
     if (rest) {
         F.blocks4 = (int64_t)h.es.blocks4;
         F.block_fill = F.blocks4 ? (double)nnz / (16.0 * (double)F.blocks4) : 0.0;

@@ -53,12 +53,11 @@ struct DiagStats {
     unsigned long long ndiags, ntrue;
 };
 
-spmv_status launch_validate_rows(int64_t m, int64_t nnz, const int32_t *rp, uint32_t *flags,
-                                 hipStream_t s);
-spmv_status launch_validate_entries(int64_t m, int64_t n, int64_t nnz, const int32_t *rp,
-                                    const int32_t *col, uint32_t *flags, int *bandwidth,
-                                    hipStream_t s);
-spmv_status launch_row_stats(int64_t m, const int32_t *rp, RowStats *out, hipStream_t s);
+// Row_ptr checks into *flags, column checks into *flags2, row statistics and
+// the bandwidth (meaningful when both stay 0), all accumulated.
+spmv_status launch_check(int64_t m, int64_t n, int64_t nnz, const int32_t *rp, const int32_t *col,
+                         uint32_t *flags, uint32_t *flags2, RowStats *rs, int *bandwidth,
+                         hipStream_t s);
 spmv_status launch_row_hist(int64_t m, const int32_t *rp, int max_rd, unsigned int *hist,
                             hipStream_t s);
 spmv_status launch_powerlaw_fit(const unsigned int *hist, int max_rd, int64_t m, double *sums,
@@ -66,9 +65,20 @@ spmv_status launch_powerlaw_fit(const unsigned int *hist, int max_rd, int64_t m,
 spmv_status launch_entry_stats(int64_t m, int64_t n, int64_t nnz, const int32_t *rp,
                                const int32_t *col, EntryStats *out, unsigned int *diag_hist,
                                bool blocks, hipStream_t s, const uint32_t *gate = nullptr,
-                               const RowStats *gate_rs = nullptr);
-spmv_status launch_diag_stats(int64_t m, int64_t n, const unsigned int *diag_hist, DiagStats *out,
-                              hipStream_t s);
+                               const RowStats *gate_rs = nullptr, uint32_t *spill = nullptr);
+// The census by bitmaps, run where launch_entry_stats set *spill (nothing
+// otherwise): diag_bitmap_bytes of workspace (0: not for this matrix -- the
+// bitmap of m + n - 1 diagonals does not fit LDS, or too few entries to
+// matter), passed on to launch_diag_stats.
+constexpr int kDiagBitmapLds = 152 * 1024;
+constexpr int64_t kDiagBitmapMinNnz = int64_t(1) << 17;
+size_t diag_bitmap_bytes(int64_t m, int64_t n, int64_t nnz);
+spmv_status launch_diag_bitmap(int64_t m, int64_t n, int64_t nnz, const int32_t *rp,
+                               const int32_t *col, const uint32_t *spill, void *work,
+                               unsigned int *diag_hist, hipStream_t s);
+spmv_status launch_diag_stats(int64_t m, int64_t n, unsigned int *diag_hist, DiagStats *out,
+                              hipStream_t s, const uint32_t *spill = nullptr,
+                              const void *work = nullptr);
 spmv_status launch_diag_compact(int64_t m, int64_t n, unsigned int *diag_hist, int32_t *offsets,
                                 unsigned int *block_scratch, hipStream_t s);
 
