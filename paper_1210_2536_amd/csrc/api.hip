@@ -977,7 +977,6 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         SMAT_TRY(V.bcol.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, nb)));
         SMAT_TRY(V.bval.alloc((size_t)elt * 16 * (size_t)std::max<int64_t>(1, nb)));
         SMAT_TRY(V.bpres.alloc(sizeof(uint32_t) * (size_t)((nb + 1) / 2 + 1)));
-        SMAT_HIP(hipMemsetAsync(V.bval.p, 0, V.bval.bytes, s));
         SMAT_HIP(hipMemsetAsync(V.bpres.p, 0, V.bpres.bytes, s));
         SMAT_TRY(launch_csr_to_bcsr(m, P.rp.as<int32_t>(), P.col.as<int32_t>(), P.val.p, elt,
                                     V.brp.as<int32_t>(), V.bcol.as<int32_t>(), V.bval.p,
@@ -1038,10 +1037,8 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         size_t words = (slots + 31) / 32;
         SMAT_TRY(V.dia_data.alloc((size_t)elt * slots));
         SMAT_TRY(V.dia_present.alloc(sizeof(uint32_t) * words));
-        SMAT_HIP(hipMemsetAsync(V.dia_data.p, 0, V.dia_data.bytes, s));
-        SMAT_HIP(hipMemsetAsync(V.dia_present.p, 0, V.dia_present.bytes, s));
-        SMAT_TRY(launch_csr_to_dia(m, n, P.m_pad, nnz, P.rp.as<int32_t>(), P.col.as<int32_t>(),
-                                   P.val.p, elt, W.diag_hist.as<unsigned>(), V.dia_data.p,
+        SMAT_TRY(launch_csr_to_dia(m, P.m_pad, V.D, P.rp.as<int32_t>(), P.col.as<int32_t>(),
+                                   P.val.p, elt, V.dia_off.as<int32_t>(), V.dia_data.p,
                                    V.dia_present.as<uint32_t>(), s));
         // windows of diagonals whose offsets span at most dia_span
         std::vector<DiaWindow> win;
@@ -1280,7 +1277,8 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             SMAT_HIP(hipStreamSynchronize(s));
             SMAT_TRY(V.binned_col.alloc(sizeof(int32_t) * (size_t)std::max<int32_t>(1, tot)));
             SMAT_TRY(V.binned_val.alloc((size_t)elt * (size_t)std::max<int32_t>(1, tot)));
-            SMAT_TRY(launch_pack_binned(hi, V.bin_rows.as<int32_t>(), P.rp.as<int32_t>(),
+            SMAT_TRY(launch_pack_binned(V.long_tpr ? V.arest : V.alaunch,
+                                        V.bin_rows.as<int32_t>(), P.rp.as<int32_t>(),
                                         P.col.as<int32_t>(), P.val.p, elt, V.binned_rp.as<int32_t>(),
                                         V.binned_col.as<int32_t>(), V.binned_val.p, s));
             SMAT_HIP(hipStreamSynchronize(s));

@@ -88,10 +88,11 @@ spmv_status launch_csr_to_coo(int64_t m, int64_t nnz, const int32_t *rp, int32_t
 spmv_status launch_csr_to_ell(int64_t m, int64_t m_pad, int K, const int32_t *rp,
                               const int32_t *col, const void *val, int elt, int32_t *ecol,
                               void *eval, hipStream_t s);
-spmv_status launch_csr_to_dia(int64_t m, int64_t n, int64_t m_pad, int64_t nnz, const int32_t *rp,
-                              const int32_t *col, const void *val, int elt,
-                              const unsigned int *slot_map, void *data, uint32_t *present,
-                              hipStream_t s);
+// Every slot and presence bit is written (no zero fill beforehand); offs: the
+// D ascending offsets, every diagonal that an entry lies on among them.
+spmv_status launch_csr_to_dia(int64_t m, int64_t m_pad, int D, const int32_t *rp,
+                              const int32_t *col, const void *val, int elt, const int32_t *offs,
+                              void *data, uint32_t *present, hipStream_t s);
 spmv_status launch_coo_to_csr(int64_t m, int64_t nnz, const int32_t *row_idx, int32_t *rp,
                               hipStream_t s);
 spmv_status launch_ell_to_csr(int64_t m, int64_t m_pad, int K, const int32_t *ecol,
@@ -103,8 +104,8 @@ spmv_status launch_dia_to_csr(int64_t m, int64_t n, int64_t m_pad, int D, const 
                               hipStream_t s);
 // 4x4 block CSR (block row R = rows 4R..4R+3): block counts per block row
 // and their exclusive scan (brp, ceil(m/4)+1 entries; scratch as below),
-// then block columns, zero-filled-beforehand values (16 per block,
-// row-major) and 16 presence bits per block; the inverse for round trips.
+// then block columns, values (16 per block, row-major, zeros included) and 16
+// presence bits per block; the inverse for round trips.
 spmv_status launch_bcsr_count(int64_t m, const int32_t *rp, const int32_t *col, int32_t *counts,
                               int32_t *brp, unsigned int *scratch, hipStream_t s);
 spmv_status launch_csr_to_bcsr(int64_t m, const int32_t *rp, const int32_t *col, const void *val,
@@ -159,10 +160,11 @@ spmv_status run_csr_adaptive(int elt, bool nt, bool rest, const AdaptiveLaunch &
 // Copy of the entries of the rows at binned positions [0, hi) in that order:
 // launch_binned_scan fills brp (hi + 1 ints: each position's first entry,
 // then the total; len hi ints and scan hi / 4096 + 2 unsigned of scratch),
-// launch_pack_binned the entries bcol / bval (brp[hi] of them).
+// launch_pack_binned the entries bcol / bval (brp[hi] of them; a: the binned
+// launch over those positions, lane_shift 0).
 spmv_status launch_binned_scan(int64_t hi, const int32_t *rows, const int32_t *rp, int32_t *len,
                                unsigned *scan, int32_t *brp, hipStream_t s);
-spmv_status launch_pack_binned(int64_t hi, const int32_t *rows, const int32_t *rp,
+spmv_status launch_pack_binned(const AdaptiveLaunch &a, const int32_t *rows, const int32_t *rp,
                                const int32_t *col, const void *val, int elt, const int32_t *brp,
                                int32_t *bcol, void *bval, hipStream_t s);
 // Column panels; prow is P x (m+1) position-indexed segment starts.  With

@@ -88,28 +88,34 @@ __global__ __launch_bounds__(kAdaptBlock) void k_csr_adaptive_rest(
     adaptive_block<T, NT, PK>(a, blockIdx.x, rows, rp, col, val, x, y, part);
 }
 
-// The entries of the rows at binned positions [0, hi) copied in that order:
-// brp (hi + 1 entries, filled by an exclusive scan of the row lengths) gives
-// position pos's range in bcol / bval.  One wave per position, lanes
-// striding the row; values are copied as bits.
+// The entries of the rows at binned positions copied in that order, by the
+// workgroups and lane widths of the launch geometry that will read them (a
+// wave per row, whatever its length: 64 us for 100k mostly short rows, so
+// 24): brp, filled by an exclusive scan of the row lengths, gives position
+// pos's range in bcol / bval.  Values are copied as bits.
 template <typename U>
-__global__ __launch_bounds__(256) void k_pack_binned(int64_t hi, const int32_t *__restrict__ rows,
-                                                     const int32_t *__restrict__ rp,
-                                                     const int32_t *__restrict__ col,
-                                                     const U *__restrict__ val,
-                                                     const int32_t *__restrict__ brp,
-                                                     int32_t *__restrict__ bcol,
-                                                     U *__restrict__ bval) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
-    const int lane = threadIdx.x & 63;
-    for (int64_t pos = blockIdx.x * (int64_t)(blockDim.x / 64) + threadIdx.x / 64; pos < hi;
-         pos += waves) {
-        const int32_t row = rows[pos];
-        const int64_t b = rp[row], e = rp[row + 1], d = (int64_t)brp[pos] - b;
-        for (int64_t q = b + lane; q < e; q += 64) {
-            bcol[q + d] = col[q];
-            bval[q + d] = val[q];
-        }
+__global__ __launch_bounds__(kAdaptBlock) void k_pack_binned(AdaptiveLaunch a,
+                                                             const int32_t *__restrict__ rows,
+                                                             const int32_t *__restrict__ rp,
+                                                             const int32_t *__restrict__ col,
+                                                             const U *__restrict__ val,
+                                                             const int32_t *__restrict__ brp,
+                                                             int32_t *__restrict__ bcol,
+                                                             U *__restrict__ bval) {
+    int q = 0;
+    while (q < 7 && blockIdx.x >= a.first[q + 1]) ++q;
+    const int b = 7 - q;
+    const int lg = b == 7 ? 8 : b;   // 256 threads or 1 << b lanes a row
+    const int64_t pos = (int64_t)a.row_begin[b] +
+                        (int64_t)(blockIdx.x - a.first[q]) * (kAdaptBlock >> lg) +
+                        (threadIdx.x >> lg);
+    if (pos >= a.row_begin[b + 1]) return;
+    const int lane = threadIdx.x & ((1 << lg) - 1);
+    const int32_t row = rows[pos];
+    const int64_t e0 = rp[row], e1 = rp[row + 1], d = (int64_t)brp[pos] - e0;
+    for (int64_t e = e0 + lane; e < e1; e += 1 << lg) {
+        bcol[e + d] = col[e];
+        bval[e + d] = val[e];
     }
 }
 
@@ -1123,17 +1129,17 @@ spmv_status launch_binned_scan(int64_t hi, const int32_t *rows, const int32_t *r
     return launch_exclusive_scan_rows(hi, len, brp, scan, s);
 }
 
-spmv_status launch_pack_binned(int64_t hi, const int32_t *rows, const int32_t *rp,
+spmv_status launch_pack_binned(const AdaptiveLaunch &a, const int32_t *rows, const int32_t *rp,
                                const int32_t *col, const void *val, int elt, const int32_t *brp,
                                int32_t *bcol, void *bval, hipStream_t s) {
-    if (hi <= 0) return SPMV_OK;
-    const unsigned grid = (unsigned)std::min<int64_t>((hi + 3) / 4, 65536);
+    const unsigned grid = a.first[8];
+    if (grid == 0) return SPMV_OK;
     if (elt == 8)
-        k_pack_binned<uint64_t><<<grid, 256, 0, s>>>(hi, rows, rp, col, (const uint64_t *)val, brp,
-                                                     bcol, (uint64_t *)bval);
+        k_pack_binned<uint64_t><<<grid, kAdaptBlock, 0, s>>>(
+            a, rows, rp, col, (const uint64_t *)val, brp, bcol, (uint64_t *)bval);
     else
-        k_pack_binned<uint32_t><<<grid, 256, 0, s>>>(hi, rows, rp, col, (const uint32_t *)val, brp,
-                                                     bcol, (uint32_t *)bval);
+        k_pack_binned<uint32_t><<<grid, kAdaptBlock, 0, s>>>(
+            a, rows, rp, col, (const uint32_t *)val, brp, bcol, (uint32_t *)bval);
     SMAT_LAUNCHED("pack_binned");
     return SPMV_OK;
 }
