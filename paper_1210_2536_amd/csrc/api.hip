@@ -103,6 +103,27 @@ __global__ void k_tune_check(int64_t m, const T *__restrict__ y, const T *__rest
     if (!(d <= tol * absrow[i])) atomicOr(bad, 1u);
 }
 
+// The plan's own copy of the matrix, in stream order.  On failure the plan
+// holds what it held before.
+spmv_status own_csr(spmv_plan_s &P, const spmv_csr &A, hipStream_t s) {
+    Dev rp, col, val;
+    SMAT_TRY(rp.alloc(sizeof(int32_t) * (size_t)(A.m + 1)));
+    SMAT_TRY(col.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, A.nnz)));
+    SMAT_TRY(val.alloc((size_t)P.elt * (size_t)std::max<int64_t>(1, A.nnz)));
+    SMAT_HIP(hipMemcpyAsync(rp.p, A.row_ptr_dev, sizeof(int32_t) * (A.m + 1),
+                            hipMemcpyDeviceToDevice, s));
+    if (A.nnz) {
+        SMAT_HIP(hipMemcpyAsync(col.p, A.col_dev, sizeof(int32_t) * A.nnz,
+                                hipMemcpyDeviceToDevice, s));
+        SMAT_HIP(hipMemcpyAsync(val.p, A.val_dev, (size_t)P.elt * A.nnz, hipMemcpyDeviceToDevice,
+                                s));
+    }
+    P.rp.take(rp);
+    P.col.take(col);
+    P.val.take(val);
+    return SPMV_OK;
+}
+
 }  // namespace
 }  // namespace smat
 
@@ -182,30 +203,51 @@ __global__ void k_init_scratch(Scratch *d) {
     if (threadIdx.x == 0) d->rs.min_rd = INT_MAX;
 }
 
-// The scratch read back into pinned host memory (one block per thread, kept
-// for the process), which the copy engine writes directly; NULL if pinned
-// memory is unavailable (a stack copy is used then).
-Scratch *pinned_scratch() {
-    thread_local Scratch *p = nullptr;
+// A block of pinned host memory per thread, kept for the process: the copy
+// engine writes it directly, where a copy to pageable memory is staged by the
+// runtime.  NULL if pinned memory is unavailable.
+constexpr size_t kPinnedBytes = 8192;
+unsigned char *pinned_block() {
+    thread_local void *p = nullptr;
     thread_local bool tried = false;
     if (!tried) {
         tried = true;
-        if (hipHostMalloc(reinterpret_cast<void **>(&p), sizeof(Scratch), hipHostMallocDefault) !=
-            hipSuccess) {
+        if (hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
         }
     }
-    return p;
+    return static_cast<unsigned char *>(p);
+}
+
+// Small device ranges read to the host, and the stream waited for.
+struct HostRead {
+    void *dst;
+    const void *src;
+    size_t bytes;
+};
+spmv_status read_small(std::initializer_list<HostRead> reads, hipStream_t s,
+                       bool pinned_ok = true) {
+    size_t need = 0;
+    for (const HostRead &r : reads) need += (r.bytes + 7) / 8 * 8;
+    unsigned char *pin = pinned_ok && need <= kPinnedBytes ? pinned_block() : nullptr;
+    size_t off = 0;
+    for (const HostRead &r : reads) {
+        SMAT_HIP(hipMemcpyAsync(pin ? pin + off : r.dst, r.src, r.bytes, hipMemcpyDeviceToHost,
+                                s));
+        off += (r.bytes + 7) / 8 * 8;
+    }
+    SMAT_HIP(hipStreamSynchronize(s));
+    off = 0;
+    for (const HostRead &r : reads) {
+        if (pin) std::memcpy(r.dst, pin + off, r.bytes);
+        off += (r.bytes + 7) / 8 * 8;
+    }
+    return SPMV_OK;
 }
 
 spmv_status read_scratch(const Scratch *d, Scratch &h, hipStream_t s, bool pinned_ok = true) {
-    Scratch *pin = pinned_ok ? pinned_scratch() : nullptr;
-    Scratch *dst = pin ? pin : &h;
-    SMAT_HIP(hipMemcpyAsync(dst, d, sizeof(Scratch), hipMemcpyDeviceToHost, s));
-    SMAT_HIP(hipStreamSynchronize(s));
-    if (pin) h = *pin;
-    return SPMV_OK;
+    return read_small({{&h, d, sizeof(Scratch)}}, s, pinned_ok);
 }
 
 // Feature extraction in stages, in the order the format search consumes them
@@ -757,9 +799,7 @@ spmv_status long_row_lengths(const spmv_plan_s &P, int64_t n7, const int32_t *ro
     SMAT_TRY(launch_binned_scan(n7, rows, P.rp.as<int32_t>(), len.as<int32_t>(),
                                 scan.as<unsigned>(), lpos.as<int32_t>(), s));
     int32_t t = 0;
-    SMAT_HIP(hipMemcpyAsync(&t, lpos.as<int32_t>() + n7, sizeof(int32_t), hipMemcpyDeviceToHost,
-                            s));
-    SMAT_HIP(hipStreamSynchronize(s));
+    SMAT_TRY(read_small({{&t, lpos.as<int32_t>() + n7, sizeof(int32_t)}}, s));
     *total = t;
     return SPMV_OK;
 }
@@ -794,9 +834,7 @@ spmv_status build_long_tiles(const spmv_plan_s &P, Variant &V, int64_t n7, const
     SMAT_TRY(launch_exclusive_scan_rows(nb * NP, cnt.as<int32_t>(), V.tile_start.as<int32_t>(),
                                         scan.as<unsigned>(), s));
     int32_t units = 0;
-    SMAT_HIP(hipMemcpyAsync(&units, V.tile_start.as<int32_t>() + nb * NP, sizeof(int32_t),
-                            hipMemcpyDeviceToHost, s));
-    SMAT_HIP(hipStreamSynchronize(s));
+    SMAT_TRY(read_small({{&units, V.tile_start.as<int32_t>() + nb * NP, sizeof(int32_t)}}, s));
     const size_t entries = (size_t)units * kWave * (size_t)long_tile_per(P.elt);
     SMAT_TRY(V.tile_part.alloc(sizeof(double) * (size_t)(NP * n7)));
     SMAT_TRY(V.tile_meta.alloc(sizeof(uint32_t) * (size_t)units * kWave));
@@ -876,9 +914,7 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
                                         scan.as<unsigned>(), s));
     SMAT_HIP(hipMemsetAsync(most.p, 0, sizeof(int), s));
     int32_t total = 0;
-    SMAT_HIP(hipMemcpyAsync(&total, spos.as<int32_t>() + m, sizeof(int32_t),
-                            hipMemcpyDeviceToHost, s));
-    SMAT_HIP(hipStreamSynchronize(s));
+    SMAT_TRY(read_small({{&total, spos.as<int32_t>() + m, sizeof(int32_t)}}, s));
     // a block takes the rows that start within `step` entries, so that the
     // last of them still ends inside the block
     const int64_t longest = std::max<int64_t>(1, std::min<int64_t>(lmax, F.max_rd));
@@ -899,10 +935,8 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     SMAT_TRY(launch_expand_starts(NP, nb, runs.as<int32_t>(), V.ex_starts.as<int32_t>(), s));
     std::vector<int32_t> start(NP + 1);
     int stride = 0;
-    SMAT_HIP(hipMemcpyAsync(start.data(), V.ex_starts.p, sizeof(int32_t) * (NP + 1),
-                            hipMemcpyDeviceToHost, s));
-    SMAT_HIP(hipMemcpyAsync(&stride, most.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    SMAT_HIP(hipStreamSynchronize(s));
+    SMAT_TRY(read_small({{start.data(), V.ex_starts.p, sizeof(int32_t) * (NP + 1)},
+                         {&stride, most.p, sizeof(int)}}, s));
     if (stride > expand_max_pieces()) {
         set_error("expanded panels: %d pieces in a row block", stride);
         return SPMV_EUNSUPPORTED;
@@ -970,9 +1004,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
                                    counts.as<int32_t>(), V.brp.as<int32_t>(), scan.as<unsigned>(),
                                    s));
         int32_t nb = 0;
-        SMAT_HIP(hipMemcpyAsync(&nb, V.brp.as<int32_t>() + mb, sizeof(int32_t),
-                                hipMemcpyDeviceToHost, s));
-        SMAT_HIP(hipStreamSynchronize(s));
+        SMAT_TRY(read_small({{&nb, V.brp.as<int32_t>() + mb, sizeof(int32_t)}}, s));
         V.nblocks = nb;
         SMAT_TRY(V.bcol.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, nb)));
         SMAT_TRY(V.bval.alloc((size_t)elt * 16 * (size_t)std::max<int64_t>(1, nb)));
@@ -1026,9 +1058,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             SMAT_TRY(launch_diag_compact(m, n, W.diag_hist.as<unsigned>(), V.dia_off.as<int32_t>(),
                                          blk.as<unsigned>(), s));
             P.dia_offsets.resize(V.D);
-            SMAT_HIP(hipMemcpyAsync(P.dia_offsets.data(), V.dia_off.p, sizeof(int32_t) * V.D,
-                                    hipMemcpyDeviceToHost, s));
-            SMAT_HIP(hipStreamSynchronize(s));
+            SMAT_TRY(read_small({{P.dia_offsets.data(), V.dia_off.p, sizeof(int32_t) * V.D}}, s));
         } else if (V.D > 0) {
             SMAT_HIP(hipMemcpyAsync(V.dia_off.p, P.dia_offsets.data(), sizeof(int32_t) * V.D,
                                     hipMemcpyHostToDevice, s));
@@ -1103,8 +1133,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             unsigned *offs = blk + (size_t)nblk * kAdaptiveBins;
             SMAT_TRY(launch_bin_rows(m, P.rp.as<int32_t>(), spec, blk, V.bin_rows.as<int32_t>(),
                                      offs, s));
-            SMAT_HIP(hipMemcpyAsync(V.bin_off, offs, sizeof(V.bin_off), hipMemcpyDeviceToHost, s));
-            SMAT_HIP(hipStreamSynchronize(s));
+            SMAT_TRY(read_small({{V.bin_off, offs, sizeof(V.bin_off)}}, s));
             unsigned blocks = 0;
             for (int q = 0; q < 8; ++q) {
                 int b = 7 - q;
@@ -1133,6 +1162,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         SMAT_TRY(bin(wg));
         // split rows: segment table on the host from their row_ptr entries
         int64_t ns = V.bin_off[9] - V.bin_off[8];
+        int64_t binned_nnz = nnz;   // entries of the rows the binned launch keeps
         if (ns > 0) {
             Dev tmp;
             SMAT_TRY(tmp.alloc(sizeof(int64_t) * 2 * ns));
@@ -1148,6 +1178,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             SMAT_HIP(hipStreamSynchronize(s));
             std::vector<int64_t> segs, begin(1, 0);
             for (int64_t r = 0; r < ns; ++r) {
+                binned_nnz -= be[2 * r + 1] - be[2 * r];
                 for (int64_t b = be[2 * r]; b < be[2 * r + 1]; b += kSplitSegment) {
                     segs.push_back(r);
                     segs.push_back(b);
@@ -1222,6 +1253,8 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
                 SMAT_HIP(hipMemcpyAsync(rows.data(), r7, sizeof(int32_t) * n7,
                                         hipMemcpyDeviceToHost, s));
                 SMAT_HIP(hipStreamSynchronize(s));
+                total7 = 0;
+                for (int64_t i = 0; i < n7; ++i) total7 += h[2 * i + 1] - h[2 * i];
                 std::vector<int64_t> ord(n7);
                 for (int64_t i = 0; i < n7; ++i) ord[i] = i;
                 std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
@@ -1249,6 +1282,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
                 V.long_rows.release();
             } else {
                 V.n_long = n7;
+                binned_nnz -= total7;
                 const unsigned b7 = V.alaunch.first[1];  // workgroups of bin 7
                 V.arest = V.alaunch;
                 V.arest.first[0] = 0;
@@ -1271,12 +1305,9 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
             SMAT_TRY(launch_binned_scan(hi, V.bin_rows.as<int32_t>(), P.rp.as<int32_t>(),
                                         len.as<int32_t>(), scan.as<unsigned>(),
                                         V.binned_rp.as<int32_t>(), s));
-            int32_t tot = 0;
-            SMAT_HIP(hipMemcpyAsync(&tot, V.binned_rp.as<int32_t>() + hi, sizeof(int32_t),
-                                    hipMemcpyDeviceToHost, s));
-            SMAT_HIP(hipStreamSynchronize(s));
-            SMAT_TRY(V.binned_col.alloc(sizeof(int32_t) * (size_t)std::max<int32_t>(1, tot)));
-            SMAT_TRY(V.binned_val.alloc((size_t)elt * (size_t)std::max<int32_t>(1, tot)));
+            const int64_t tot = std::max<int64_t>(1, binned_nnz);
+            SMAT_TRY(V.binned_col.alloc(sizeof(int32_t) * (size_t)tot));
+            SMAT_TRY(V.binned_val.alloc((size_t)elt * (size_t)tot));
             SMAT_TRY(launch_pack_binned(V.long_tpr ? V.arest : V.alaunch,
                                         V.bin_rows.as<int32_t>(), P.rp.as<int32_t>(),
                                         P.col.as<int32_t>(), P.val.p, elt, V.binned_rp.as<int32_t>(),
@@ -2206,17 +2237,21 @@ static spmv_status plan_create_impl(const spmv_csr *A, const spmv_plan_opts *opt
     }
     I.features = F;
 
-    // plan-owned CSR copy (every conversion starts from it)
-    SMAT_TRY(P->rp.alloc(sizeof(int32_t) * (size_t)(A->m + 1)));
-    SMAT_TRY(P->col.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, A->nnz)));
-    SMAT_TRY(P->val.alloc((size_t)P->elt * (size_t)std::max<int64_t>(1, A->nnz)));
-    SMAT_HIP(hipMemcpyAsync(P->rp.p, A->row_ptr_dev, sizeof(int32_t) * (A->m + 1),
-                            hipMemcpyDeviceToDevice, s));
-    if (A->nnz) {
-        SMAT_HIP(hipMemcpyAsync(P->col.p, A->col_dev, sizeof(int32_t) * A->nnz,
-                                hipMemcpyDeviceToDevice, s));
-        SMAT_HIP(hipMemcpyAsync(P->val.p, A->val_dev, (size_t)P->elt * A->nnz,
-                                hipMemcpyDeviceToDevice, s));
+    // Every conversion starts from the caller's CSR arrays, which stay valid
+    // until this call returns; only a kernel that reads them on each run gets
+    // a plan-owned copy, once it is chosen.  (Copying first cost 25 us and
+    // three blocks of a 310 us plan of 4.4M float64 entries whose ELL form
+    // dropped them again.)  Arrays off 16-byte boundaries, which the kernels'
+    // wide loads do not expect, are copied first, and so is an empty matrix.
+    const bool aligned = A->nnz > 0 && ((reinterpret_cast<uintptr_t>(A->row_ptr_dev) |
+                                         reinterpret_cast<uintptr_t>(A->col_dev) |
+                                         reinterpret_cast<uintptr_t>(A->val_dev)) & 15u) == 0;
+    if (aligned) {
+        P->rp.borrow(const_cast<int32_t *>(A->row_ptr_dev), sizeof(int32_t) * (size_t)(A->m + 1));
+        P->col.borrow(const_cast<int32_t *>(A->col_dev), sizeof(int32_t) * (size_t)A->nnz);
+        P->val.borrow(const_cast<void *>(A->val_dev), (size_t)P->elt * (size_t)A->nnz);
+    } else {
+        SMAT_TRY(own_csr(*P, *A, s));
     }
     P->has_csr = true;
 
@@ -2255,15 +2290,23 @@ static spmv_status plan_create_impl(const spmv_csr *A, const spmv_plan_opts *opt
         spmv_selector_s *sel = opts.model;
         float raw[12];
         raw_features(F, A->dtype, raw);
-        Dev draw, dsc;
-        SMAT_TRY(draw.alloc(sizeof(raw)));
-        SMAT_TRY(dsc.alloc(sizeof(float) * SPMV_K_COUNT));
-        SMAT_HIP(hipMemcpyAsync(draw.p, raw, sizeof(raw), hipMemcpyHostToDevice, s));
-        SMAT_TRY(run_mlp_infer(sel->params.as<float>(), sel->n_out, sel->mean.as<float>(),
-                               sel->stdv.as<float>(), draw.as<float>(), 1, dsc.as<float>(), s));
         float sc[SPMV_K_COUNT];
-        SMAT_HIP(hipMemcpyAsync(sc, dsc.p, sizeof(sc), hipMemcpyDeviceToHost, s));
+        // one row: read from and written to pinned memory by the kernel itself
+        float *pin = reinterpret_cast<float *>(pinned_block());
+        Dev draw;
+        if (pin) {
+            std::memcpy(pin, raw, sizeof(raw));
+        } else {
+            SMAT_TRY(draw.alloc(sizeof(raw) + sizeof(sc)));
+            SMAT_HIP(hipMemcpyAsync(draw.p, raw, sizeof(raw), hipMemcpyHostToDevice, s));
+        }
+        float *row = pin ? pin : draw.as<float>();
+        SMAT_TRY(run_mlp_infer(sel->params.as<float>(), sel->n_out, sel->mean.as<float>(),
+                               sel->stdv.as<float>(), row, 1, row + 12, s));
+        if (!pin)
+            SMAT_HIP(hipMemcpyAsync(sc, row + 12, sizeof(sc), hipMemcpyDeviceToHost, s));
         SMAT_HIP(hipStreamSynchronize(s));
+        if (pin) std::memcpy(sc, pin + 12, sizeof(sc));
         std::vector<std::pair<float, int>> order;
         for (int k = 0; k < SPMV_K_COUNT; ++k) {
             I.mlp_scores[k] = sc[k];
@@ -2346,6 +2389,18 @@ static spmv_status plan_create_impl(const spmv_csr *A, const spmv_plan_opts *opt
         SMAT_HIP(hipStreamSynchronize(s));
         I.t_tune_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() -
                                                                 t_tune0).count();
+    }
+    if (needs_csr(*P->var) && P->rp.borrowed) {
+        spmv_status st = own_csr(*P, *A, s);
+        if (st == SPMV_ENOMEM && mode != SPMV_SELECT_FORCED && chosen != SPMV_K_CSR_VECTOR) {
+            // no room beside the chosen kernel's own arrays: CSR alone
+            SMAT_HIP(hipStreamSynchronize(s));
+            P->var = std::make_unique<Variant>();
+            chosen = SPMV_K_CSR_VECTOR;
+            SMAT_TRY(build_variant(*P, F, W, chosen, prm_base, s, *P->var));
+            st = own_csr(*P, *A, s);
+        }
+        SMAT_TRY(st);
     }
     SMAT_HIP(hipStreamSynchronize(s));
     W.diag_hist.release();

@@ -51,6 +51,16 @@ struct Dev {
         bytes = b;
         borrowed = true;
     }
+    // Take over `o`'s memory.
+    void take(Dev &o) {
+        release();
+        p = o.p;
+        bytes = o.bytes;
+        from = o.from;
+        borrowed = o.borrowed;
+        o.p = nullptr;
+        o.release();
+    }
     spmv_status alloc(size_t b) {
         release();
         if (b == 0) b = 16;

@@ -15,19 +15,49 @@ import numpy as np
 from . import capi as C
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+def _device_calls():
+    """(current device, its current stream's handle by device index).  A small
+    product's whole call is 7 us, and the public forms of these two build a
+    Stream object and check for initialisation each time (1.5 us)."""
+    c = _torch()._C
+    if hasattr(c, "_cuda_getDevice") and hasattr(c, "_cuda_getCurrentRawStream"):
+        return c._cuda_getDevice, c._cuda_getCurrentRawStream
+    cuda = _torch().cuda
+    return cuda.current_device, lambda index: cuda.current_stream(index).cuda_stream
+
+
+_calls = None
+
+
+def _current_device():
+    global _calls
+    if _calls is None:
+        _torch().cuda.init()
+        _calls = _device_calls()
+    return _calls[0]()
 
 
 def _stream_handle(stream=None):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """hipStream_t of `stream`, or of the current torch stream."""
+    if stream is not None:
+        return stream.cuda_stream
+    index = _current_device()
+    return _calls[1](index)
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None and t.numel() else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None and t.numel() else None
 
 
 def _dtype_code(t):
@@ -195,7 +225,8 @@ class TorchAllocator:
         def alloc(nbytes, ctx):
             torch = _torch()
             try:
-                if self.stream is not None:
+                if self.stream is not None and \
+                        self.stream != torch.cuda.current_stream(self.device):
                     with torch.cuda.stream(self.stream):
                         t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
                 else:
@@ -317,7 +348,6 @@ class Plan:
     def run(self, x, y=None, stream=None, out=None):
         """y = A x on the current torch stream (or `stream`); y (or `out`)
         is overwritten, or allocated when neither is given."""
-        torch = _torch()
         if out is not None:
             if y is not None:
                 raise TypeError("give y or out, not both")
@@ -325,18 +355,19 @@ class Plan:
         if x.dtype != self.dtype or not x.is_contiguous() or x.numel() != self.n:
             raise TypeError("x must be a contiguous vector of length n and the matrix dtype")
         if y is None:
-            y = torch.empty(self.m, dtype=self.dtype, device=self.device)
+            y = _torch().empty(self.m, dtype=self.dtype, device=self.device)
         elif y.dtype != self.dtype or not y.is_contiguous() or y.numel() != self.m:
             raise TypeError("y must be a contiguous vector of length m and the matrix dtype")
-        if x.device != self.device or y.device != self.device:
+        index = self.device.index
+        if x.get_device() != index or y.get_device() != index:   # -1 off the GPU
             raise TypeError("x and y must be on the plan's device")
-        if torch.cuda.current_device() == self.device.index:
-            C.check(C.lib().spmv_run(self.handle, _ptr(x), _ptr(y), _stream_handle(stream)),
-                    "spmv_run")
+        if _current_device() == index:
+            st = C.lib().spmv_run(self.handle, _ptr(x), _ptr(y), _stream_handle(stream))
         else:
-            with torch.cuda.device(self.device):   # the library works on the current device
-                C.check(C.lib().spmv_run(self.handle, _ptr(x), _ptr(y), _stream_handle(stream)),
-                        "spmv_run")
+            with _torch().cuda.device(self.device):   # the library works on the current device
+                st = C.lib().spmv_run(self.handle, _ptr(x), _ptr(y), _stream_handle(stream))
+        if st:
+            C.check(st, "spmv_run")
         return y
 
     __call__ = run
