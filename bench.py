@@ -210,7 +210,8 @@ def main():
                        tune_ms=info["t_tune_ms"] if k == 0 else 0.0,
                        bytes=workloads.plan_bytes(pi), confidence=pi["confidence"],
                        n_measured=pi["n_measured"], params=pi["params"],
-                       feature_stage=pi["feature_stage"], long_lanes=pi["long_lanes"])
+                       feature_stage=pi["feature_stage"], long_lanes=pi["long_lanes"],
+                       dia_bytes=pi["dia_ndiags"] * pi["m_pad"] * np.dtype(dt).itemsize)
             recs.append(dict(rec=rec, tuned=part, plain=plain if k == 0 else None, x=x,
                              y=y[r0:r0 + part.m], py=y, owner=tuned))
         del rp, col, val
@@ -312,6 +313,9 @@ def main():
         v = (16 // (8 if t == "double" else 4)) if p["wide_loads"] == 1 else 1
         if k == "ell":
             return f"k_ell<{t}, {p['ell_unroll']}, {nt}, {v}>"
+        if (k == "dia_direct" and v * p["dia_rows_per_thread"] == 4 and v > 1 and
+                rec.get("dia_bytes", 0) > 256 << 20):
+            return f"k_dia_groups<{t}, {p['dia_rows_per_thread']}, {nt}, {v}>"
         if k in ("dia", "dia_direct"):
             return (f"k_{'dia_lds' if k == 'dia' else 'dia_direct'}"
                     f"<{t}, {p['dia_rows_per_thread']}, {nt}, {v}>")

@@ -109,7 +109,8 @@ typedef struct {
                                    rows of up to L * this many entries        */
     int32_t adaptive_wg_min;    /* CSR_ADAPTIVE: rows longer than this get a
                                    whole workgroup                            */
-    int32_t dia_rows_per_thread;/* DIA: rows per thread (tile = block * this) */
+    int32_t dia_rows_per_thread;/* DIA: loads per thread and diagonal, of one row or
+                                   (wide) 16 bytes of rows; 0 = default */
     int32_t dia_span;           /* DIA: max offset span staged per LDS window */
     int32_t coo_chunk;          /* COO: entries per lane per wavefront chunk  */
     int32_t ell_unroll;         /* ELL: slots fetched per loop trip (1, 2, 4) */

@@ -428,7 +428,7 @@ spmv_params default_params(int kernel, const spmv_features &F) {
     p.vector_lanes = default_lanes(F);
     p.adaptive_rows_per_lane = 2;
     p.adaptive_wg_min = 4096;
-    p.dia_rows_per_thread = F.m >= (4 << 20) ? 4 : F.m >= (1 << 20) ? 2 : 1;
+    p.dia_rows_per_thread = 0;  // resolved by resolve_params
     p.dia_span = 64;
     p.coo_chunk = F.nnz >= (8 << 20) ? 8 : F.nnz >= (1 << 20) ? 4 : 2;
     p.ell_unroll = 4;
@@ -494,6 +494,14 @@ spmv_params resolve_params(int kernel, spmv_params p, const spmv_features &F, in
     // the chip many times over (measured: faster from about a million rows,
     // slower on smaller matrices)
     if (p.wide_loads == 0) p.wide_loads = F.m >= (1 << 20) ? 1 : 2;
+    // DIA: kDiaLaneRows rows a lane under 16-byte loads, one under narrow ones.
+    // More rows wait longer for each diagonal with fewer waves to fill the
+    // wait.  Measured with 1 | 2 | 4 16-byte loads a lane (us): 7-point 256^3
+    // float64 direct 200 | 199 | 221, x in LDS 223 | 212 | 225; float32 104 |
+    // 105 | 118, LDS 142 | 142 | 170; 9 diagonals of 1.2M rows float64 23.3 |
+    // 22.1 | 27.5, float32 12.6 | 17.1 | 26.1.
+    if (p.dia_rows_per_thread == 0)
+        p.dia_rows_per_thread = p.wide_loads == 1 ? kDiaLaneRows * elt / 16 : 1;
     if (p.panel_direct_max == 0) p.panel_direct_max = kPanelDirectMaxDefault;
     if (p.tile_row_min == 0) p.tile_row_min = default_tile_row_min(F.n, elt);
     if (p.bcsr_lanes == 0) {
@@ -546,7 +554,7 @@ spmv_status check_params(const spmv_params &p) {
         set_error("params.adaptive_* out of range");
         return SPMV_EINVAL;
     }
-    if (!(p.dia_rows_per_thread == 1 || p.dia_rows_per_thread == 2 ||
+    if (!(p.dia_rows_per_thread == 0 || p.dia_rows_per_thread == 1 || p.dia_rows_per_thread == 2 ||
           p.dia_rows_per_thread == 4 || p.dia_rows_per_thread == 8) ||
         p.dia_span < 0 || p.dia_span > 8192) {
         set_error("params.dia_rows_per_thread must be 1, 2, 4 or 8 and dia_span in [0, 8192]");

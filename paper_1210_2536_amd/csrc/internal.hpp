@@ -12,6 +12,8 @@
 namespace smat {
 
 constexpr int kWave = 64;           // gfx9 wavefront width
+constexpr int kDiaLaneRows = 4;     // rows of a lane of a DIA tile with 16-byte loads
+constexpr uint64_t kDiaGroupBytes = uint64_t(256) << 20;   // DIA values streamed by groups above
 constexpr int kRowPad = 64;         // ELL / DIA slot stride is m rounded up to this
 constexpr int kFp64MaxDepth = 4096; // longest sequential float64 summation chain
 constexpr int kAdaptiveBins = 9;    // widths 1..64 (7 bins) + workgroup + split

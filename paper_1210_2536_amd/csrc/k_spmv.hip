@@ -381,6 +381,23 @@ __global__ __launch_bounds__(256) void k_dia_direct(int64_t m, int64_t n, int64_
     dia_tile_direct<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y);
 }
 
+// The same with the loads of 4 diagonals in flight per lane, for diagonals that
+// stream from HBM (kDiaGroupBytes).  In the loop over single diagonals each
+// lane waits for memory once per diagonal; from the caches that costs little
+// and neighbouring diagonals find x in L1, where 4 at a time crowd it out.
+// Measured, values from HBM (loop | groups, MI355X): 7-point 256^3 float64 199
+// | 190 us (6.3 TB/s), float32 104 | 102, 7-point 160^3 float64 55 | 53; below
+// the line the loop: band of 9 diagonals, 1.2M float32 12.6 | 13.8, 15 diagonals
+// of 500k float64 15.2 | 16.0.
+template <typename T, int RPT, bool NT, int V>
+__global__ __launch_bounds__(256) void k_dia_groups(int64_t m, int64_t n, int64_t m_pad, int D,
+                                                    const int32_t *__restrict__ offs,
+                                                    const T *__restrict__ data,
+                                                    const T *__restrict__ x, T *__restrict__ y) {
+    const int64_t r0 = (int64_t)blockIdx.x * blockDim.x * RPT * V;
+    dia_tile_groups<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y);
+}
+
 // ---------------------------------------------------------------- long rows, x in LDS
 // float64 rows of the longest bin (a workgroup each in the binned kernels)
 // in groups of G = 1024 / TPR per workgroup.  x streams through LDS in
@@ -913,7 +930,11 @@ spmv_status dia_dispatch(bool lds, int64_t m, int64_t n, int64_t m_pad, int D,
     int64_t tile = (int64_t)block * rpt * V;
     unsigned g = grid_for(m, (int)tile);
     size_t sh = lds ? (size_t)(tile + max_span) * sizeof(T) : 0;
-    if (wide)
+    // values that the Infinity Cache cannot hold, at the default tile
+    constexpr int G = kDiaLaneRows / W;
+    if (!lds && wide && rpt == G && (uint64_t)D * m_pad * sizeof(T) > kDiaGroupBytes)
+        k_dia_groups<T, G, NT, W><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y);
+    else if (wide)
         dia_launch<T, NT, W>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, s);
     else
         dia_launch<T, NT, 1>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, s);

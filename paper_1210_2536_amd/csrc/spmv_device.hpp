@@ -321,6 +321,103 @@ __device__ __forceinline__ void dia_tile_direct(int64_t r0, int64_t m, int64_t n
     }
 }
 
+// dia_tile_groups: dia_tile_direct with the loads of 4 diagonals in flight, for
+// streams from HBM.  Every x element and value of a group is requested before
+// its first product (x first: its lines are shared by neighbouring diagonals,
+// the values pass once).  EDGE: some rows or columns of the tile do
+// not exist; addresses are clamped into the arrays and those products left
+// out, so the tiles at the matrix's ends keep as many loads in flight as the
+// others.
+template <typename T, int U, int RPT, bool NT, int V, bool EDGE>
+__device__ __forceinline__ void dia_group(int64_t r0, int64_t n, int64_t m_pad,
+                                          const int32_t *__restrict__ offs,
+                                          const T *__restrict__ dd, const T *__restrict__ x,
+                                          double (&acc)[RPT][V]) {
+    typedef T vec __attribute__((ext_vector_type(V)));
+    T v[U][RPT][V];
+    vec xv[U][RPT];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            const int64_t j0 = r0 + offs[u] + (int64_t)((threadIdx.x + q * blockDim.x) * V);
+            if constexpr (EDGE) {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    xv[u][q][e] = x[min(max(j0 + e, (int64_t)0), n - 1)];
+            } else {
+                __builtin_memcpy(&xv[u][q], x + j0, sizeof(vec));   // only element-aligned
+            }
+        }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            int64_t i0 = r0 + (int64_t)((threadIdx.x + q * blockDim.x) * V);
+            if constexpr (EDGE) i0 = min(i0, m_pad - V);
+            ld_rows<T, V, NT>(dd + (int64_t)u * m_pad + i0, v[u][q]);
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            const int64_t j0 = r0 + offs[u] + (int64_t)((threadIdx.x + q * blockDim.x) * V);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const double t = fma((double)v[u][q][e], (double)xv[u][q][e], acc[q][e]);
+                if (!EDGE || (j0 + e >= 0 && j0 + e < n)) acc[q][e] = t;
+            }
+        }
+}
+
+template <typename T, int RPT, bool NT, int V, bool EDGE>
+__device__ __forceinline__ void dia_diagonals(int64_t r0, int64_t n, int64_t m_pad,
+                                              int D, const int32_t *__restrict__ offs,
+                                              const T *__restrict__ data,
+                                              const T *__restrict__ x, double (&acc)[RPT][V]) {
+    // at most 8 values and 8 x vectors of a lane in flight: more spill
+    constexpr int U = EDGE ? 2 : 4;
+    int d = 0;
+    for (; d + U <= D; d += U)
+        dia_group<T, U, RPT, NT, V, EDGE>(r0, n, m_pad, offs + d, data + (int64_t)d * m_pad, x,
+                                          acc);
+    if (U > 3 && d + 3 == D)
+        dia_group<T, 3, RPT, NT, V, EDGE>(r0, n, m_pad, offs + d, data + (int64_t)d * m_pad, x,
+                                          acc);
+    else if (U > 2 && d + 2 == D)
+        dia_group<T, 2, RPT, NT, V, EDGE>(r0, n, m_pad, offs + d, data + (int64_t)d * m_pad, x,
+                                          acc);
+    else if (U > 1 && d + 1 == D)
+        dia_group<T, 1, RPT, NT, V, EDGE>(r0, n, m_pad, offs + d, data + (int64_t)d * m_pad, x,
+                                          acc);
+}
+
+template <typename T, int RPT, bool NT, int V>
+__device__ __forceinline__ void dia_tile_groups(int64_t r0, int64_t m, int64_t n, int64_t m_pad,
+                                                int D, const int32_t *__restrict__ offs,
+                                                const T *__restrict__ data,
+                                                const T *__restrict__ x, T *__restrict__ y) {
+    double acc[RPT][V];
+#pragma unroll
+    for (int q = 0; q < RPT; ++q)
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[q][e] = 0.0;
+    const int64_t R = (int64_t)blockDim.x * RPT * V;
+    // offsets ascend, so the first and the last bound the tile's columns
+    if (r0 + R <= m && r0 + offs[0] >= 0 && r0 + R + offs[D - 1] <= n)
+        dia_diagonals<T, RPT, NT, V, false>(r0, n, m_pad, D, offs, data, x, acc);
+    else
+        dia_diagonals<T, RPT, NT, V, true>(r0, n, m_pad, D, offs, data, x, acc);
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+        const int64_t i0 = r0 + (int64_t)(threadIdx.x + q * blockDim.x) * V;
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (i0 + e < m) y[i0 + e] = (T)acc[q][e];
+    }
+}
+
 // Row sums over threads that take consecutive entries whatever their rows:
 // `acc` is the thread's sum of the row still open at its end (of all its
 // entries if no row starts in it), `bal` the ballot of the threads in which a
