@@ -322,9 +322,8 @@ def main():
         if k == "coo":
             return f"k_coo<{t}, {nt}> + k_coo_fixup<{t}>"
         if k == "bcsr":
-            if t == "double":   # 8 lanes per block
-                return f"k_bcsr_coop<{p['bcsr_lanes']}, {nt}>"
-            return f"k_bcsr<{t}, {p['bcsr_lanes']}, {nt}>"
+            lanes = max(p["bcsr_lanes"], 8 if t == "double" else 4)
+            return f"k_bcsr<{t}, {lanes}, {nt}>"
         if k == "csr_panel":
             if p["panel_xcd"] == 0:   # two steps; rows above the blocks' limit apart
                 # rows by tiles share the two launches

@@ -139,14 +139,11 @@ typedef struct {
                                    one row per lane; 0 = default (1 from
                                    2^20 rows on, 2 below)                  */
     int32_t bcsr_lanes;         /* BCSR: lanes per block row, a power of two
-                                   in [1, 64].  float32: one block per lane
-                                   at a time (0 = default: the mean blocks
-                                   per block row rounded up to a power of
-                                   two).  float64: 8 lanes read a block
-                                   together, so lanes / 8 blocks of a row
-                                   are read at once (values below 8 are
-                                   raised to 8; 0 = default 8, widened as
-                                   the 1e-12 bound needs)                  */
+                                   in [1, 64]; at least the lanes of a block
+                                   (16 bytes each: float32 4, float64 8).
+                                   0 = default: about 2 lanes per block of
+                                   a mean block row, widened in float64 as
+                                   the 1e-12 bound needs                   */
     int32_t long_lds;           /* CSR_ADAPTIVE and CSR_PANEL: where the
                                    rows of the longest bin (a workgroup each
                                    in the binned launch) go.  1 = x chunks

@@ -65,14 +65,9 @@ constexpr unsigned kKindsAll = kKindsCsr | kKindsEll | kKindsDia | kKindsBcsr;
 template <typename T, int L, bool NT>
 __device__ __forceinline__ void bcsr_tile(const LevelDesc &d, int64_t tile, const T *x, T *y) {
     const int64_t R = tile * (kPBlock / L) + threadIdx.x / L;
-    if constexpr (sizeof(T) == 8) {
-        if constexpr (L >= 8)
-            bcsr_row_coop<L, NT>(R, threadIdx.x & (L - 1), d.mb, d.m, d.n, d.brp, d.bcol,
-                                 (const double *)d.bval, x, y);
-    } else {
-        bcsr_row_lanes<T, L, NT>(R, threadIdx.x & (L - 1), d.mb, d.m, d.n, d.brp, d.bcol,
-                                 (const T *)d.bval, x, y);
-    }
+    if constexpr (L >= bcsr_block_lanes(sizeof(T)))
+        bcsr_row<T, L, NT, 1>(R, threadIdx.x & (L - 1), d.mb, d.m, d.n, d.brp, d.bcol,
+                              (const T *)d.bval, x, y);
 }
 
 // One (level, tile) work item; the same device functions as the stand-alone
@@ -136,8 +131,6 @@ __device__ __forceinline__ void batch_item(const LevelDesc &d, int64_t tile, con
     case LK_BCSR:
         if constexpr (!(KINDS & (1u << LK_BCSR))) break;
         switch (d.lanes) {
-        case 1: bcsr_tile<T, 1, NT>(d, tile, x, y); break;
-        case 2: bcsr_tile<T, 2, NT>(d, tile, x, y); break;
         case 4: bcsr_tile<T, 4, NT>(d, tile, x, y); break;
         case 8: bcsr_tile<T, 8, NT>(d, tile, x, y); break;
         case 16: bcsr_tile<T, 16, NT>(d, tile, x, y); break;
@@ -425,7 +418,7 @@ extern "C" spmv_status spmv_batch_create(const spmv_plan_t *plans, int32_t nplan
             // the level's own lane count (float64: at least the 8 lanes of
             // one block), kPBlock / lanes block rows per work item
             d.kind = LK_BCSR;
-            d.lanes = P.elt == 8 ? std::max(8, V.prm.bcsr_lanes) : V.prm.bcsr_lanes;
+            d.lanes = std::max(bcsr_block_lanes(P.elt), V.prm.bcsr_lanes);
             d.mb = (P.m + 3) / 4;
             d.brp = V.brp.as<int32_t>();
             d.bcol = V.bcol.as<int32_t>();

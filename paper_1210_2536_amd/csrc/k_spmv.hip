@@ -678,23 +678,13 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_ranks(const int32_t *__re
 }
 
 // ---------------------------------------------------------------- BCSR 4x4
-// Two lane mappings, chosen by value type (both measured on gfx950):
-//
-// float32 (k_bcsr): a group of L lanes per block row; lane l takes blocks l,
-// l+L, ... of its block row.  A block's 16 values (row-major) arrive in
-// 16-byte loads, its 4 x values in one (element-aligned) load away from the
-// last column block; each lane keeps one running sum per row (products of a
-// block in column order), and the L lanes' sums are added by xor shuffles.
-//
-// float64 (k_bcsr_coop): a block's 128 bytes are read by 8 lanes together,
-// 16 bytes (half a row) each, so consecutive lanes read consecutive 16-byte
-// pieces and a wave's loads are fully coalesced.  A block row has L lanes
-// (8 <= L <= 64): G = L / 8 groups, group g taking blocks g, g + G, ... of
-// the row.  A lane reads the 2 x values under its piece in one load and
-// keeps one running sum for its row; lanes of the same row (the pair inside
-// a block, then the G groups) are added by xor shuffles in a fixed order.
-//
-// Zero-filled positions add exact zeros.
+// Zero-filled positions add exact zeros.  Bound by the block stream; what held
+// it back was the chain row pointer -> block column -> x, once per block of a
+// lane: four blocks are in flight now.  float32 lanes used to hold whole blocks
+// (64 bytes a lane, 64 lines a load).
+// Measured, blocks from HBM (before | now, MI355X): 400k rows of 16 blocks
+// float64 54.4 | 44.7 us (4.9 TB/s), float32 29.0 | 27.1; 100k rows 15.4 | 12.6
+// and 9.5 | 8.9; 400k rows of 4 blocks 16.0 | 14.5 and 10.2 | 9.7.
 template <typename T, int L, bool NT>
 __global__ __launch_bounds__(256) void k_bcsr(int64_t mb, int64_t m, int64_t n,
                                               const int32_t *__restrict__ brp,
@@ -702,18 +692,7 @@ __global__ __launch_bounds__(256) void k_bcsr(int64_t mb, int64_t m, int64_t n,
                                               const T *__restrict__ bval,
                                               const T *__restrict__ x, T *__restrict__ y) {
     const int64_t R = (int64_t)blockIdx.x * (blockDim.x / L) + threadIdx.x / L;
-    bcsr_row_lanes<T, L, NT>(R, threadIdx.x & (L - 1), mb, m, n, brp, bcol, bval, x, y);
-}
-
-template <int L, bool NT>
-__global__ __launch_bounds__(256) void k_bcsr_coop(int64_t mb, int64_t m, int64_t n,
-                                                   const int32_t *__restrict__ brp,
-                                                   const int32_t *__restrict__ bcol,
-                                                   const double *__restrict__ bval,
-                                                   const double *__restrict__ x,
-                                                   double *__restrict__ y) {
-    const int64_t R = (int64_t)blockIdx.x * (blockDim.x / L) + threadIdx.x / L;
-    bcsr_row_coop<L, NT>(R, threadIdx.x & (L - 1), mb, m, n, brp, bcol, bval, x, y);
+    bcsr_row<T, L, NT, 4>(R, threadIdx.x & (L - 1), mb, m, n, brp, bcol, bval, x, y);
 }
 
 // ---------------------------------------------------------------- COO
@@ -1042,27 +1021,15 @@ spmv_status bcsr_dispatch(int64_t m, int64_t n, const int32_t *brp, const int32_
         set_error("bcsr: lanes must be a power of two in [1, min(64, block)], got %d", lanes);
         return SPMV_EINVAL;
     }
-    if constexpr (sizeof(T) == 8) {
-        if (lanes < 8) lanes = 8;  // a float64 block takes 8 lanes
-        if (lanes > block) {
-            set_error("bcsr: block of %d threads cannot hold %d lanes per block row", block,
-                      lanes);
-            return SPMV_EINVAL;
-        }
-        const unsigned g = grid_for(mb, block / lanes);
-#define L_CASE(L)                                                                          \
-    case L: k_bcsr_coop<L, NT><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y); break;
-        switch (lanes) { L_CASE(8) L_CASE(16) L_CASE(32) L_CASE(64) }
-#undef L_CASE
-    } else {
-        const unsigned g = grid_for(mb, block / lanes);
+    lanes = std::max(lanes, bcsr_block_lanes(sizeof(T)));
+    const unsigned g = grid_for(mb, block / lanes);
 #define L_CASE(L)                                                                            \
-    case L: k_bcsr<T, L, NT><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y); break;
-        switch (lanes) {
-            L_CASE(1) L_CASE(2) L_CASE(4) L_CASE(8) L_CASE(16) L_CASE(32) L_CASE(64)
-        }
+    case L:                                                                                  \
+        if constexpr (L >= bcsr_block_lanes(sizeof(T)))                                      \
+            k_bcsr<T, L, NT><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y);           \
+        break;
+    switch (lanes) { L_CASE(4) L_CASE(8) L_CASE(16) L_CASE(32) L_CASE(64) }
 #undef L_CASE
-    }
     SMAT_LAUNCHED("bcsr");
     return SPMV_OK;
 }
