@@ -21,6 +21,7 @@ namespace {
 
 constexpr int kMaxLevels = 4096;      // persistent mode
 constexpr int kMaxGraphPlans = 4096;  // graph mode
+constexpr int kCus = 256;      // compute units of gfx950
 constexpr int kPBlock = 256;   // persistent workgroup size
 constexpr int kPDiaRpt = 4;    // rows per thread of a DIA tile
 
@@ -40,15 +41,58 @@ struct LevelDesc {
     AdaptiveLaunch alaunch;
 };
 
-template <typename T, int L, bool NT>
+// A tile of a csr_vector level: R groups of kPBlock / L rows whose loads are
+// requested together (a level of 27-entry rows is a chain row pointer, column,
+// x per group otherwise); each row is summed as csr_row_lanes does.
+template <typename T, int L, bool NT, int R>
 __device__ __forceinline__ void vector_tile(const LevelDesc &d, int64_t tile, const T *x, T *y) {
-    int64_t row = tile * (kPBlock / L) + threadIdx.x / L;
-    int lane = threadIdx.x & (L - 1);
-    if (row < d.m) {
-        double acc = csr_row_lanes<T, L, NT>(row, lane, d.rp, d.col, (const T *)d.val, x);
-        if (lane == 0) y[row] = (T)acc;
+    constexpr int per = kPBlock / L;
+    const int64_t row0 = tile * per * R + threadIdx.x / L;
+    const int lane = threadIdx.x & (L - 1);
+    const T *val = (const T *)d.val;
+    if constexpr (R == 1) {
+        if (row0 < d.m) {
+            double acc = csr_row_lanes<T, L, NT>(row0, lane, d.rp, d.col, val, x);
+            if (lane == 0) y[row0] = (T)acc;
+        }
+    } else {
+        int32_t p[R], e[R], most = 0;
+        double acc[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int64_t row = min(row0 + q * per, d.m - 1);
+            p[q] = d.rp[row] + lane;
+            e[q] = d.rp[row + 1];
+            acc[q] = 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) most = max(most, e[q] - p[q]);
+        for (int32_t o = 0; o < most; o += L) {
+            int32_t c[R];
+            T v[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                if (p[q] + o < e[q]) {
+                    c[q] = ld<NT>(d.col + p[q] + o);
+                    v[q] = ld<NT>(val + p[q] + o);
+                }
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                if (p[q] + o < e[q]) acc[q] = fma((double)v[q], (double)x[c[q]], acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+#pragma unroll
+            for (int off = L / 2; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, L);
+            const int64_t row = row0 + q * per;
+            if (lane == 0 && row < d.m) y[row] = (T)acc[q];
+        }
     }
 }
+
+// Row groups of a csr_vector tile: 4 where the level still has a tile for each
+// workgroup the GPU holds, and the lanes of a row leave registers for them.
+constexpr int kPVectorRows = 2;
 
 // Level-kind sets the persistent kernel is compiled for (bit k: LevelKind
 // k).  A launch takes the smallest set that holds the kinds of its levels:
@@ -88,13 +132,21 @@ __device__ __forceinline__ void batch_item(const LevelDesc &d, int64_t tile, con
     case LK_VECTOR:
         if constexpr (!(KINDS & (1u << LK_VECTOR))) break;
         switch (d.lanes) {
-        case 1: vector_tile<T, 1, NT>(d, tile, x, y); break;
-        case 2: vector_tile<T, 2, NT>(d, tile, x, y); break;
-        case 4: vector_tile<T, 4, NT>(d, tile, x, y); break;
-        case 8: vector_tile<T, 8, NT>(d, tile, x, y); break;
-        case 16: vector_tile<T, 16, NT>(d, tile, x, y); break;
-        case 32: vector_tile<T, 32, NT>(d, tile, x, y); break;
-        default: vector_tile<T, 64, NT>(d, tile, x, y); break;
+#define SMAT_VECTOR_TILE(L)                                             \
+    case L:                                                              \
+        if (d.K == kPVectorRows)                                         \
+            vector_tile<T, L, NT, kPVectorRows>(d, tile, x, y);          \
+        else                                                             \
+            vector_tile<T, L, NT, 1>(d, tile, x, y);                     \
+        break
+        case 1: vector_tile<T, 1, NT, 1>(d, tile, x, y); break;
+        case 2: vector_tile<T, 2, NT, 1>(d, tile, x, y); break;
+        case 4: vector_tile<T, 4, NT, 1>(d, tile, x, y); break;
+        SMAT_VECTOR_TILE(8);
+        SMAT_VECTOR_TILE(16);
+        SMAT_VECTOR_TILE(32);
+        SMAT_VECTOR_TILE(64);
+#undef SMAT_VECTOR_TILE
         }
         break;
     case LK_ADAPTIVE:
@@ -151,9 +203,12 @@ __device__ __forceinline__ void batch_item(const LevelDesc &d, int64_t tile, con
 }
 
 // Work items base .. total-1 (items below `base` belong to levels launched
-// on their own before this kernel), strided over the grid; an item's level
-// is found by binary search over the levels' first items.  xy: the levels'
-// x pointers, then their y pointers.
+// on their own before this kernel), strided over the grid from the last item
+// to the first: the smallest levels, whose few items are long chains of
+// dependent loads, start first and hide behind the large ones.  An item's
+// level is found by binary search over the levels' first items, no later than
+// the workgroup's previous level.  xy: the levels' x pointers, then their y
+// pointers.
 template <typename T, unsigned KINDS>
 __global__ __launch_bounds__(kPBlock) void k_batch_persistent(const LevelDesc *__restrict__ L,
                                                               int nlev, int64_t base,
@@ -162,8 +217,10 @@ __global__ __launch_bounds__(kPBlock) void k_batch_persistent(const LevelDesc *_
     extern __shared__ unsigned char smem_raw[];
     T *xs = reinterpret_cast<T *>(smem_raw);
     __shared__ double part[kPBlock / kWave];
-    for (int64_t t = base + blockIdx.x; t < total; t += gridDim.x) {
-        int lo = 0, hi = nlev - 1;   // the last level whose first item is <= t
+    int last = nlev - 1;
+    for (int64_t t = total - 1 - (int64_t)blockIdx.x; t >= base; t -= gridDim.x) {
+        int lo = 0, hi = last;   // the last level whose first item is <= t
+        if (L[last].tile_begin <= t) lo = last;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (L[mid].tile_begin <= t)
@@ -171,6 +228,7 @@ __global__ __launch_bounds__(kPBlock) void k_batch_persistent(const LevelDesc *_
             else
                 hi = mid - 1;
         }
+        last = lo;
         const LevelDesc &d = L[lo];
         const int64_t tile = t - d.tile_begin;
         const T *x = (const T *)xy[lo];
@@ -179,7 +237,8 @@ __global__ __launch_bounds__(kPBlock) void k_batch_persistent(const LevelDesc *_
             batch_item<T, true, KINDS>(d, tile, x, y, xs, part);
         else
             batch_item<T, false, KINDS>(d, tile, x, y, xs, part);
-        __syncthreads();  // LDS reuse by the next item
+        if constexpr (KINDS & ((1u << LK_ADAPTIVE) | (1u << LK_DIA)))
+            __syncthreads();  // LDS reuse by the next item
     }
 }
 
@@ -377,7 +436,9 @@ extern "C" spmv_status spmv_batch_create(const spmv_plan_t *plans, int32_t nplan
         case SPMV_K_CSR_VECTOR:
             d.kind = LK_VECTOR;
             d.lanes = V.prm.vector_lanes;
-            d.tile_rows = kPBlock / d.lanes;
+            d.K = d.lanes >= 8 && P.m / (kPVectorRows * (kPBlock / d.lanes)) >= 4 * kCus
+                      ? kPVectorRows : 1;
+            d.tile_rows = d.K * (kPBlock / d.lanes);
             break;
         case SPMV_K_CSR_ADAPTIVE:
             // one work item per workgroup of the level's binned launch; rows
