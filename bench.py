@@ -314,7 +314,7 @@ def main():
         if k == "ell":
             return f"k_ell<{t}, {p['ell_unroll']}, {nt}, {v}>"
         if (k == "dia_direct" and v * p["dia_rows_per_thread"] == 4 and v > 1 and
-                rec.get("dia_bytes", 0) > 256 << 20):
+                rec.get("dia_bytes", 0) > 120 << 20):
             return f"k_dia_groups<{t}, {p['dia_rows_per_thread']}, {nt}, {v}>"
         if k in ("dia", "dia_direct"):
             return (f"k_{'dia_lds' if k == 'dia' else 'dia_direct'}"

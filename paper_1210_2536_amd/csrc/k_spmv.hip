@@ -335,7 +335,7 @@ template <typename T, int U, bool NT, int V>
 __global__ __launch_bounds__(1024) void k_ell(int64_t m, int64_t m_pad, int K,
                                               const int32_t *__restrict__ ecol,
                                               const T *__restrict__ eval, const T *__restrict__ x,
-                                              T *__restrict__ y) {
+                                              T *__restrict__ y, bool past) {
     if constexpr (V == 1) {
         int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
         if (i >= m) return;
@@ -345,9 +345,7 @@ __global__ __launch_bounds__(1024) void k_ell(int64_t m, int64_t m_pad, int K,
         if (i0 >= m) return;
         double acc[V];
         ell_rows_wide<T, U, V, NT>(i0, m, m_pad, K, ecol, eval, x, acc);
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (i0 + e < m) y[i0 + e] = (T)acc[e];
+        st_rows<T, V>(y, i0, m, acc, past);
     }
 }
 
@@ -363,11 +361,12 @@ __global__ __launch_bounds__(256) void k_dia_lds(int64_t m, int64_t n, int64_t m
                                                  const int32_t *__restrict__ offs, int nwin,
                                                  const DiaWindow *__restrict__ win,
                                                  const T *__restrict__ data,
-                                                 const T *__restrict__ x, T *__restrict__ y) {
+                                                 const T *__restrict__ x, T *__restrict__ y,
+                                                 bool past) {
     extern __shared__ unsigned char smem_raw[];
     T *xs = reinterpret_cast<T *>(smem_raw);
     const int64_t r0 = (int64_t)blockIdx.x * blockDim.x * RPT * V;
-    dia_tile_lds<T, RPT, NT, V>(r0, m, n, m_pad, offs, nwin, win, data, x, y, xs);
+    dia_tile_lds<T, RPT, NT, V>(r0, m, n, m_pad, offs, nwin, win, data, x, y, xs, past);
 }
 
 // DIA without LDS: x comes through L1/L2 (neighbouring diagonals hit the same
@@ -376,26 +375,29 @@ template <typename T, int RPT, bool NT, int V>
 __global__ __launch_bounds__(256) void k_dia_direct(int64_t m, int64_t n, int64_t m_pad, int D,
                                                     const int32_t *__restrict__ offs,
                                                     const T *__restrict__ data,
-                                                    const T *__restrict__ x, T *__restrict__ y) {
+                                                    const T *__restrict__ x, T *__restrict__ y,
+                                                    bool past) {
     const int64_t r0 = (int64_t)blockIdx.x * blockDim.x * RPT * V;
-    dia_tile_direct<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y);
+    dia_tile_direct<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y, past);
 }
 
 // The same with the loads of 4 diagonals in flight per lane, for diagonals that
-// stream from HBM (kDiaGroupBytes).  In the loop over single diagonals each
-// lane waits for memory once per diagonal; from the caches that costs little
-// and neighbouring diagonals find x in L1, where 4 at a time crowd it out.
-// Measured, values from HBM (loop | groups, MI355X): 7-point 256^3 float64 199
-// | 190 us (6.3 TB/s), float32 104 | 102, 7-point 160^3 float64 55 | 53; below
-// the line the loop: band of 9 diagonals, 1.2M float32 12.6 | 13.8, 15 diagonals
-// of 500k float64 15.2 | 16.0.
+// stream from HBM (kHbmBytes).  In the loop over single diagonals each lane
+// waits for memory once per diagonal; from the caches that costs little and
+// neighbouring diagonals find x in L1, where 4 at a time crowd it out.
+// Measured, one matrix (loop | groups, MI355X): 7-point 256^3 float64 199 | 190
+// us, float32 104 | 102, 160^3 float64 55 | 53; several matrices in turn, with
+// y past the caches: 195 us (6.1 TB/s) and 93 (6.5).  Below the line the loop:
+// band of 9 diagonals, 1.2M float32 12.6 | 13.8, 15 diagonals of 500k float64
+// 15.2 | 16.0.
 template <typename T, int RPT, bool NT, int V>
 __global__ __launch_bounds__(256) void k_dia_groups(int64_t m, int64_t n, int64_t m_pad, int D,
                                                     const int32_t *__restrict__ offs,
                                                     const T *__restrict__ data,
-                                                    const T *__restrict__ x, T *__restrict__ y) {
+                                                    const T *__restrict__ x, T *__restrict__ y,
+                                                    bool past) {
     const int64_t r0 = (int64_t)blockIdx.x * blockDim.x * RPT * V;
-    dia_tile_groups<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y);
+    dia_tile_groups<T, RPT, NT, V>(r0, m, n, m_pad, D, offs, data, x, y, past);
 }
 
 // ---------------------------------------------------------------- long rows, x in LDS
@@ -852,11 +854,11 @@ template <typename T> constexpr int kWideRows = 16 / (int)sizeof(T);
 
 template <typename T, bool NT, int V>
 void ell_launch(unsigned g, int block, int unroll, int64_t m, int64_t m_pad, int K,
-                const int32_t *ecol, const T *eval, const T *x, T *y, hipStream_t s) {
+                const int32_t *ecol, const T *eval, const T *x, T *y, bool past, hipStream_t s) {
     switch (unroll) {
-    case 1: k_ell<T, 1, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y); break;
-    case 2: k_ell<T, 2, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y); break;
-    default: k_ell<T, 4, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y); break;
+    case 1: k_ell<T, 1, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y, past); break;
+    case 2: k_ell<T, 2, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y, past); break;
+    default: k_ell<T, 4, NT, V><<<g, block, 0, s>>>(m, m_pad, K, ecol, eval, x, y, past); break;
     }
 }
 
@@ -866,11 +868,13 @@ spmv_status ell_dispatch(int64_t m, int64_t m_pad, int K, const int32_t *ecol, c
     if (m == 0) return SPMV_OK;
     if (block <= 0) block = 256;
     constexpr int W = kWideRows<T>;
+    const bool past = NT && (uint64_t)K * m_pad * (sizeof(T) + 4) > kHbmBytes;
     if (wide)
         ell_launch<T, NT, W>(grid_for((m + W - 1) / W, block), block, unroll, m, m_pad, K, ecol,
-                             eval, x, y, s);
+                             eval, x, y, past, s);
     else
-        ell_launch<T, NT, 1>(grid_for(m, block), block, unroll, m, m_pad, K, ecol, eval, x, y, s);
+        ell_launch<T, NT, 1>(grid_for(m, block), block, unroll, m, m_pad, K, ecol, eval, x, y,
+                             past, s);
     SMAT_LAUNCHED("ell");
     return SPMV_OK;
 }
@@ -878,20 +882,20 @@ spmv_status ell_dispatch(int64_t m, int64_t m_pad, int K, const int32_t *ecol, c
 template <typename T, bool NT, int V>
 void dia_launch(bool lds, unsigned g, int block, int rpt, size_t sh, int64_t m, int64_t n,
                 int64_t m_pad, int D, const int32_t *offs, int nwin, const DiaWindow *win,
-                const T *data, const T *x, T *y, hipStream_t s) {
+                const T *data, const T *x, T *y, bool past, hipStream_t s) {
     if (lds) {
         switch (rpt) {
-        case 1: k_dia_lds<T, 1, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y); break;
-        case 2: k_dia_lds<T, 2, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y); break;
-        case 4: k_dia_lds<T, 4, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y); break;
-        default: k_dia_lds<T, 8, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y); break;
+        case 1: k_dia_lds<T, 1, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y, past); break;
+        case 2: k_dia_lds<T, 2, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y, past); break;
+        case 4: k_dia_lds<T, 4, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y, past); break;
+        default: k_dia_lds<T, 8, NT, V><<<g, block, sh, s>>>(m, n, m_pad, offs, nwin, win, data, x, y, past); break;
         }
     } else {
         switch (rpt) {
-        case 1: k_dia_direct<T, 1, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y); break;
-        case 2: k_dia_direct<T, 2, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y); break;
-        case 4: k_dia_direct<T, 4, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y); break;
-        default: k_dia_direct<T, 8, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y); break;
+        case 1: k_dia_direct<T, 1, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y, past); break;
+        case 2: k_dia_direct<T, 2, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y, past); break;
+        case 4: k_dia_direct<T, 4, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y, past); break;
+        default: k_dia_direct<T, 8, NT, V><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y, past); break;
         }
     }
 }
@@ -909,14 +913,16 @@ spmv_status dia_dispatch(bool lds, int64_t m, int64_t n, int64_t m_pad, int D,
     int64_t tile = (int64_t)block * rpt * V;
     unsigned g = grid_for(m, (int)tile);
     size_t sh = lds ? (size_t)(tile + max_span) * sizeof(T) : 0;
-    // values that the Infinity Cache cannot hold, at the default tile
+    // values from HBM, at the default tile
     constexpr int G = kDiaLaneRows / W;
-    if (!lds && wide && rpt == G && (uint64_t)D * m_pad * sizeof(T) > kDiaGroupBytes)
-        k_dia_groups<T, G, NT, W><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y);
+    const uint64_t bytes = (uint64_t)D * m_pad * sizeof(T);
+    const bool past = NT && bytes > kHbmBytes;
+    if (!lds && wide && rpt == G && bytes > kHbmBytes)
+        k_dia_groups<T, G, NT, W><<<g, block, 0, s>>>(m, n, m_pad, D, offs, data, x, y, past);
     else if (wide)
-        dia_launch<T, NT, W>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, s);
+        dia_launch<T, NT, W>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, past, s);
     else
-        dia_launch<T, NT, 1>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, s);
+        dia_launch<T, NT, 1>(lds, g, block, rpt, sh, m, n, m_pad, D, offs, nwin, win, data, x, y, past, s);
     SMAT_LAUNCHED(lds ? "dia_lds" : "dia_direct");
     return SPMV_OK;
 }

@@ -181,6 +181,30 @@ __device__ __forceinline__ void ld_rows(const T *p, T (&v)[V]) {
     }
 }
 
+// Rows i0 .. i0+V-1 of y as one store away from the end; y is only
+// element-aligned.  past: around the caches (kHbmBytes).
+template <typename T, int V>
+__device__ __forceinline__ void st_rows(T *y, int64_t i0, int64_t m, const double (&acc)[V],
+                                        bool past) {
+    if (V > 1 && i0 + V <= m) {
+        typedef T vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+        vec w;
+#pragma unroll
+        for (int e = 0; e < V; ++e) w[e] = (T)acc[e];
+        if (past) {
+            asm volatile("");   // on both sides: the compiler would merge the two
+            __builtin_nontemporal_store(w, reinterpret_cast<vec *>(y + i0));
+            asm volatile("");   // stores into a plain one
+        } else {
+            *reinterpret_cast<vec *>(y + i0) = w;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+            if (i0 + e < m) y[i0 + e] = (T)acc[e];
+    }
+}
+
 // ELL rows i0 .. i0+V-1 of one lane (i0 a multiple of V, i0 < m): the slot
 // columns and values of the V rows come in one load each.  Each row's sum
 // runs over its slots in order, exactly as ell_row.
@@ -230,7 +254,8 @@ __device__ __forceinline__ void dia_tile_lds(int64_t r0, int64_t m, int64_t n, i
                                              const int32_t *__restrict__ offs, int nwin,
                                              const DiaWindow *__restrict__ win,
                                              const T *__restrict__ data,
-                                             const T *__restrict__ x, T *__restrict__ y, T *xs) {
+                                             const T *__restrict__ x, T *__restrict__ y, T *xs,
+                                             bool past = false) {
     const int R = blockDim.x * RPT * V;
     double acc[RPT][V];
 #pragma unroll
@@ -266,9 +291,7 @@ __device__ __forceinline__ void dia_tile_lds(int64_t r0, int64_t m, int64_t n, i
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int64_t i0 = r0 + (int64_t)(threadIdx.x + q * blockDim.x) * V;
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (i0 + e < m) y[i0 + e] = (T)acc[q][e];
+        st_rows<T, V>(y, i0, m, acc[q], past);
     }
 }
 
@@ -277,7 +300,8 @@ template <typename T, int RPT, bool NT, int V = 1>
 __device__ __forceinline__ void dia_tile_direct(int64_t r0, int64_t m, int64_t n, int64_t m_pad,
                                                 int D, const int32_t *__restrict__ offs,
                                                 const T *__restrict__ data,
-                                                const T *__restrict__ x, T *__restrict__ y) {
+                                                const T *__restrict__ x, T *__restrict__ y,
+                                                bool past = false) {
     double acc[RPT][V];
 #pragma unroll
     for (int q = 0; q < RPT; ++q)
@@ -315,9 +339,7 @@ __device__ __forceinline__ void dia_tile_direct(int64_t r0, int64_t m, int64_t n
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int64_t i0 = r0 + (int64_t)(threadIdx.x + q * blockDim.x) * V;
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (i0 + e < m) y[i0 + e] = (T)acc[q][e];
+        st_rows<T, V>(y, i0, m, acc[q], past);
     }
 }
 
@@ -397,7 +419,7 @@ template <typename T, int RPT, bool NT, int V>
 __device__ __forceinline__ void dia_tile_groups(int64_t r0, int64_t m, int64_t n, int64_t m_pad,
                                                 int D, const int32_t *__restrict__ offs,
                                                 const T *__restrict__ data,
-                                                const T *__restrict__ x, T *__restrict__ y) {
+                                                const T *__restrict__ x, T *__restrict__ y, bool past) {
     double acc[RPT][V];
 #pragma unroll
     for (int q = 0; q < RPT; ++q)
@@ -412,9 +434,7 @@ __device__ __forceinline__ void dia_tile_groups(int64_t r0, int64_t m, int64_t n
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int64_t i0 = r0 + (int64_t)(threadIdx.x + q * blockDim.x) * V;
-#pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (i0 + e < m) y[i0 + e] = (T)acc[q][e];
+        st_rows<T, V>(y, i0, m, acc[q], past);
     }
 }
 
