@@ -972,19 +972,20 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     SMAT_TRY(V.ex_meta.alloc(sizeof(uint32_t) * (size_t)(nb * (E / expand_per(elt)))));
     SMAT_TRY(V.ex_slot.alloc(sizeof(uint16_t) * (size_t)(nb * E)));
     SMAT_TRY(V.ex_val.alloc((size_t)elt * (size_t)(nb * E)));
-    SMAT_TRY(V.ex_piece.alloc(sizeof(int32_t) * (size_t)(nb * stride)));
+    SMAT_TRY(V.ex_runs.alloc(sizeof(int2) * (size_t)(nb * NP)));
     SMAT_TRY(V.ex_rp.alloc(sizeof(int32_t) * (size_t)(m + 1)));
     SMAT_HIP(hipMemcpyAsync(V.ex_rp.p, rp, sizeof(int32_t) * (size_t)(m + 1),
                             hipMemcpyDeviceToDevice, s));
     SMAT_TRY(launch_expand_fill(elt, m, nb, NP, lmax, lg, rp, col, P.val.p, spos.as<int32_t>(),
                                 V.ex_blocks.as<ExpandBlock>(), runs.as<int32_t>(), stride,
                                 V.ex_off.as<uint16_t>(), V.ex_meta.as<uint32_t>(),
-                                V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
-                                s));
+                                V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_runs.as<int2>(), s));
     SMAT_HIP(hipStreamSynchronize(s));
     V.expand = true;
     V.ex_P = NP;
     V.ex_stride = stride;
+    // lanes that copy a run of one panel's pieces into LDS: the mean run
+    while (V.ex_lr < 6 && ((int64_t)NP * nb << V.ex_lr) <= pieces) ++V.ex_lr;
     V.ex_lmax = lmax;
     V.ex_nb = nb;
     V.ex_nchunks = (int64_t)chunks.size();
@@ -1441,8 +1442,9 @@ spmv_status run_variant(const spmv_plan_s &P, const Variant &V, const void *x, v
             const ExpandRun r{V.ex_nchunks, V.ex_nb, V.ex_chunks.as<ExpandChunk>(),
                               V.ex_starts.as<int32_t>(), V.ex_off.as<uint16_t>(), V.ex_xe.p,
                               V.ex_blocks.as<ExpandBlock>(), V.ex_meta.as<uint32_t>(),
-                              V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_piece.as<int32_t>(),
-                              V.ex_stride, nt && V.ex_off.bytes + V.ex_xe.bytes > kExpandNt1Bytes,
+                              V.ex_slot.as<uint16_t>(), V.ex_val.p, V.ex_runs.as<int2>(),
+                              V.ex_P, V.ex_lr, V.ex_stride,
+                              nt && V.ex_off.bytes + V.ex_xe.bytes > kExpandNt1Bytes,
                               nt};
             const TileRun t = tile_run(V);
             SMAT_TRY(run_expand(elt, r, V.long_tiles ? &t : nullptr, x, P.n, y, s));
@@ -2593,10 +2595,10 @@ extern "C" spmv_status spmv_convert_roundtrip(spmv_plan_t P, int32_t *rp, int32_
                                         hipMemcpyDeviceToDevice, s));
             }
             SMAT_TRY(launch_expand_to_csr(elt, V.ex_nb, V.ex_P, V.ex_lmax,
-                                          V.ex_rp.as<int32_t>(), V.ex_starts.as<int32_t>(),
-                                          V.ex_blocks.as<ExpandBlock>(), V.ex_off.as<uint16_t>(),
+                                          V.ex_rp.as<int32_t>(), V.ex_blocks.as<ExpandBlock>(),
+                                          V.ex_off.as<uint16_t>(),
                                           V.ex_slot.as<uint16_t>(), V.ex_val.p,
-                                          V.ex_piece.as<int32_t>(), V.ex_stride, col, val, s));
+                                          V.ex_runs.as<int2>(), col, val, s));
             break;
         }
         SMAT_TRY(launch_panels_to_csr(m, V.bin_rows.as<int32_t>(), V.P, V.prow.as<int32_t>(),

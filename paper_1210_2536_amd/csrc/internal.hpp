@@ -295,13 +295,12 @@ spmv_status launch_expand_fill(int elt, int64_t m, int64_t nb, int P, int32_t lm
                                const int32_t *rp, const int32_t *col, const void *val,
                                const int32_t *spos, const ExpandBlock *blocks,
                                const int32_t *runs, int pieces_stride, uint16_t *off,
-                               uint32_t *meta, uint16_t *slot, void *oval, int32_t *piece,
+                               uint32_t *meta, uint16_t *slot, void *oval, int2 *run,
                                hipStream_t s);
 spmv_status launch_expand_to_csr(int elt, int64_t nb, int P, int32_t lmax, const int32_t *rp,
-                                 const int32_t *starts, const ExpandBlock *blocks,
-                                 const uint16_t *off, const uint16_t *slot, const void *oval,
-                                 const int32_t *piece, int pieces_stride, int32_t *col, void *val,
-                                 hipStream_t s);
+                                 const ExpandBlock *blocks, const uint16_t *off,
+                                 const uint16_t *slot, const void *oval, const int2 *runs,
+                                 int32_t *col, void *val, hipStream_t s);
 // Both steps: every row of the blocks but those longer than lmax, which the
 // tiles `t`, if given, take in the same two launches.  nt1, nt: the first and
 // second step's streams are read past the caches.
@@ -315,8 +314,8 @@ struct ExpandRun {
     const uint32_t *meta;
     const uint16_t *slot;
     const void *val;
-    const int32_t *piece;
-    int stride;
+    const int2 *runs;
+    int P, lr, stride;
     bool nt1, nt;
 };
 spmv_status run_expand(int elt, const ExpandRun &r, const TileRun *t, const void *x, int64_t n,

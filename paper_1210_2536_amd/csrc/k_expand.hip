@@ -11,18 +11,19 @@
 //           panel offset in, a value of x out, both streams contiguous.
 //   rows    a workgroup takes a row block (consecutive rows with at most
 //           kRowsThreads * PER entries), copies the block's pieces of xe
-//           into LDS (one contiguous piece per panel), and walks the block's
-//           entries in row order, each naming its LDS slot with 16 bits.
+//           into LDS (one contiguous run per panel, 8 bytes to say where;
+//           4 bytes per piece until then cost 4-6% of the matrices below),
+//           and walks the block's entries in row order, each naming its LDS
+//           slot with 16 bits.
 //
 // Both gathers are LDS reads, so an entry costs 2 + s bytes in the first
-// step and 2 s + 2 (+ 4 / G slot addresses) in the second, all of it
-// streamed.  x is only copied in between, so a row is summed in float64 from
+// step and 2 s + 2 in the second, all of it streamed.  x is only copied in between, so a row is summed in float64 from
 // the same products as in any other CSR kernel.
 //
-// Measured (MI355X): uniform 33 a row, n = 730k, float32 32 + 52 us (5.3 and
-// 5.2 TB/s), float64 55 + 84 us, where slot-major ELL takes 118 and 190 us and
+// Measured (MI355X): uniform 33 a row, n = 730k, float32 33 + 48 us (5.2 and
+// 5.3 TB/s), float64 52 + 79 us, where slot-major ELL takes 118 and 190 us and
 // the XCD panels 143 and 222 us; the 7.98M rows of up to 1024 entries of a Zipf
-// matrix with n = 8M, float32, 117 + 252 us for 968 + 102 us by XCD panels.
+// matrix with n = 8M, float32, 117 + 240 us for 968 + 102 us by XCD panels.
 // Rows as plain blocks of 16384 (8192 float64) entries: shrinking the blocks
 // so that their number fills the last round of resident workgroups was no
 // faster (n = 300k float32 39 -> 44 us: a block's fixed cost outweighs the
@@ -152,15 +153,15 @@ template <typename T, int PER, bool NT>
 __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
     const ExpandBlock *__restrict__ blocks, const uint32_t *__restrict__ meta,
     const uint16_t *__restrict__ slot, const T *__restrict__ val,
-    const int32_t *__restrict__ piece, int pieces_stride, const T *__restrict__ xe,
-    T *__restrict__ y, unsigned sums, int64_t n7, int64_t P, const int32_t *__restrict__ lrows,
-    const double *__restrict__ part) {
+    const int2 *__restrict__ runs, int P, int lr, int pieces_stride, const T *__restrict__ xe,
+    T *__restrict__ y, unsigned sums, int64_t n7, int64_t nparts,
+    const int32_t *__restrict__ lrows, const double *__restrict__ part) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (blockIdx.x >= sums) {
         constexpr int kThreads = kReduceRows * kReduceGroups, kParts = kRowsThreads / kThreads;
         typedef double gs_t[kReduceGroups][kReduceRows];
         const unsigned sub = threadIdx.x / kThreads;
-        tiles_reduce_block<T>((blockIdx.x - sums) * kParts + sub, threadIdx.x % kThreads, n7, P,
+        tiles_reduce_block<T>((blockIdx.x - sums) * kParts + sub, threadIdx.x % kThreads, n7, nparts,
                               lrows, part, y, reinterpret_cast<gs_t *>(smem)[sub]);
         return;
     }
@@ -200,19 +201,32 @@ __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
             vv[q] = ld<NT>(reinterpret_cast<const vec *>(
                 val + expand_at<PER, G>(b, t * PER + q * G)));
     }
-    constexpr int PQ = (kRowsPieces + kRowsThreads - 1) / kRowsThreads;
-    const int32_t *pc = piece + b * pieces_stride;
+    // the block's run of each panel by 1 << lr lanes, four runs of a lane at once
     const vec *xp = reinterpret_cast<const vec *>(xe);
-    int32_t at[PQ];
+    const int2 *run = runs + b * P;
+    constexpr int A = 4;
+    const int lanes = 1 << lr, groups = kRowsThreads >> lr;
+    for (int p0 = t >> lr; p0 < P; p0 += A * groups) {
+        int32_t from[A], to[A], left[A], most = 0;
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-        const int k = q * kRowsThreads + t;
-        at[q] = k < blk.pieces ? ld<NT>(pc + k) : 0;
-    }
+        for (int q = 0; q < A; ++q) {
+            const int p = p0 + q * groups;
+            const int2 d = p < P ? run[p] : int2{0, 0};
+            const int i = t & (lanes - 1);
+            from[q] = d.x + i;
+            to[q] = (d.y & 0xFFFF) + i;
+            left[q] = (int)((unsigned)d.y >> 16) - i;
+            most = max(most, left[q]);
+        }
+        for (int o = 0; o < most; o += lanes) {
+            vec w[A];
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-        const int k = q * kRowsThreads + t;
-        if (k < blk.pieces) xv[k] = xp[at[q]];
+            for (int q = 0; q < A; ++q)
+                if (o < left[q]) w[q] = xp[from[q] + o];
+#pragma unroll
+            for (int q = 0; q < A; ++q)
+                if (o < left[q]) xv[to[q] + o] = w[q];
+        }
     }
     if (t == 0) {
         vec z;
@@ -360,7 +374,7 @@ __global__ __launch_bounds__(1024) void k_expand_fill(
     const int32_t *__restrict__ spos, const ExpandBlock *__restrict__ blocks,
     const int32_t *__restrict__ runs, int pieces_stride, uint16_t *__restrict__ off,
     uint32_t *__restrict__ meta, uint16_t *__restrict__ slot, U *__restrict__ oval,
-    int32_t *__restrict__ piece) {
+    int2 *__restrict__ run) {
     extern __shared__ int lds[];
     // per panel: entries placed, first piece in LDS, first piece of all
     int *cur = lds, *base = lds + P, *first = lds + 2 * P;
@@ -428,7 +442,7 @@ __global__ __launch_bounds__(1024) void k_expand_fill(
         const int64_t s = first[p];
         const int c = runs[(int64_t)p * nb + b + 1] - (int)s;
         for (int k = cur[p]; k < c * G; ++k) off[s * G + k] = 0;
-        for (int k = 0; k < c; ++k) piece[b * pieces_stride + base[p] + k] = (int32_t)s + k;
+        run[b * P + p] = int2{(int32_t)s, (int)((unsigned)base[p] | (unsigned)c << 16)};
     }
     const unsigned w = bits[t * PER / 32] >> (t * PER % 32) & ((1u << PER) - 1u);
     scan[t] = __popc(w);
@@ -443,18 +457,17 @@ __global__ __launch_bounds__(1024) void k_expand_fill(
 }
 
 // CSR entries of the rows in blocks, rebuilt from the two steps' arrays: an
-// entry's slot gives its piece, the piece its place in the expanded order,
-// that place its panel and offset.
+// entry's slot lies in its panel's run, which says where the entry's offset is.
 template <typename U, int W, int G, int PER>
 __global__ __launch_bounds__(1024) void k_expand_to_csr(
-    int P, int32_t lmax, const int32_t *__restrict__ rp, const int32_t *__restrict__ starts,
-    const ExpandBlock *__restrict__ blocks, const uint16_t *__restrict__ off,
-    const uint16_t *__restrict__ slot, const U *__restrict__ oval,
-    const int32_t *__restrict__ piece, int pieces_stride, int32_t *__restrict__ col,
+    int P, int32_t lmax, const int32_t *__restrict__ rp, const ExpandBlock *__restrict__ blocks,
+    const uint16_t *__restrict__ off, const uint16_t *__restrict__ slot,
+    const U *__restrict__ oval, const int2 *__restrict__ runs, int32_t *__restrict__ col,
     U *__restrict__ val) {
     const int64_t b = blockIdx.x;
     const ExpandBlock blk = blocks[b];
     if (threadIdx.x) return;
+    const int2 *run = runs + b * P;
     int q = 0;
     for (int64_t r = blk.row0; r < (int64_t)blk.row0 + blk.rows; ++r) {
         const int32_t e0 = rp[r], len = rp[r + 1] - e0;
@@ -463,17 +476,17 @@ __global__ __launch_bounds__(1024) void k_expand_to_csr(
             continue;
         }
         for (int32_t e = 0; e < len; ++e, ++q) {
-            const int s = slot[expand_at<PER, kSlotVec>(b, q)];
-            const int32_t at = piece[b * pieces_stride + s / G];
-            int lo = 0, hi = P - 1;   // last panel starting at or before the piece
+            const int s = slot[expand_at<PER, kSlotVec>(b, q)], k = s / G;
+            int lo = 0, hi = P - 1;   // last panel whose run starts at or before the piece
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (starts[mid] <= at)
+                if ((run[mid].y & 0xFFFF) <= k)
                     lo = mid;
                 else
                     hi = mid - 1;
             }
-            col[e0 + e] = lo * W + off[(int64_t)at * G + s % G];
+            const int64_t at = run[lo].x + (k - (run[lo].y & 0xFFFF));
+            col[e0 + e] = lo * W + off[at * G + s % G];
             val[e0 + e] = oval[expand_at<PER, G>(b, q)];
         }
     }
@@ -536,35 +549,32 @@ spmv_status launch_expand_fill(int elt, int64_t m, int64_t nb, int P, int32_t lm
                                const int32_t *rp, const int32_t *col, const void *val,
                                const int32_t *spos, const ExpandBlock *blocks,
                                const int32_t *runs, int pieces_stride, uint16_t *off,
-                               uint32_t *meta, uint16_t *slot, void *oval, int32_t *piece,
+                               uint32_t *meta, uint16_t *slot, void *oval, int2 *run,
                                hipStream_t s) {
     const size_t sh = 3 * sizeof(int) * (size_t)P;
     if (elt == 8)
         k_expand_fill<uint64_t, kExpandBytes / 8, 2, 8><<<(unsigned)nb, 1024, sh, s>>>(
             m, nb, P, lmax, lg, rp, col, (const uint64_t *)val, spos, blocks, runs, pieces_stride,
-            off, meta, slot, (uint64_t *)oval, piece);
+            off, meta, slot, (uint64_t *)oval, run);
     else
         k_expand_fill<uint32_t, kExpandBytes / 4, 4, 16><<<(unsigned)nb, 1024, sh, s>>>(
             m, nb, P, lmax, lg, rp, col, (const uint32_t *)val, spos, blocks, runs, pieces_stride,
-            off, meta, slot, (uint32_t *)oval, piece);
+            off, meta, slot, (uint32_t *)oval, run);
     SMAT_LAUNCHED("expand_fill");
     return SPMV_OK;
 }
 
 spmv_status launch_expand_to_csr(int elt, int64_t nb, int P, int32_t lmax, const int32_t *rp,
-                                 const int32_t *starts, const ExpandBlock *blocks,
-                                 const uint16_t *off, const uint16_t *slot, const void *oval,
-                                 const int32_t *piece, int pieces_stride, int32_t *col, void *val,
-                                 hipStream_t s) {
+                                 const ExpandBlock *blocks, const uint16_t *off,
+                                 const uint16_t *slot, const void *oval, const int2 *runs,
+                                 int32_t *col, void *val, hipStream_t s) {
     if (nb == 0) return SPMV_OK;
     if (elt == 8)
         k_expand_to_csr<uint64_t, kExpandBytes / 8, 2, 8><<<(unsigned)nb, 64, 0, s>>>(
-            P, lmax, rp, starts, blocks, off, slot, (const uint64_t *)oval, piece, pieces_stride,
-            col, (uint64_t *)val);
+            P, lmax, rp, blocks, off, slot, (const uint64_t *)oval, runs, col, (uint64_t *)val);
     else
         k_expand_to_csr<uint32_t, kExpandBytes / 4, 4, 16><<<(unsigned)nb, 64, 0, s>>>(
-            P, lmax, rp, starts, blocks, off, slot, (const uint32_t *)oval, piece, pieces_stride,
-            col, (uint32_t *)val);
+            P, lmax, rp, blocks, off, slot, (const uint32_t *)oval, runs, col, (uint32_t *)val);
     SMAT_LAUNCHED("expand_to_csr");
     return SPMV_OK;
 }
@@ -596,7 +606,7 @@ static spmv_status expand_dispatch(const ExpandRun &r, const TileRun *t, const T
         const size_t sh = std::max(((size_t)r.stride + 1) * 16, sums_lds);
 #define ROWS(NT)                                                                             \
     k_panel_rows<T, PER, NT><<<second, kRowsThreads, sh, s>>>(                               \
-        r.blocks, r.meta, r.slot, (const T *)r.val, r.piece, r.stride, (const T *)r.xe, y,   \
+        r.blocks, r.meta, r.slot, (const T *)r.val, r.runs, r.P, r.lr, r.stride,                     (const T *)r.xe, y,                                                                  \
         (unsigned)r.nb, t ? t->n7 : 0, t ? t->P : 0, t ? t->rows : nullptr, t ? t->part : nullptr)
         if (r.nt)
             ROWS(true);

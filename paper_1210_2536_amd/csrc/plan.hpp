@@ -129,11 +129,11 @@ struct Variant {
     Dev tile_blocks, tile_start, tile_meta, tile_part, tile_off, tile_val;
     // column panels in two steps: rows of at most ex_lmax entries
     bool expand = false;
-    int ex_P = 0, ex_stride = 0;
+    int ex_P = 0, ex_stride = 0, ex_lr = 0;
     int32_t ex_lmax = 0;
     int64_t ex_nb = 0, ex_nchunks = 0;
     AdaptiveLaunch along{};   // the longer rows, a workgroup each
-    Dev ex_rp, ex_off, ex_xe, ex_chunks, ex_blocks, ex_meta, ex_slot, ex_val, ex_piece, ex_starts;
+    Dev ex_rp, ex_off, ex_xe, ex_chunks, ex_blocks, ex_meta, ex_slot, ex_val, ex_runs, ex_starts;
     // BCSR 4x4
     Dev brp, bcol, bval, bpres;
     int64_t nblocks = 0;
@@ -146,7 +146,7 @@ struct Variant {
                tile_blocks.bytes + tile_start.bytes + tile_meta.bytes + tile_part.bytes +
                tile_off.bytes + tile_val.bytes + binned_rp.bytes + binned_col.bytes +
                binned_val.bytes + ex_rp.bytes + ex_off.bytes + ex_xe.bytes + ex_chunks.bytes +
-               ex_blocks.bytes + ex_meta.bytes + ex_slot.bytes + ex_val.bytes + ex_piece.bytes +
+               ex_blocks.bytes + ex_meta.bytes + ex_slot.bytes + ex_val.bytes + ex_runs.bytes +
                ex_starts.bytes;
     }
 };

@@ -126,3 +126,20 @@ def test_other_forms_stay_as_asked():
         q = Plan(t(rp.astype(np.int32)), t(col), t(val), n=30_000, selector="csr_panel",
                  params=got)
         assert q.info()["params"] == got
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("panels", [1, 3, 65, 260, 900])
+def test_runs_of_panels(dtype, panels):
+    """A row block's runs of xe per panel: empty ones, ones of a lane, ones
+    longer than the lanes that copy them, and more than are copied at once."""
+    rng = np.random.default_rng([75, panels])
+    W = PANEL[dtype]
+    n = panels * W - 7
+    rows = []
+    for r in range(2500):
+        a = rng.integers(0, min(n, W), size=r % 7)           # the first panel
+        b = rng.integers(0, panels, size=r % 13) // 3 * 3 * W + rng.integers(0, W, size=r % 13)
+        rows.append(np.unique(np.concatenate([a, b[b < n]])))
+    rp = np.concatenate([[0], np.cumsum([c.size for c in rows])])
+    _check(rp, np.concatenate(rows).astype(np.int32), n, dtype, rng, f"panels={panels}")
