@@ -125,15 +125,9 @@ __device__ T block_reduce(T v, Op op, T *lds, T identity) {
 }
 
 struct OpAdd { template <typename T> __device__ T operator()(T a, T b) const { return a + b; } };
-struct OpMax { template <typename T> __device__ T operator()(T a, T b) const { return a > b ? a : b; } };
-struct OpMin { template <typename T> __device__ T operator()(T a, T b) const { return a < b ? a : b; } };
 
-// An atomic maximum / minimum that costs nothing where it changes nothing.
-__device__ __forceinline__ void raise_max(int *p, int v) {
-    if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
-}
-__device__ __forceinline__ void lower_min(int *p, int v) {
-    if (v < __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(p, v);
+__device__ __forceinline__ int load_word(const int *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The CSR checks with the row statistics and the bandwidth max |j - i|, which
@@ -149,12 +143,13 @@ __global__ __launch_bounds__(kCheckBlock) void k_check(int64_t m, int64_t n, int
                                                        const int32_t *__restrict__ col,
                                                        uint32_t *flags, uint32_t *flags2,
                                                        RowStats *rs, int *bandwidth) {
-    __shared__ unsigned long long lds_u[kCheckBlock / kWave];
-    __shared__ int lds_i[kCheckBlock / kWave];
+    constexpr int kWaves = kCheckBlock / kWave;
+    __shared__ unsigned long long w2[kWaves];
+    __shared__ int wx[kWaves], wn[kWaves], wb[kWaves];
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t threads = (int64_t)gridDim.x * blockDim.x;
     uint32_t bad = 0, bad2 = 0;
-    unsigned long long s1 = 0, s2 = 0;
+    unsigned long long s2 = 0;
     int mx = 0, mn = INT_MAX, bw = 0;
     for (int64_t i = t; i <= m; i += threads) {
         const int32_t v = rp[i];
@@ -164,7 +159,6 @@ __global__ __launch_bounds__(kCheckBlock) void k_check(int64_t m, int64_t n, int
         if (i < m) {
             const int32_t k = rp[i + 1] - v;
             if (rp[i + 1] < v) bad |= kBadRowPtrOrder;
-            s1 += (unsigned long long)k;
             s2 += (unsigned long long)k * (unsigned long long)k;
             mx = k > mx ? k : mx;
             mn = k < mn ? k : mn;
@@ -192,17 +186,40 @@ __global__ __launch_bounds__(kCheckBlock) void k_check(int64_t m, int64_t n, int
     });
     if (bad) atomicOr(flags, bad);
     if (bad2) atomicOr(flags2, bad2);
-    s1 = block_reduce(s1, OpAdd(), lds_u, 0ull);
-    s2 = block_reduce(s2, OpAdd(), lds_u, 0ull);
-    mx = block_reduce(mx, OpMax(), lds_i, 0);
-    mn = block_reduce(mn, OpMin(), lds_i, INT_MAX);
-    bw = block_reduce(bw, OpMax(), lds_i, 0);
-    if (threadIdx.x == 0) {
-        atomicAdd(&rs->sum_rd, s1);
+    // all four across the workgroup with one exchange
+    auto wave = [&](int from) {
+        for (int off = from; off > 0; off >>= 1) {
+            s2 += __shfl_xor(s2, off, kWave);
+            mx = max(mx, __shfl_xor(mx, off, kWave));
+            mn = min(mn, __shfl_xor(mn, off, kWave));
+            bw = max(bw, __shfl_xor(bw, off, kWave));
+        }
+    };
+    wave(kWave / 2);
+    const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    if (lane == 0) {
+        w2[w] = s2;
+        wx[w] = mx;
+        wn[w] = mn;
+        wb[w] = bw;
+    }
+    __syncthreads();
+    if (w > 0) return;
+    s2 = lane < kWaves ? w2[lane] : 0ull;
+    mx = lane < kWaves ? wx[lane] : 0;
+    mn = lane < kWaves ? wn[lane] : INT_MAX;
+    bw = lane < kWaves ? wb[lane] : 0;
+    wave(kWaves / 2);
+    if (lane == 0) {
+        // the rows' lengths add up to nnz wherever the checks pass
+        if (blockIdx.x == 0) rs->sum_rd = (unsigned long long)nnz;
+        // what the others found so far, read together: an atomic that changes
+        // nothing is left out, and the words of all workgroups lie in one line
+        const int gx = load_word(&rs->max_rd), gn = load_word(&rs->min_rd), gb = load_word(bandwidth);
         atomicAdd(&rs->sum_rd2, s2);
-        raise_max(&rs->max_rd, mx);
-        lower_min(&rs->min_rd, mn);
-        raise_max(bandwidth, bw);
+        if (mx > gx) atomicMax(&rs->max_rd, mx);
+        if (mn < gn) atomicMin(&rs->min_rd, mn);
+        if (bw > gb) atomicMax(bandwidth, bw);
     }
 }
 
@@ -380,7 +397,8 @@ __global__ __launch_bounds__(kStatsBlock) void k_entry_stats(
     if (census) {
         __syncthreads();
         if (spill && spilled) {
-            if (threadIdx.x == 0) atomicOr(spill, 1u);
+            if (threadIdx.x == 0 && !load_word(reinterpret_cast<const int *>(spill)))
+                atomicOr(spill, 1u);
             return;
         }
         for (int b = threadIdx.x; b < kHash + kProbes; b += blockDim.x)
