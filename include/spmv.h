@@ -155,22 +155,27 @@ typedef struct {
                                    tile_row_min):
                                    x cut into 80 KB panels, one workgroup
                                    per (row block, panel) holding its panel
-                                   in LDS, one float64 partial per (row,
-                                   panel), the partials added in a fixed
-                                   order by a second kernel; 2 = binned
-                                   launch; 0 = default (tiles from 1024
-                                   rows longer than 1024, else 2).  Tiles
+                                   in LDS and summing the block's entries in
+                                   it by equal shares of its threads, one
+                                   float64 partial per (row, panel), the
+                                   partials added in a fixed order in the
+                                   launch that follows; 2 = binned launch;
+                                   0 = default (tiles from 10 MB of values
+                                   in such rows, else 2).  Tiles
                                    fall back to chunks
-                                   (float64) or 2 where their partials and
-                                   segment starts would exceed 1/5 of the
-                                   long rows' bytes per run or no lane count
-                                   keeps the 1e-12 bound; chunks fall back
+                                   (float64) or 2 where their partials
+                                   would exceed 1/5 of the
+                                   long rows' bytes per run or the panels
+                                   are too many for the 1e-12 bound; chunks
+                                   fall back
                                    to 2 in float32 and for rows too long for
                                    the bound with 64 lanes per row          */
     int32_t tile_row_min;       /* CSR_ADAPTIVE and CSR_PANEL with long-row
                                    tiles: the rows longer than this many
-                                   entries go to the tiles (0 = default
-                                   1024; at least 64)                      */
+                                   entries go to the tiles (at least 64;
+                                   0 = default: by the panel count, 256 to
+                                   4096, doubled while the partials would
+                                   cost too much)                          */
     int32_t panel_direct_max;   /* CSR_PANEL: rows of at most this many
                                    entries (rounded down to a length-bin
                                    boundary) skip the column panels -- no
@@ -327,8 +332,8 @@ typedef struct {
                                            point's (0 when all agree)      */
     int32_t long_lanes;                 /* params.long_lds 1 or 3 in effect:
                                            lanes per long row (chunks: 32 or
-                                           64; tiles: the most of any row
-                                           block, 8-64), else 0             */
+                                           64; tiles: 64, shared by rows),
+                                           else 0                           */
     int64_t long_rows;                  /* rows taken by that kernel        */
     /* opts.time_baseline = 1 (else -1): median time of one run of the plan
      * and of the plain CSR kernel on the same matrix, and the break-even

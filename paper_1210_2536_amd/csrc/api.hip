@@ -1213,7 +1213,7 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         // for a kernel that keeps x in LDS: x chunks streamed through each
         // workgroup of rows (long_lds 1, float64) or one x panel per (row
         // block, panel) workgroup (long_lds 3).  Default: tiles from
-        // kTileRowsDefault rows longer than tile_row_min.  Tiles that do not
+        // kTileBytesDefault of values in rows longer than tile_row_min.  Tiles that do not
         // suit the matrix fall back to chunks where those keep the float64
         // chain bound, else to the binned launch.
         int ll = prm.long_lds;

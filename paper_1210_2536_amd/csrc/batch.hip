@@ -4,9 +4,10 @@
 // independent SpMVs of one value type (up to kMaxLevels plans).  Small
 // matrices are far too small to fill the GPU on their own, so
 //   mode 0: one persistent launch; workgroup w takes the (level, tile) work
-//           items w, w + grid, w + 2 grid, ... of the list that runs through
-//           the levels in order (largest first), so consecutive workgroups
-//           share a level's tiles and no counter or atomic is involved;
+//           items w, w + grid, w + 2 grid, ... from the end of the list that
+//           runs through the levels in order (largest first), so consecutive
+//           workgroups share a level's tiles, the short levels do not run
+//           last and no counter or atomic is involved;
 //   mode 1: the per-level launches captured once into a HIP graph and
 //           replayed.
 // K12 stream copy (achievable HBM bandwidth probe) lives here as well.

@@ -136,6 +136,11 @@ __device__ __forceinline__ int load_word(const int *p) {
 // whatever row_ptr holds: rows are only looked up in rp[0..m] (m >= 1
 // whenever nnz > 0) and columns only read below nnz; a row_ptr that ends a
 // row past the last one is flagged as out of order.
+//
+// Bound by latency: the search for the first row, then columns, row starts and
+// the next row's end one after the other, and at the end one cache line that
+// every workgroup updates.  4.4M entries in 24 us; 34 with a barrier pair per
+// statistic and an atomic for each.
 constexpr int kCheckBlock = 1024, kCheckGrid = 512;   // two workgroups a compute unit
 
 __global__ __launch_bounds__(kCheckBlock) void k_check(int64_t m, int64_t n, int64_t nnz,
