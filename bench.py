@@ -211,6 +211,7 @@ def main():
                        bytes=workloads.plan_bytes(pi), confidence=pi["confidence"],
                        n_measured=pi["n_measured"], params=pi["params"],
                        feature_stage=pi["feature_stage"], long_lanes=pi["long_lanes"],
+                       max_rd=pi["features"]["max_rd"],
                        dia_bytes=pi["dia_ndiags"] * pi["m_pad"] * np.dtype(dt).itemsize)
             recs.append(dict(rec=rec, tuned=part, plain=plain if k == 0 else None, x=x,
                              y=y[r0:r0 + part.m], py=y, owner=tuned))
@@ -295,7 +296,7 @@ def main():
         # without them, then theirs
         long = ""
         if rec.get("long_lanes"):
-            long = (f" + k_long_tiles<{t}> + k_long_tiles_reduce<{t}>" if p.get("long_lds") == 3
+            long = (f" + k_long_tiles<{t}, false|true> + k_long_tiles_reduce<{t}>" if p.get("long_lds") == 3
                     else f" + k_long_rows_lds<{rec['long_lanes']}>")
         # column panels that leave their shortest rows to the binned kernel
         short = (k == "csr_panel" and
@@ -308,7 +309,7 @@ def main():
         if k == "csr_adaptive":   # rows read from the plan's copy in binned order
             if rec.get("long_lanes") and p.get("long_lds") == 3:
                 # the tiles first, then the short rows with the tiles' sums
-                return f"k_long_tiles<{t}> + k_csr_adaptive_tiles<{t}, {nt}, true>"
+                return f"k_long_tiles<{t}, false|true> + k_csr_adaptive_tiles<{t}, {nt}, true>"
             return f"k_csr_adaptive{rest}<{t}, {nt}, true>{long}"
         v = (16 // (8 if t == "double" else 4)) if p["wide_loads"] == 1 else 1
         if k == "ell":
@@ -328,8 +329,9 @@ def main():
             if p["panel_xcd"] == 0:   # two steps; rows above the blocks' limit apart
                 # rows by tiles share the two launches
                 rows = (long if p.get("long_lds") != 3 else "") if long else \
-                    f" + k_csr_adaptive_rest<{t}, {nt}, false>"
-                return f"k_panel_expand<{t}> + k_panel_rows<{t}, {nt}>{rows}"
+                    f" + k_csr_adaptive_rest<{t}, {nt}, false>" if rec["max_rd"] > 1024 else ""
+                return (f"k_panel_expand<{t}, false|true> + "
+                        f"k_panel_rows<{t}, {8 if t == 'double' else 16}, {nt}>{rows}")
             if p["panel_xcd"] != 2:
                 return f"k_csr_panel_xcd{rest}<{t}, {nt}> + k_panel_reduce{rest}<{t}>{long}"
             return f"k_csr_panel{rest}<{t}, {nt}, false|true>{long}"

@@ -18,6 +18,7 @@
 #include <cstring>
 #include <limits>
 #include <memory>
+#include <new>
 
 namespace smat {
 
@@ -895,9 +896,19 @@ constexpr uint64_t kExpandNt1Bytes = uint64_t(192) << 20;
 // kTileRowMinMax, a sixteenth to an eighth here).
 constexpr int kExpandRowMax = 1024;
 
+// They hold up to 3 s + 4 bytes an entry where the XCD panels hold s + 4 and,
+// per row, eight row pointers and partials: where the plan's storage cap lies
+// between the two, the XCD panels are built.
 bool expand_fits(const spmv_plan_s &P, const spmv_params &prm) {
     const int G = 16 / P.elt;
     const int64_t E = expand_block_entries(P.elt), NP = expand_panels(P.n, P.elt);
+    // at most: blocks, their values and slots, and pieces (a partly filled one
+    // per block and panel) with offsets and x
+    const uint64_t nb = (uint64_t)((P.nnz + P.m) / (E - kExpandRowMax) + 1);
+    const uint64_t pieces = (uint64_t)P.nnz / G + nb * NP;
+    const uint64_t bytes = nb * E * (P.elt + 2) + pieces * (16 + 2 * G) + nb * NP * 8 +
+                           (uint64_t)P.m * 4;
+    if (bytes > P.mem_cap) return false;
     return prm.panel_xcd == 0 && prm.panel_kib == 4096 && prm.panel_direct_max <= 0 && P.m > 0 &&
            P.n > 0 && P.nnz > 0 && NP <= kExpandMaxPanels && E / G + NP <= expand_max_pieces() &&
            P.nnz + P.m < (1ll << 31) - 2 * E;
@@ -992,8 +1003,8 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     return SPMV_OK;
 }
 
-spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W, int kernel,
-                          const spmv_params &prm_in, hipStream_t s, Variant &V) {
+spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W, int kernel,
+                         const spmv_params &prm_in, hipStream_t s, Variant &V) {
     const spmv_params prm = resolve_params(kernel, prm_in, F, P.elt);
     V.kernel = kernel;
     V.prm = prm;
@@ -1381,6 +1392,22 @@ spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W
         set_error("unknown kernel %d", kernel);
         return SPMV_EINVAL;
     }
+}
+
+// The chosen kernel's arrays.  Column panels in two steps take more memory
+// than the XCD panels: where it is not there, those are built instead.
+spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W, int kernel,
+                          const spmv_params &prm_in, hipStream_t s, Variant &V) {
+    const spmv_status st = build_kernel(P, F, W, kernel, prm_in, s, V);
+    if (st != SPMV_ENOMEM || kernel != SPMV_K_CSR_PANEL || prm_in.panel_xcd != 0 ||
+        !expand_fits(P, resolve_params(kernel, prm_in, F, P.elt)))
+        return st;
+    SMAT_HIP(hipStreamSynchronize(s));
+    V.~Variant();
+    new (&V) Variant();
+    spmv_params prm = prm_in;
+    prm.panel_xcd = 1;
+    return build_kernel(P, F, W, kernel, prm, s, V);
 }
 
 TileRun tile_run(const Variant &V) {
@@ -2195,6 +2222,7 @@ static spmv_status plan_create_impl(const spmv_csr *A, const spmv_plan_opts *opt
         SMAT_HIP(hipMemGetInfo(&fr, &tot));
         cap = fr / 4;
     }
+    P->mem_cap = mode == SPMV_SELECT_FORCED ? ~0ull : cap;   // forced kernels pass the cap
     spmv_params prm_base = default_params(0, F);
     if (opts.use_params) {
         merge_params(prm_base, opts.params);

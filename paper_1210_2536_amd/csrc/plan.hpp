@@ -169,6 +169,7 @@ struct spmv_plan_s {
     int device = -1;                   // the device the plan was created on
     int64_t m = 0, n = 0, nnz = 0;
     int dtype = 0, elt = 4;
+    uint64_t mem_cap = ~0ull;          // storage cap while the plan is made
     int64_t m_pad = 0;
     smat::Dev rp, col, val;             // CSR copy (CSR kernels and COO)
     bool has_csr = false;

@@ -143,3 +143,28 @@ def test_runs_of_panels(dtype, panels):
         rows.append(np.unique(np.concatenate([a, b[b < n]])))
     rp = np.concatenate([[0], np.cumsum([c.size for c in rows])])
     _check(rp, np.concatenate(rows).astype(np.int32), n, dtype, rng, f"panels={panels}")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64], ids=["f32", "f64"])
+def test_storage_cap_between_the_forms(dtype):
+    """A cap that only the XCD panels fit leaves the two steps unbuilt."""
+    import torch
+    from paper_1210_2536_amd import capi as C
+    from paper_1210_2536_amd.spmv import Plan
+    rng = np.random.default_rng(76)
+    elt = np.dtype(dtype).itemsize
+    m, n, k = 20_000, 600_000, 100
+    col = np.sort(rng.integers(0, n // k, size=(m, k)) + np.arange(k) * (n // k), axis=1)
+    rp = torch.arange(0, m * k + 1, k, dtype=torch.int32, device="cuda")
+    ci = torch.from_numpy(col.reshape(-1).astype(np.int32)).cuda()
+    va = torch.from_numpy(rng.integers(-8, 9, size=m * k).astype(dtype)).cuda()
+    x = torch.from_numpy(rng.integers(-64, 65, size=n).astype(dtype)).cuda()
+    rest = [q for q in C.KERNELS if q != "csr_panel"]
+    xcd_bytes = m * k * (elt + 4) + 16 * (m + 1) * 4 + 16 * m * elt
+    y = []
+    for cap, form in ((xcd_bytes, 1), (100 << 20, 0)):
+        p = Plan(rp, ci, va, n=n, selector="exhaustive", disable=rest, mem_cap=cap)
+        i = p.info()
+        assert i["kernel_name"] == "csr_panel" and i["params"]["panel_xcd"] == form
+        y.append(p.run(x))
+    assert torch.equal(y[0], y[1])   # whole numbers: exact in any order
