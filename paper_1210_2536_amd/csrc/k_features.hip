@@ -139,9 +139,14 @@ __device__ __forceinline__ int load_word(const int *p) {
 //
 // Bound by latency: the search for the first row, then columns, row starts and
 // the next row's end one after the other, and at the end one cache line that
-// every workgroup updates.  4.4M entries in 24 us; 34 with a barrier pair per
+// every workgroup updates.  4.4M entries in 20 us; 34 with a barrier pair per
 // statistic and an atomic for each.
-constexpr int kCheckBlock = 1024, kCheckGrid = 512;   // two workgroups a compute unit
+//
+// One workgroup a compute unit up to kCheckMany entries, two above: each ends
+// on that line.  Measured (256 | 512 workgroups): 4.4M entries 19.5 | 25.3 us,
+// 11.7M 30.9 | 33.6, 27M 87 | 68.
+constexpr int kCheckBlock = 1024, kCheckGrid = 512;
+constexpr int64_t kCheckMany = int64_t(1) << 24;
 
 __global__ __launch_bounds__(kCheckBlock) void k_check(int64_t m, int64_t n, int64_t nnz,
                                                        const int32_t *__restrict__ rp,
@@ -422,7 +427,12 @@ __global__ __launch_bounds__(kStatsBlock) void k_entry_stats(
 //   count   the entries of the other diagonals are counted (the corners'
 //           short diagonals, and those that are nearly full).
 // All exact; 19 + 18 + 22 us for those entries (and 16 until the table spills).
-constexpr int kBitsBlock = 1024, kBitsGrid = 256;
+// Bitmaps beyond one workgroup's LDS are made in kBitsParts parts, each walking
+// the entries again, from kPartsMinNnz entries on: 11.7M random entries of
+// 730k rows 56 + 43 + 43 us where the histogram took 440 (about 170 at the
+// line, as long as the bitmaps take there).
+constexpr int kBitsBlock = 1024, kBitsGrid = 256, kBitsParts = 2;
+constexpr int64_t kPartsMinNnz = int64_t(1) << 22;
 
 __global__ __launch_bounds__(kBitsBlock) void k_diag_bits(int64_t m, int64_t nnz, int words,
                                                           const int32_t *__restrict__ rp,
@@ -433,11 +443,14 @@ __global__ __launch_bounds__(kBitsBlock) void k_diag_bits(int64_t m, int64_t nnz
     if (!*spill) return;
     extern __shared__ uint32_t bits[];
     __shared__ int r0, r1;
+    // this workgroup's part of the diagonals
+    const int pw = (words + (int)gridDim.y - 1) / (int)gridDim.y, w0 = (int)blockIdx.y * pw;
+    const int wn = min(pw, words - w0);
     if (threadIdx.x == 0) {
         r0 = INT_MAX;
         r1 = -1;
     }
-    for (int w = threadIdx.x; w < words; w += kBitsBlock) bits[w] = 0;
+    for (int w = threadIdx.x; w < wn; w += kBitsBlock) bits[w] = 0;
     __syncthreads();
     int64_t lo = INT64_MAX, hi = -1;
     walk_runs(m, nnz, rp, col, [&](int64_t p0, int len, const int32_t *c, int64_t row) {
@@ -449,7 +462,8 @@ __global__ __launch_bounds__(kBitsBlock) void k_diag_bits(int64_t m, int64_t nnz
             if (j >= len) continue;
             while (p0 + j >= rend) rend = rp[++row + 1];
             const int64_t b = (int64_t)c[j] - row + m - 1;
-            atomicOr(&bits[b >> 5], 1u << (b & 31));
+            const unsigned at = (unsigned)((int)(b >> 5) - w0);
+            if (at < (unsigned)wn) atomicOr(&bits[at], 1u << (b & 31));
         }
         hi = row > hi ? row : hi;
         return true;
@@ -459,9 +473,9 @@ __global__ __launch_bounds__(kBitsBlock) void k_diag_bits(int64_t m, int64_t nnz
         atomicMax(&r1, (int)hi);
     }
     __syncthreads();
-    uint32_t *out = maps + (int64_t)blockIdx.x * words;
-    for (int w = threadIdx.x; w < words; w += kBitsBlock) out[w] = bits[w];
-    if (threadIdx.x == 0) rows[blockIdx.x] = r1 >= 0 ? r1 - r0 + 1 : 0;
+    uint32_t *out = maps + (int64_t)blockIdx.x * words + w0;
+    for (int w = threadIdx.x; w < wn; w += kBitsBlock) out[w] = bits[w];
+    if (threadIdx.x == 0 && w0 == 0) rows[blockIdx.x] = r1 >= 0 ? r1 - r0 + 1 : 0;
 }
 
 // A workgroup per 32 words: the joined words, the words of diagonals to count,
@@ -664,7 +678,8 @@ spmv_status launch_check(int64_t m, int64_t n, int64_t nnz, const int32_t *rp, c
                          hipStream_t s) {
     // enough threads for a row or a run of entries each, in whole workgroups
     const int64_t work = std::max(m + 1, (nnz + kEntryRun - 1) / kEntryRun);
-    k_check<<<grid_for(work, kCheckBlock, kCheckGrid), kCheckBlock, 0, s>>>(
+    const int64_t most = std::max(m, nnz) < kCheckMany ? kCheckGrid / 2 : kCheckGrid;
+    k_check<<<grid_for(work, kCheckBlock, most), kCheckBlock, 0, s>>>(
         m, n, nnz, rp, col, flags, flags2, rs, bandwidth);
     SMAT_LAUNCHED("check");
     return SPMV_OK;
@@ -691,7 +706,9 @@ spmv_status launch_entry_stats(int64_t m, int64_t n, int64_t nnz, const int32_t 
                                const RowStats *gate_rs, uint32_t *spill) {
     if (nnz == 0) return SPMV_OK;
     int64_t threads = (nnz + kEntryRun - 1) / kEntryRun;
-    const unsigned g = grid_for(threads, kStatsBlock, kStatsGrid);
+    // the census alone: a table a compute unit fills and spills soonest (11.7M
+    // random entries 13.0 us, 16.5 with two; the block count 188 with one, 139)
+    const unsigned g = grid_for(threads, kStatsBlock, blocks ? kStatsGrid : kStatsGrid / 2);
     if (blocks)
         k_entry_stats<true><<<g, kStatsBlock, 0, s>>>(m, n, nnz, rp, col, out, diag_hist, gate,
                                                       gate_rs, spill);
@@ -709,7 +726,9 @@ static int bits_grid(int64_t nnz) {
 
 size_t diag_bitmap_bytes(int64_t m, int64_t n, int64_t nnz) {
     const int64_t words = (m + n - 1 + 31) / 32;
-    if (words * 4 > kDiagBitmapLds || nnz < kDiagBitmapMinNnz) return 0;
+    if (words * 4 > kBitsParts * (int64_t)kDiagBitmapLds || nnz < kDiagBitmapMinNnz ||
+        (words * 4 > kDiagBitmapLds && nnz < kPartsMinNnz))
+        return 0;
     return sizeof(uint32_t) * (size_t)(words * (bits_grid(nnz) + 2) + kBitsGrid);
 }
 
@@ -721,7 +740,9 @@ spmv_status launch_diag_bitmap(int64_t m, int64_t n, int64_t nnz, const int32_t 
     int *rows = reinterpret_cast<int *>(maps + (int64_t)g * words);
     SMAT_HIP(hipFuncSetAttribute((const void *)k_diag_bits,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, kDiagBitmapLds));
-    k_diag_bits<<<g, kBitsBlock, (size_t)words * 4, s>>>(m, nnz, words, rp, col, spill, maps, rows);
+    const int parts = (int)(((int64_t)words * 4 + kDiagBitmapLds - 1) / kDiagBitmapLds);
+    k_diag_bits<<<dim3(g, parts), kBitsBlock, (size_t)((words + parts - 1) / parts) * 4, s>>>(
+        m, nnz, words, rp, col, spill, maps, rows);
     SMAT_LAUNCHED("diag_bits");
     k_diag_merge<<<(words + 31) / 32, 256, 0, s>>>(m, n, words, g, spill, maps, rows, seen, cand,
                                                    diag_hist);

@@ -24,7 +24,7 @@ def _with_diagonals(rng, m, n, per_row, diags):
 
 
 @pytest.mark.parametrize("case", ["square", "wide", "tall", "few_rows", "below_min", "lds_full",
-                                  "lds_over", "one_share"])
+                                  "lds_over", "one_share", "two_parts", "parts_over"])
 def test_census_counts(case):
     import torch
     from paper_1210_2536_amd import spmv as G
@@ -38,6 +38,8 @@ def test_census_counts(case):
         "below_min": (4000, 4000, 30, [(0, 1), (3, 0.65)]),          # under 2^17 entries
         "lds_full": (600_000, 645_185, 3, [(0, 1), (645_180, 1)]),    # 152 KiB of diagonals
         "lds_over": (600_000, 645_186, 3, [(0, 1), (-599_999, 1)]),   # one bit more
+        "two_parts": (1_100_000, 1_390_369, 4, [(0, 1), (-1_099_999, 1), (1_390_360, 1)]),
+        "parts_over": (1_100_000, 1_390_370, 4, [(0, 1), (1_390_369, 1)]),   # one bit more
         "one_share": (2000, 2000, 66, [(0, 1), (1990, 1)]),
     }[case]
     rp, col = _with_diagonals(rng, m, n, k, diags)
