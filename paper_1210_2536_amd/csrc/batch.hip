@@ -57,29 +57,32 @@ __device__ __forceinline__ void vector_tile(const LevelDesc &d, int64_t tile, co
             if (lane == 0) y[row0] = (T)acc;
         }
     } else {
-        int32_t p[R], e[R], most = 0;
+        // o runs to the longest row of the group: it is compared with what each
+        // row has left, as a position p + o would wrap where nnz lies within a
+        // row length of 2^31
+        int32_t p[R], left[R], most = 0;
         double acc[R];
 #pragma unroll
         for (int q = 0; q < R; ++q) {
             const int64_t row = min(row0 + q * per, d.m - 1);
             p[q] = d.rp[row] + lane;
-            e[q] = d.rp[row + 1];
+            left[q] = d.rp[row + 1] - p[q];
             acc[q] = 0.0;
         }
 #pragma unroll
-        for (int q = 0; q < R; ++q) most = max(most, e[q] - p[q]);
+        for (int q = 0; q < R; ++q) most = max(most, left[q]);
         for (int32_t o = 0; o < most; o += L) {
             int32_t c[R];
             T v[R];
 #pragma unroll
             for (int q = 0; q < R; ++q)
-                if (p[q] + o < e[q]) {
+                if (o < left[q]) {
                     c[q] = ld<NT>(d.col + p[q] + o);
                     v[q] = ld<NT>(val + p[q] + o);
                 }
 #pragma unroll
             for (int q = 0; q < R; ++q)
-                if (p[q] + o < e[q]) acc[q] = fma((double)v[q], (double)x[c[q]], acc[q]);
+                if (o < left[q]) acc[q] = fma((double)v[q], (double)x[c[q]], acc[q]);
         }
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -91,8 +94,8 @@ __device__ __forceinline__ void vector_tile(const LevelDesc &d, int64_t tile, co
     }
 }
 
-// Row groups of a csr_vector tile: 4 where the level still has a tile for each
-// workgroup the GPU holds, and the lanes of a row leave registers for them.
+// Row groups of a csr_vector tile with 8 lanes a row or more, where the level
+// still has four such tiles for each compute unit (spmv_batch_create); else one.
 constexpr int kPVectorRows = 2;
 
 // Level-kind sets the persistent kernel is compiled for (bit k: LevelKind
