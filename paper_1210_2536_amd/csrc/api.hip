@@ -630,6 +630,14 @@ constexpr uint64_t kTileNtBytes = uint64_t(160) << 20;
 // besides its entries -- copying an 80 KB panel of x -- in entries, and the
 // fewest entries a tile is cut to.
 constexpr int64_t kTileResident = 512, kTileFixed = 8192, kTileShareMin = 4096;
+// Row blocks that spread over a smaller share of the panels are cut anew
+// (random columns fill their tiles to within a wave unit of each other), to
+// kTileUnevenRounds rounds of resident workgroups (2 | 3 | 5 rounds: 60k rows
+// of 2000 within 6000 float32 146 | 151 | 161 us, float64 207 | 194 | 195); over
+// a still smaller share their columns count as a band, which takes tiles from
+// this many entries a row and in all.
+constexpr double kTileEven = 0.9, kTileBand = 0.75, kTileUnevenRounds = 2.0;
+constexpr int64_t kTileBandRow = 1024, kTileBandMin = int64_t(1) << 24;
 
 // Row blocks for `total` entries over NP panels: the fewest rounds of resident
 // workgroups, counting a round as long as its tiles.  A round too many is what
@@ -816,40 +824,71 @@ spmv_status long_row_lengths(const spmv_plan_s &P, int64_t n7, const int32_t *ro
 // Long rows by tiles (x panels of long_tile_width values per workgroup) over
 // the n7 rows of V.long_rows holding `total` entries.
 // V.long_tiles stays false (nothing built) when the partials would cost over
-// 1/kTileExtraShare of the long rows' own bytes per run, or the panels are too
-// many for the float64 chain.
+// 1/kTileExtraShare of the long rows' own bytes per run, the panels are too
+// many for the float64 chain or, unless the tiles were asked for, *band: the
+// rows' columns lie close together.
+//
+// Rows of a band have their entries in one panel or two.  Row blocks made for
+// all panels then leave most tiles empty and the others long, and the gathers
+// that tiles save come from the caches.  The tiles as they are counted say over
+// how many panels a block spreads (all units over the fullest tiles').  Where
+// that is not nearly all of them the blocks are cut smaller, and short rows or
+// few entries of a band stay in the binned launch.  Measured, float64, binned |
+// tiles cut for all panels | cut for the band: 100k rows of 300 columns within
+// 900 75 | 213 | - us, 20k of 3000 within 9000 146 | 129 | 112, 60k of 2000
+// within 6000 299 | - | 207, 5M entries of Zipf rows within 5000 20 | 47 | 32.
 spmv_status build_long_tiles(const spmv_plan_s &P, Variant &V, int64_t n7, const Dev &lpos,
-                             int64_t total, hipStream_t s) {
+                             int64_t total, bool asked, bool *band, hipStream_t s) {
     const int64_t W = long_tile_width(P.elt);
     const int64_t NP = (P.n + W - 1) / W;
     if (n7 == 0 || NP < 1 || NP > kFp64MaxDepth - 64) return SPMV_OK;
     if (16.0 * (double)NP * n7 * kTileExtraShare > (double)total * (P.elt + 4)) return SPMV_OK;
     const int32_t *rows = V.long_rows.as<int32_t>();
     SMAT_TRY(long_tiles_prepare());
-    const int64_t want = tile_row_blocks(total, NP);
-    const int64_t step = (total + want - 1) / want, nb = (total + step - 1) / step;
-    Dev seg, cnt, scan;
+    Dev seg, cnt, scan, fullest;
     SMAT_TRY(seg.alloc(sizeof(int32_t) * (size_t)(n7 * (NP + 1))));
-    SMAT_TRY(cnt.alloc(sizeof(int32_t) * (size_t)(nb * NP)));
-    SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(nb * NP / 4096 + 2)));
-    SMAT_TRY(V.tile_blocks.alloc(sizeof(TileBlock) * (size_t)nb));
-    SMAT_TRY(V.tile_start.alloc(sizeof(int32_t) * (size_t)(nb * NP + 1)));
+    SMAT_TRY(fullest.alloc(sizeof(int32_t)));
     SMAT_TRY(launch_long_tile_seg(n7, NP, W, rows, P.rp.as<int32_t>(), P.col.as<int32_t>(),
                                   seg.as<int32_t>(), s));
-    SMAT_TRY(launch_tile_blocks(n7, nb, step, lpos.as<int32_t>(), V.tile_blocks.as<TileBlock>(),
-                                s));
-    SMAT_TRY(launch_tile_count(P.elt, n7, nb, NP, V.tile_blocks.as<TileBlock>(),
-                               seg.as<int32_t>(), cnt.as<int32_t>(), s));
-    SMAT_TRY(launch_exclusive_scan_rows(nb * NP, cnt.as<int32_t>(), V.tile_start.as<int32_t>(),
-                                        scan.as<unsigned>(), s));
+    int64_t want = tile_row_blocks(total, NP), nb = 0;
     int32_t units = 0;
-    SMAT_TRY(read_small({{&units, V.tile_start.as<int32_t>() + nb * NP, sizeof(int32_t)}}, s));
+    for (int tries = 0;; ++tries) {
+        const int64_t step = (total + want - 1) / want;
+        nb = (total + step - 1) / step;
+        SMAT_TRY(cnt.alloc(sizeof(int32_t) * (size_t)(nb * NP)));
+        SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(nb * NP / 4096 + 2)));
+        SMAT_TRY(V.tile_blocks.alloc(sizeof(TileBlock) * (size_t)nb));
+        SMAT_TRY(V.tile_start.alloc(sizeof(int32_t) * (size_t)(nb * NP + 1)));
+        SMAT_TRY(launch_tile_blocks(n7, nb, step, lpos.as<int32_t>(),
+                                    V.tile_blocks.as<TileBlock>(), s));
+        SMAT_TRY(launch_tile_count(P.elt, n7, nb, NP, V.tile_blocks.as<TileBlock>(),
+                                   seg.as<int32_t>(), cnt.as<int32_t>(), fullest.as<int32_t>(),
+                                   s));
+        SMAT_TRY(launch_exclusive_scan_rows(nb * NP, cnt.as<int32_t>(),
+                                            V.tile_start.as<int32_t>(), scan.as<unsigned>(), s));
+        int32_t most = 0;
+        SMAT_TRY(read_small({{&units, V.tile_start.as<int32_t>() + nb * NP, sizeof(int32_t)},
+                             {&most, fullest.p, sizeof(int32_t)}}, s));
+        const double spread = (double)units / std::max(1, most);
+        if (spread >= kTileEven * (double)NP) break;
+        *band = spread < kTileBand * (double)NP;
+        if (*band && !asked && total < std::max(kTileBandRow * n7, kTileBandMin)) {
+            V.tile_blocks.release();
+            V.tile_start.release();
+            return SPMV_OK;
+        }
+        want = std::min({(int64_t)(kTileUnevenRounds * kTileResident / spread),
+                         (int64_t)((double)total / (spread * kTileShareMin)),
+                         16 * kTileResident / NP});
+        if (tries == 2 || want <= nb + nb / 8) break;   // cut finely enough
+    }
     const size_t entries = (size_t)units * kWave * (size_t)long_tile_per(P.elt);
     SMAT_TRY(V.tile_part.alloc(sizeof(double) * (size_t)(NP * n7)));
     SMAT_TRY(V.tile_meta.alloc(sizeof(uint32_t) * (size_t)units * kWave));
     SMAT_TRY(V.tile_off.alloc(sizeof(uint16_t) * entries));
     SMAT_TRY(V.tile_val.alloc((size_t)P.elt * entries));
     SMAT_HIP(hipMemsetAsync(V.tile_meta.p, 0, V.tile_meta.bytes, s));
+    SMAT_HIP(hipMemsetAsync(V.tile_part.p, 0, V.tile_part.bytes, s));
     int lg = 0;   // lanes per segment of the packing pass
     while (lg < 6 && (double)(2 << lg) * (double)NP * (double)n7 < (double)total) ++lg;
     SMAT_TRY(launch_tile_fill(P.elt, n7, nb, NP, lg, rows, P.rp.as<int32_t>(),
@@ -1246,7 +1285,8 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
                 SMAT_TRY(V.long_rows.alloc(sizeof(int32_t) * (size_t)n7));
                 SMAT_HIP(hipMemcpyAsync(V.long_rows.p, r7, sizeof(int32_t) * n7,
                                         hipMemcpyDeviceToDevice, s));
-                SMAT_TRY(build_long_tiles(P, V, n7, lpos, total7, s));
+                bool band = false;
+                SMAT_TRY(build_long_tiles(P, V, n7, lpos, total7, prm.long_lds == 3, &band, s));
                 if (!V.long_tiles && prm_in.tile_row_min == 0 && wg < kTileRowMinMax &&
                     wg < prm.adaptive_wg_min) {
                     // rows too short for so many panels: only longer ones
@@ -1256,7 +1296,7 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
                     ll = prm.long_lds;
                     continue;
                 }
-                if (!V.long_tiles) ll = chunks_ok ? 1 : 2;
+                if (!V.long_tiles) ll = chunks_ok && !band ? 1 : 2;
             }
             if (ll == 1) {
                 // the long rows longest first, so that the rows of one

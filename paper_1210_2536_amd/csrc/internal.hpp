@@ -214,11 +214,13 @@ spmv_status launch_long_tile_seg(int64_t n7, int64_t P, int64_t W, const int32_t
                                  const int32_t *rp, const int32_t *col, int32_t *seg,
                                  hipStream_t s);
 // Row blocks of `step` entries (lpos: the rows' lengths scanned), the wave
-// units per tile, the packed entries (2^lg lanes share a segment).
+// units per tile (0 where no row has an entry) and the sum over the blocks of
+// their fullest tile's, the packed entries (2^lg lanes share a segment).
 spmv_status launch_tile_blocks(int64_t n7, int64_t nb, int64_t step, const int32_t *lpos,
                                TileBlock *blocks, hipStream_t s);
 spmv_status launch_tile_count(int elt, int64_t n7, int64_t nb, int64_t P, const TileBlock *blocks,
-                              const int32_t *seg, int32_t *cnt, hipStream_t s);
+                              const int32_t *seg, int32_t *cnt, int32_t *fullest,
+                              hipStream_t s);
 spmv_status launch_tile_fill(int elt, int64_t n7, int64_t nb, int64_t P, int lg,
                              const int32_t *rows, const int32_t *rp, const int32_t *col,
                              const void *val, const int32_t *seg, const TileBlock *blocks,

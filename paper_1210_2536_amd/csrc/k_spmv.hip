@@ -576,7 +576,8 @@ __global__ __launch_bounds__(256) void k_tile_blocks(int64_t n7, int64_t nb, int
     blocks[b] = TileBlock{(int32_t)r[0], (int32_t)(r[1] - r[0])};
 }
 
-// Wave units of tile (b, p), one wave per tile.
+// Wave units of tile (b, p), one wave per tile; none where no row of the block
+// has an entry in the panel (those partials stay zero).
 template <int UNIT>
 __global__ __launch_bounds__(256) void k_tile_count(int64_t n7, int64_t nb, int64_t P,
                                                     const TileBlock *__restrict__ blocks,
@@ -588,9 +589,34 @@ __global__ __launch_bounds__(256) void k_tile_count(int64_t n7, int64_t nb, int6
     const int64_t b = w / P, p = w - b * P;
     const int32_t *s0 = seg + p * n7 + blocks[b].row0, *s1 = s0 + n7;
     int64_t sum = 0;
-    for (int i = lane; i < blocks[b].rows; i += kWave) sum += max(1, s1[i] - s0[i]);
+    bool any = false;
+    for (int i = lane; i < blocks[b].rows; i += kWave) {
+        sum += max(1, s1[i] - s0[i]);
+        any = any || s1[i] > s0[i];
+    }
     for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (!__ballot(any)) sum = 0;
     if (lane == 0) cnt[w] = (int32_t)((sum + UNIT - 1) / UNIT);
+}
+
+// The units of every row block's fullest tile, added up into *fullest.
+__global__ __launch_bounds__(1024) void k_tile_fullest(int64_t nb, int64_t P,
+                                                       const int32_t *__restrict__ cnt,
+                                                       int32_t *__restrict__ fullest) {
+    __shared__ int sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    int part = 0;
+    for (int64_t b = threadIdx.x / kWave; b < nb; b += 1024 / kWave) {
+        int most = 0;
+        for (int64_t p = lane; p < P; p += kWave) most = max(most, cnt[b * P + p]);
+        for (int o = kWave / 2; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+        part += most;
+    }
+    if (lane == 0) atomicAdd(&sum, part);
+    __syncthreads();
+    if (threadIdx.x == 0) *fullest = sum;
 }
 
 // The entries of tile (b, p) in the kernel's order; row starts into the low
@@ -608,6 +634,7 @@ __global__ __launch_bounds__(1024) void k_tile_fill(
     const int t = threadIdx.x;
     const int64_t p = (int64_t)blockIdx.x % P, b = (int64_t)blockIdx.x / P;
     const int64_t u0 = start[blockIdx.x], u1 = start[blockIdx.x + 1];
+    if (u0 == u1) return;   // the whole workgroup: nothing in this tile
     const TileBlock blk = blocks[b];
     const int32_t *s0 = seg + p * n7 + blk.row0, *s1 = s0 + n7;
     const int lanes = 1 << lg, lane = t & (lanes - 1);
@@ -1200,13 +1227,16 @@ spmv_status launch_tile_blocks(int64_t n7, int64_t nb, int64_t step, const int32
 }
 
 spmv_status launch_tile_count(int elt, int64_t n7, int64_t nb, int64_t P, const TileBlock *blocks,
-                              const int32_t *seg, int32_t *cnt, hipStream_t s) {
+                              const int32_t *seg, int32_t *cnt, int32_t *fullest,
+                              hipStream_t s) {
     const unsigned g = (unsigned)((nb * P + 3) / 4);
     if (elt == 8)
         k_tile_count<kWave * TileShape<double>::PER><<<g, 256, 0, s>>>(n7, nb, P, blocks, seg, cnt);
     else
         k_tile_count<kWave * TileShape<float>::PER><<<g, 256, 0, s>>>(n7, nb, P, blocks, seg, cnt);
     SMAT_LAUNCHED("tile_count");
+    k_tile_fullest<<<1, 1024, 0, s>>>(nb, P, cnt, fullest);
+    SMAT_LAUNCHED("tile_fullest");
     return SPMV_OK;
 }
 

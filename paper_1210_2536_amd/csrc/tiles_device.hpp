@@ -112,7 +112,7 @@ __device__ __forceinline__ void tile_block(const TileArgs<T> &a, unsigned bid,
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const unsigned P = (unsigned)a.P, b = bid / P, p = bid - b * P;
     const int u0 = uniform(a.start[bid]), u1 = uniform(a.start[bid + 1]);
-    if (u0 == u1) return;   // no rows (one row filled the blocks before)
+    if (u0 == u1) return;   // no entries: the partials are zero since the plan was made
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     // the thread's entries of a pass, all requested before any is used
