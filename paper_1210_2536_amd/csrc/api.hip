@@ -934,6 +934,10 @@ constexpr uint64_t kExpandNt1Bytes = uint64_t(192) << 20;
 // filled only up to the last row that still fits: at most half is lost at
 // kTileRowMinMax, a sixteenth to an eighth here).
 constexpr int kExpandRowMax = 1024;
+// Without tiles each of the longer rows is summed by one workgroup of a third
+// launch.  Rows above this go to the tiles, which the two launches hold anyway,
+// whatever their number, or the XCD panels are built.
+constexpr int kAloneMax = 8192;
 
 // They hold up to 3 s + 4 bytes an entry where the XCD panels hold s + 4 and,
 // per row, eight row pointers and partials: where the plan's storage cap lies
@@ -1212,7 +1216,7 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
         int wg = try_tiles ? std::min(prm.adaptive_wg_min, prm.tile_row_min) : prm.adaptive_wg_min;
         // panels in two steps: row blocks, cut between rows, take rows of a
         // limited length; the longest bin starts there
-        const bool expand = panels && expand_fits(P, prm);
+        bool expand = panels && expand_fits(P, prm);
         int wg_plain = prm.adaptive_wg_min;   // without tiles
         if (expand) {
             wg_plain = std::min(wg_plain, kExpandRowMax);
@@ -1275,7 +1279,7 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
             if (n7 > 0 && (ll == 0 || ll == 3))
                 SMAT_TRY(long_row_lengths(P, n7, r7, lpos, &total7, s));
             if (ll == 0)
-                ll = total7 * elt >= kTileBytesDefault ? 3 : 2;
+                ll = total7 * elt >= kTileBytesDefault || (expand && F.max_rd > kAloneMax) ? 3 : 2;
             int tpr = n7 >= 8192 ? 32 : 64;
             if ((F.max_rd + tpr - 1) / tpr + ilog2(tpr) > kFp64MaxDepth) tpr = 64;
             const bool chunks_ok = P.dtype == SPMV_F64 &&
@@ -1331,6 +1335,13 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
                 // no tiles: bins with the binned launch's own threshold
                 V.long_rows.release();
                 wg = wg_plain;
+                SMAT_TRY(bin(wg));
+                continue;
+            }
+            if (ll == 2 && expand && F.max_rd > kAloneMax && (int64_t)V.P * (m + 1) < (1ll << 31)) {
+                // the XCD panels cut such a row by panels
+                expand = false;
+                wg = wg_plain = prm.adaptive_wg_min;
                 SMAT_TRY(bin(wg));
                 continue;
             }
