@@ -95,8 +95,21 @@ __device__ __forceinline__ void vector_tile(const LevelDesc &d, int64_t tile, co
 }
 
 // Row groups of a csr_vector tile with 8 lanes a row or more, where the level
-// still has four such tiles for each compute unit (spmv_batch_create); else one.
+// still has four such tiles for each compute unit (two_row_groups); else one.
 constexpr int kPVectorRows = 2;
+
+// Two groups for float32 levels that are small or stream from HBM.  Measured, 27
+// entries a row, one group | two, float32: 48^3 rows (24 MB) and its coarse
+// levels 12.3 | 10.5 us, 64^3 (56 MB) 26.4 | 23.3, 80^3 (110 MB) 37.8 | 40.7, 96^3
+// (191 MB) 61 | 66, 112^3 (303 MB) 124 | 116, 128^3 187 | 178; float64 48^3 15.4 |
+// 17.4, 64^3 28.2 | 32.2, 80^3 47.8 | 54.3, 160^3's coarse levels 202 | 208.
+constexpr uint64_t kTwoGroupsMost = uint64_t(64) << 20, kTwoGroupsFrom = uint64_t(256) << 20;
+
+bool two_row_groups(const spmv_plan_s &P, int lanes) {
+    const uint64_t bytes = (uint64_t)P.nnz * (P.elt + 4);
+    return P.elt == 4 && lanes >= 8 && (bytes <= kTwoGroupsMost || bytes > kTwoGroupsFrom) &&
+           P.m / (kPVectorRows * (kPBlock / lanes)) >= 4 * kCus;
+}
 
 // Level-kind sets the persistent kernel is compiled for (bit k: LevelKind
 // k).  A launch takes the smallest set that holds the kinds of its levels:
@@ -138,8 +151,8 @@ __device__ __forceinline__ void batch_item(const LevelDesc &d, int64_t tile, con
         switch (d.lanes) {
 #define SMAT_VECTOR_TILE(L)                                             \
     case L:                                                              \
-        if (d.K == kPVectorRows)                                         \
-            vector_tile<T, L, NT, kPVectorRows>(d, tile, x, y);          \
+        if (sizeof(T) == 4 && d.K == kPVectorRows)                       \
+            vector_tile<T, L, NT, sizeof(T) == 4 ? kPVectorRows : 1>(d, tile, x, y); \
         else                                                             \
             vector_tile<T, L, NT, 1>(d, tile, x, y);                     \
         break
@@ -440,8 +453,7 @@ extern "C" spmv_status spmv_batch_create(const spmv_plan_t *plans, int32_t nplan
         case SPMV_K_CSR_VECTOR:
             d.kind = LK_VECTOR;
             d.lanes = V.prm.vector_lanes;
-            d.K = d.lanes >= 8 && P.m / (kPVectorRows * (kPBlock / d.lanes)) >= 4 * kCus
-                      ? kPVectorRows : 1;
+            d.K = two_row_groups(P, d.lanes) ? kPVectorRows : 1;
             d.tile_rows = d.K * (kPBlock / d.lanes);
             break;
         case SPMV_K_CSR_ADAPTIVE:
