@@ -938,6 +938,15 @@ constexpr int kExpandRowMax = 1024;
 // launch.  Rows above this go to the tiles, which the two launches hold anyway,
 // whatever their number, or the XCD panels are built.
 constexpr int kAloneMax = 8192;
+// Row blocks whose columns lie in panels of at most this many columns together
+// (a band, and enough blocks to matter) are left to the XCD panels: what the two
+// steps save, gathers that miss the caches, is not there, and they move 28 bytes
+// an entry where those move 12 (float64).  Measured, XCD panels | two steps:
+// columns within 2000 of 600k, 60 a row, float32 149 | 125 us, float64 191 | 249;
+// within 3000 of 100k, 600 a row, 131 | 185 and 168 | 374; within 300 of 1M, 12
+// a row, 49.5 | 55 and 72 | 96; above the line, within 50000 of 1M, 74 | 49 and 98
+// | 74.
+constexpr int64_t kExpandBandColumns = 40960;
 
 // They hold up to 3 s + 4 bytes an entry where the XCD panels hold s + 4 and,
 // per row, eight row pointers and partials: where the plan's storage cap lies
@@ -966,15 +975,15 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     const int NP = (int)expand_panels(P.n, elt);
     const int32_t *rp = P.rp.as<int32_t>(), *col = P.col.as<int32_t>();
     SMAT_TRY(expand_prepare());
-    Dev len, scan, spos, most;
+    Dev len, scan, spos, stats;
     SMAT_TRY(len.alloc(sizeof(int32_t) * (size_t)m));
     SMAT_TRY(scan.alloc(sizeof(unsigned) * (size_t)(m / 4096 + 2)));
     SMAT_TRY(spos.alloc(sizeof(int32_t) * (size_t)(m + 1)));
-    SMAT_TRY(most.alloc(sizeof(int)));
+    SMAT_TRY(stats.alloc(2 * sizeof(int)));
     SMAT_TRY(launch_expand_lengths(m, rp, lmax, len.as<int32_t>(), s));
     SMAT_TRY(launch_exclusive_scan_rows(m, len.as<int32_t>(), spos.as<int32_t>(),
                                         scan.as<unsigned>(), s));
-    SMAT_HIP(hipMemsetAsync(most.p, 0, sizeof(int), s));
+    SMAT_HIP(hipMemsetAsync(stats.p, 0, 2 * sizeof(int), s));
     int32_t total = 0;
     SMAT_TRY(read_small({{&total, spos.as<int32_t>() + m, sizeof(int32_t)}}, s));
     // a block takes the rows that start within `step` entries, so that the
@@ -990,15 +999,23 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     SMAT_TRY(scan2.alloc(sizeof(unsigned) * (size_t)(NP * nb / 4096 + 2)));
     SMAT_TRY(launch_expand_count(elt, m, nb, step, NP, lmax, lg, rp, col, spos.as<int32_t>(),
                                  V.ex_blocks.as<ExpandBlock>(), cnt.as<int32_t>(),
-                                 most.as<int>(), s));
+                                 stats.as<int>(), s));
     SMAT_TRY(launch_exclusive_scan_rows(NP * nb, cnt.as<int32_t>(), runs.as<int32_t>(),
                                         scan2.as<unsigned>(), s));
     SMAT_TRY(V.ex_starts.alloc(sizeof(int32_t) * (size_t)(NP + 1)));
     SMAT_TRY(launch_expand_starts(NP, nb, runs.as<int32_t>(), V.ex_starts.as<int32_t>(), s));
     std::vector<int32_t> start(NP + 1);
-    int stride = 0;
+    int counted[2] = {0, 0};   // most pieces of a block, runs that hold any
     SMAT_TRY(read_small({{start.data(), V.ex_starts.p, sizeof(int32_t) * (NP + 1)},
-                         {&stride, most.p, sizeof(int)}}, s));
+                         {counted, stats.p, sizeof(counted)}}, s));
+    const int stride = counted[0];
+    // a band: the blocks' entries lie in a few panels
+    if (nb >= kExpandResident / 2 && (int64_t)counted[1] * 4 <= NP * nb * 3 &&
+        (int64_t)counted[1] * expand_width(elt) <= nb * kExpandBandColumns &&
+        (int64_t)V.P * (m + 1) < (1ll << 31)) {
+        V.ex_band = true;
+        return SPMV_OK;
+    }
     if (stride > expand_max_pieces()) {
         set_error("expanded panels: %d pieces in a row block", stride);
         return SPMV_EUNSUPPORTED;
@@ -1038,8 +1055,7 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     V.expand = true;
     V.ex_P = NP;
     V.ex_stride = stride;
-    // lanes that copy a run of one panel's pieces into LDS: the mean run
-    while (V.ex_lr < 6 && ((int64_t)NP * nb << V.ex_lr) <= pieces) ++V.ex_lr;
+    V.ex_lr = expand_run_lanes(NP, nb, pieces, counted[1]);
     V.ex_lmax = lmax;
     V.ex_nb = nb;
     V.ex_nchunks = (int64_t)chunks.size();
@@ -1407,6 +1423,7 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
                 V.along = bins_launch(V.bin_off, 7, 7, 0);
                 V.prm.panel_xcd = 0;
                 SMAT_TRY(build_expand(P, F, V, spec.upper[6], s));
+                if (V.ex_band) return SPMV_OK;
                 // streams that leave no room in the 256 MB Infinity Cache for
                 // xe between the two steps are read past it
                 if (prm_in.stream_nt == 0)
@@ -1446,13 +1463,15 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
 }
 
 // The chosen kernel's arrays.  Column panels in two steps take more memory
-// than the XCD panels: where it is not there, those are built instead.
+// than the XCD panels: where it is not there, and for a band of columns, those
+// are built instead.
 spmv_status build_variant(spmv_plan_s &P, const spmv_features &F, FeatureWork &W, int kernel,
                           const spmv_params &prm_in, hipStream_t s, Variant &V) {
     const spmv_status st = build_kernel(P, F, W, kernel, prm_in, s, V);
-    if (st != SPMV_ENOMEM || kernel != SPMV_K_CSR_PANEL || prm_in.panel_xcd != 0 ||
-        !expand_fits(P, resolve_params(kernel, prm_in, F, P.elt)))
-        return st;
+    const bool no_memory = st == SPMV_ENOMEM && kernel == SPMV_K_CSR_PANEL &&
+                           prm_in.panel_xcd == 0 &&
+                           expand_fits(P, resolve_params(kernel, prm_in, F, P.elt));
+    if (!no_memory && !(st == SPMV_OK && V.ex_band)) return st;
     SMAT_HIP(hipStreamSynchronize(s));
     V.~Variant();
     new (&V) Variant();

@@ -278,6 +278,7 @@ int64_t expand_width(int elt);            // columns per panel
 int expand_per(int elt);                  // entries per thread of a row block
 int64_t expand_block_entries(int elt);    // entries per row block, at most
 int expand_max_pieces();                  // pieces per row block, at most
+int expand_run_lanes(int P, int64_t nb, int64_t pieces, int64_t runs);
 constexpr int kExpandMaxPanels = 4096;    // panel counters of the plan-time kernels in LDS
 spmv_status expand_prepare();             // LDS limits (before the first launch)
 // Plan time: entries per row (an empty row and a row longer than lmax, which
@@ -289,7 +290,7 @@ spmv_status launch_expand_lengths(int64_t m, const int32_t *rp, int32_t lmax, in
                                   hipStream_t s);
 spmv_status launch_expand_count(int elt, int64_t m, int64_t nb, int64_t step, int P, int32_t lmax,
                                 int lg, const int32_t *rp, const int32_t *col,
-                                const int32_t *spos, ExpandBlock *blocks, int32_t *cnt, int *most,
+                                const int32_t *spos, ExpandBlock *blocks, int32_t *cnt, int *stats,
                                 hipStream_t s);
 spmv_status launch_expand_starts(int P, int64_t nb, const int32_t *runs, int32_t *starts,
                                  hipStream_t s);

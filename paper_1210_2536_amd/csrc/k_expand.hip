@@ -51,6 +51,7 @@ namespace {
 constexpr int kExpandThreads = kTileThreads;
 constexpr int kExpandBytes = kTileBytes;   // x per panel: two workgroups fill a CU's LDS
 constexpr int kRowsThreads = 1024;
+constexpr int kRunsAhead = 4;         // runs of xe that a lane requests together
 constexpr int kRowsPieces = 5100;     // 16-byte pieces of xe per row block, at most
 // Behind a block's pieces lies one of zeros: its first value is the slot of an
 // entry that adds zero, its second that of the entry standing for a row which
@@ -201,10 +202,11 @@ __global__ __launch_bounds__(kRowsThreads, 8) void k_panel_rows(
             vv[q] = ld<NT>(reinterpret_cast<const vec *>(
                 val + expand_at<PER, G>(b, t * PER + q * G)));
     }
-    // the block's run of each panel by 1 << lr lanes, four runs of a lane at once
+    // the block's run of each panel by 1 << lr lanes, kRunsAhead runs of a lane at
+    // once
     const vec *xp = reinterpret_cast<const vec *>(xe);
     const int2 *run = runs + b * P;
-    constexpr int A = 4;
+    constexpr int A = kRunsAhead;
     const int lanes = 1 << lr, groups = kRowsThreads >> lr;
     for (int p0 = t >> lr; p0 < P; p0 += A * groups) {
         int32_t from[A], to[A], left[A], most = 0;
@@ -321,20 +323,20 @@ __device__ __forceinline__ int64_t expand_lower_row(const int32_t *__restrict__ 
 
 // Row block b: the rows whose entries start in [b step, (b + 1) step).  Its
 // pieces per panel into cnt[p * nb + b], their sum into blocks[b], the largest
-// sum into *most.
+// sum into stats[0], the panels that hold any, over all blocks, into stats[1].
 template <int W, int G>
 __global__ __launch_bounds__(1024) void k_expand_count(
     int64_t m, int64_t nb, int64_t step, int P, int32_t lmax, int lg,
     const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
     const int32_t *__restrict__ spos, ExpandBlock *__restrict__ blocks,
-    int32_t *__restrict__ cnt, int *__restrict__ most) {
+    int32_t *__restrict__ cnt, int *__restrict__ stats) {
     extern __shared__ int hist[];
     __shared__ int64_t rows[2];
-    __shared__ int total;
+    __shared__ int total, filled;
     const int64_t b = blockIdx.x;
     for (int p = threadIdx.x; p < P; p += 1024) hist[p] = 0;
     if (threadIdx.x < 2) rows[threadIdx.x] = expand_lower_row(spos, m, (b + threadIdx.x) * step);
-    if (threadIdx.x == 0) total = 0;
+    if (threadIdx.x == 0) total = filled = 0;
     __syncthreads();
     const int64_t r0 = rows[0], r1 = rows[1];
     const int lanes = 1 << lg, lane = threadIdx.x & (lanes - 1);
@@ -344,17 +346,22 @@ __global__ __launch_bounds__(1024) void k_expand_count(
         for (int32_t e = e0 + lane; e < e1; e += lanes) atomicAdd(&hist[col[e] / W], 1);
     }
     __syncthreads();
-    int sum = 0;
+    int sum = 0, any = 0;
     for (int p = threadIdx.x; p < P; p += 1024) {
         const int c = (hist[p] + G - 1) / G;
         cnt[(int64_t)p * nb + b] = c;
         sum += c;
+        any += c > 0;
     }
-    if (sum) atomicAdd(&total, sum);
+    if (sum) {
+        atomicAdd(&total, sum);
+        atomicAdd(&filled, any);
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         blocks[b] = ExpandBlock{(int32_t)r0, (int32_t)(r1 - r0), spos[r1] - spos[r0], total};
-        atomicMax(most, total);
+        atomicMax(&stats[0], total);
+        atomicAdd(&stats[1], filled);
     }
 }
 
@@ -499,6 +506,34 @@ int expand_per(int elt) { return 64 / elt; }
 int64_t expand_block_entries(int elt) { return (int64_t)kRowsThreads * expand_per(elt); }
 int expand_max_pieces() { return kRowsPieces; }
 
+// Lanes (a power of two, its logarithm) that copy a run of one panel's pieces,
+// from the pieces, the runs that hold any and the blocks.  Steps of one
+// workgroup, each of which waits for memory: its P runs by groups of lanes, and
+// as many more as the runs of such a step are longer than the lanes.  Spread
+// columns (all runs alike) keep the mean run's lanes, at most a wave; where a
+// block's entries lie in a few panels their runs take up to the whole
+// workgroup.  By 64 lanes a run | this: 12 columns a row within 50000 of 1M
+// float32 58 | 49 us, float64 77 | 74; 280 within 20000 of 150k 187 | 124 and
+// 379 | 265.
+int expand_run_lanes(int P, int64_t nb, int64_t pieces, int64_t runs) {
+    int lr = 0;
+    while (lr < 6 && ((int64_t)P * nb << lr) <= pieces) ++lr;
+    if (runs * 4 > (int64_t)P * nb * 3) return lr;
+    const double run = (double)pieces / (double)std::max<int64_t>(1, runs);
+    const double filled = (double)runs / (double)nb;
+    double best = 1e300;
+    for (int l = 0; (1 << l) <= kRowsThreads; ++l) {
+        const double at_once = (double)kRunsAhead * (kRowsThreads >> l);
+        const double steps = std::ceil(P / at_once) + (std::ceil(run / (1 << l)) - 1.0) *
+                                                          std::ceil(filled / at_once);
+        if (steps < best) {
+            best = steps;
+            lr = l;
+        }
+    }
+    return lr;
+}
+
 spmv_status expand_prepare() {
 #define ATTR(F, BYTES)                                                                      \
     SMAT_HIP(hipFuncSetAttribute((const void *)(F), hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -525,15 +560,15 @@ spmv_status launch_expand_lengths(int64_t m, const int32_t *rp, int32_t lmax, in
 
 spmv_status launch_expand_count(int elt, int64_t m, int64_t nb, int64_t step, int P, int32_t lmax,
                                 int lg, const int32_t *rp, const int32_t *col,
-                                const int32_t *spos, ExpandBlock *blocks, int32_t *cnt, int *most,
+                                const int32_t *spos, ExpandBlock *blocks, int32_t *cnt, int *stats,
                                 hipStream_t s) {
     const size_t sh = sizeof(int) * (size_t)P;
     if (elt == 8)
         k_expand_count<kExpandBytes / 8, 2><<<(unsigned)nb, 1024, sh, s>>>(
-            m, nb, step, P, lmax, lg, rp, col, spos, blocks, cnt, most);
+            m, nb, step, P, lmax, lg, rp, col, spos, blocks, cnt, stats);
     else
         k_expand_count<kExpandBytes / 4, 4><<<(unsigned)nb, 1024, sh, s>>>(
-            m, nb, step, P, lmax, lg, rp, col, spos, blocks, cnt, most);
+            m, nb, step, P, lmax, lg, rp, col, spos, blocks, cnt, stats);
     SMAT_LAUNCHED("expand_count");
     return SPMV_OK;
 }

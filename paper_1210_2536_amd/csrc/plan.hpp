@@ -127,8 +127,9 @@ struct Variant {
     bool long_tiles = false, tile_nt = false;
     int64_t tile_P = 0, tile_nb = 0;
     Dev tile_blocks, tile_start, tile_meta, tile_part, tile_off, tile_val;
-    // column panels in two steps: rows of at most ex_lmax entries
-    bool expand = false;
+    // column panels in two steps: rows of at most ex_lmax entries; ex_band:
+    // not built, a band of columns
+    bool expand = false, ex_band = false;
     int ex_P = 0, ex_stride = 0, ex_lr = 0;
     int32_t ex_lmax = 0;
     int64_t ex_nb = 0, ex_nchunks = 0;
