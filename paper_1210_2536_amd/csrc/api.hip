@@ -508,14 +508,17 @@ spmv_params resolve_params(int kernel, spmv_params p, const spmv_features &F, in
     if (p.bcsr_lanes == 0) {
         const int64_t mb = std::max<int64_t>(1, (F.m + 3) / 4);
         const int64_t avg = (std::max<int64_t>(0, F.blocks4) + mb - 1) / mb;
-        // 16 bytes of a block a lane, 2 lanes per block of a mean block row
-        // (rounded down to a power of two): each lane then has 4 (float64) or
-        // 2 blocks to request together, and short rows leave few lanes idle.
-        // Measured, 400k rows of 16 blocks with 8 | 16 | 32 | 64 lanes: float64
-        // 47.2 | 46.1 | 44.7 | 46.3 us, float32 28.8 | 27.5 | 27.1 | 33.7; of 4
-        // blocks: 14.5 | 14.9 | 19.0 | 28.8 and 9.7 | 11.5 | 16.2 | 28.2.
+        // 16 bytes of a block a lane.  float64: 2 lanes per block of a mean
+        // block row (rounded down to a power of two), so that each lane has 4
+        // blocks to request together and short rows leave few lanes idle;
+        // float32: one lane per block, also rounded down.  Measured with 8 | 16 |
+        // 32 | 64 lanes, 400k rows of 16 blocks: float64 47.2 | 46.1 | 44.7 | 46.3
+        // us, float32 28.8 | 27.5 | 27.1 | 33.7; 27-point 128^3 (18 blocks): float64
+        // 322 | 315 | 306 | 448, float32 172 | 161 | 229 | 252; 7-point 128^3 with 4 |
+        // 8 lanes: float32 45 | 52.
         int L = elt;
-        while (L < 64 && L <= avg) L *= 2;
+        const int64_t most = elt == 8 ? avg : avg / 2;
+        while (L < 64 && L <= most) L *= 2;
         p.bcsr_lanes = L;
     }
     return p;
@@ -1565,8 +1568,8 @@ spmv_status run_variant(const spmv_plan_s &P, const Variant &V, const void *x, v
         return SPMV_OK;
     }
     case SPMV_K_BCSR:
-        return run_bcsr(elt, nt, m, P.n, V.brp.as<int32_t>(), V.bcol.as<int32_t>(), V.bval.p, x,
-                        y, V.prm.bcsr_lanes, std::min(V.prm.block, 256), s);
+        return run_bcsr(elt, nt, m, P.n, V.nblocks, V.brp.as<int32_t>(), V.bcol.as<int32_t>(),
+                        V.bval.p, x, y, V.prm.bcsr_lanes, std::min(V.prm.block, 256), s);
     case SPMV_K_ELL:
         return run_ell(elt, nt, m, P.m_pad, V.K, V.ecol.as<int32_t>(), V.eval.p, x, y,
                        V.prm.block, V.prm.ell_unroll, V.prm.wide_loads == 1, s);
@@ -1727,10 +1730,11 @@ std::vector<spmv_params> tune_grid(int kernel, const spmv_params &b, const spmv_
                     }
         break;
     case SPMV_K_BCSR:
-        for (int f : {1, 2, 4, 8})  // blocks of a row side by side
+        for (int f : {1, 2, 4, 8, 16})  // blocks of a row side by side
             for (int nt : nts) {
                 spmv_params p = b;
                 p.bcsr_lanes = (dtype == SPMV_F64 ? 8 : 4) * f;
+                if (p.bcsr_lanes > 64) continue;
                 p.stream_nt = nt;
                 add(p);
             }

@@ -124,8 +124,8 @@ spmv_status launch_bcsr_to_csr(int64_t m, const int32_t *brp, const int32_t *bco
                                const void *bval, const uint16_t *pres, int elt, int32_t *rp,
                                int32_t *col, void *val, int32_t *counts, unsigned int *scratch,
                                hipStream_t s);
-// BCSR SpMV: `lanes` lanes per block row (power of two <= 64).
-spmv_status run_bcsr(int elt, bool nt, int64_t m, int64_t n, const int32_t *brp,
+// BCSR SpMV over nblocks blocks: `lanes` lanes per block row (power of two <= 64).
+spmv_status run_bcsr(int elt, bool nt, int64_t m, int64_t n, int64_t nblocks, const int32_t *brp,
                      const int32_t *bcol, const void *bval, const void *x, void *y, int lanes,
                      int block, hipStream_t s);
 // scratch: at least ceil(m / 4096) unsigned ints

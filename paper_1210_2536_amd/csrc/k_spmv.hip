@@ -714,14 +714,17 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_ranks(const int32_t *__re
 // Measured, blocks from HBM (before | now, MI355X): 400k rows of 16 blocks
 // float64 54.4 | 44.7 us (4.9 TB/s), float32 29.0 | 27.1; 100k rows 15.4 | 12.6
 // and 9.5 | 8.9; 400k rows of 4 blocks 16.0 | 14.5 and 10.2 | 9.7.
-template <typename T, int L, bool NT>
+// A blocks in flight; one matrix from the Infinity Cache, float64, 8 lanes, A = 1
+// | 4 | default lanes, A = 4: 200k rows of 16 blocks 18.8 | 20.5 | 19.9 us, of 32
+// blocks 34.0 | 38.7 | 35.7, 400k rows of 16 40.1 | 44.7 | 44.8.
+template <typename T, int L, bool NT, int A>
 __global__ __launch_bounds__(256) void k_bcsr(int64_t mb, int64_t m, int64_t n,
                                               const int32_t *__restrict__ brp,
                                               const int32_t *__restrict__ bcol,
                                               const T *__restrict__ bval,
                                               const T *__restrict__ x, T *__restrict__ y) {
     const int64_t R = (int64_t)blockIdx.x * (blockDim.x / L) + threadIdx.x / L;
-    bcsr_row<T, L, NT, 4>(R, threadIdx.x & (L - 1), mb, m, n, brp, bcol, bval, x, y);
+    bcsr_row<T, L, NT, A>(R, threadIdx.x & (L - 1), mb, m, n, brp, bcol, bval, x, y);
 }
 
 // ---------------------------------------------------------------- COO
@@ -1045,8 +1048,9 @@ spmv_status panel_dispatch(const AdaptiveLaunch &a, const int32_t *rows, int P, 
 }
 
 template <typename T, bool NT>
-spmv_status bcsr_dispatch(int64_t m, int64_t n, const int32_t *brp, const int32_t *bcol,
-                          const T *bval, const T *x, T *y, int lanes, int block, hipStream_t s) {
+spmv_status bcsr_dispatch(int64_t m, int64_t n, int64_t nblocks, const int32_t *brp,
+                          const int32_t *bcol, const T *bval, const T *x, T *y, int lanes,
+                          int block, hipStream_t s) {
     const int64_t mb = (m + 3) / 4;
     if (mb == 0) return SPMV_OK;
     if (block <= 0 || block > 256) block = 256;
@@ -1056,10 +1060,19 @@ spmv_status bcsr_dispatch(int64_t m, int64_t n, const int32_t *brp, const int32_
     }
     lanes = std::max(lanes, bcsr_block_lanes(sizeof(T)));
     const unsigned g = grid_for(mb, block / lanes);
+    if constexpr (sizeof(T) == 8) {
+        // one block of a long row at a time (never the default's lanes): best
+        // where one matrix is run from the Infinity Cache again and again
+        if (lanes == 8 && nblocks >= 8 * mb) {
+            k_bcsr<T, 8, NT, 1><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y);
+            SMAT_LAUNCHED("bcsr");
+            return SPMV_OK;
+        }
+    }
 #define L_CASE(L)                                                                            \
     case L:                                                                                  \
         if constexpr (L >= bcsr_block_lanes(sizeof(T)))                                      \
-            k_bcsr<T, L, NT><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y);           \
+            k_bcsr<T, L, NT, 4><<<g, block, 0, s>>>(mb, m, n, brp, bcol, bval, x, y);        \
         break;
     switch (lanes) { L_CASE(4) L_CASE(8) L_CASE(16) L_CASE(32) L_CASE(64) }
 #undef L_CASE
@@ -1069,11 +1082,12 @@ spmv_status bcsr_dispatch(int64_t m, int64_t n, const int32_t *brp, const int32_
 
 }  // namespace
 
-spmv_status run_bcsr(int elt, bool nt, int64_t m, int64_t n, const int32_t *brp,
+spmv_status run_bcsr(int elt, bool nt, int64_t m, int64_t n, int64_t nblocks, const int32_t *brp,
                      const int32_t *bcol, const void *bval, const void *x, void *y, int lanes,
                      int block, hipStream_t s) {
 #define CALL(T, NT)                                                                         \
-    bcsr_dispatch<T, NT>(m, n, brp, bcol, (const T *)bval, (const T *)x, (T *)y, lanes, block, s)
+    bcsr_dispatch<T, NT>(m, n, nblocks, brp, bcol, (const T *)bval, (const T *)x,   \
+                         (T *)y, lanes, block, s)
     return elt == 8 ? (nt ? CALL(double, true) : CALL(double, false))
                     : (nt ? CALL(float, true) : CALL(float, false));
 #undef CALL
