@@ -671,7 +671,8 @@ __global__ __launch_bounds__(1024) void k_tile_fill(
                 mark(k);
                 if (e0 == e1) put(k, kTileEmpty<U>, U(0));
             }
-            for (int32_t e = e0 + lane; e < e1; e += lanes)
+            // 64 bits: the step past the last entry leaves int32 near 2^31
+            for (int64_t e = (int64_t)e0 + lane; e < e1; e += lanes)
                 put(k + (e - e0), (uint16_t)(col[e] - p * W), val[e]);
         }
         base += total;

@@ -20,30 +20,33 @@ def _give_memory_back():
     torch.cuda.empty_cache()
 
 
-def _matrix(short):
-    """Rows of LONG entries (columns 0 .. LONG - 1) and, last, one row for each
-    length in `short`; every value 1."""
+def _matrix(short, short_last=True):
+    """Rows of LONG entries (columns 0 .. LONG - 1) and, last or first, one row
+    for each length in `short`; every value 1."""
     long_rows = ROWS - len(short)
-    nnz = long_rows * LONG + sum(short)
+    lengths = [LONG] * long_rows
+    lengths = lengths + short if short_last else short + lengths
+    ends = [0]
+    for k in lengths:
+        ends.append(ends[-1] + k)
+    nnz = ends[-1]
     assert nnz < (1 << 31) - 1
     col = torch.empty(nnz, dtype=torch.int32, device="cuda")
     one = torch.arange(LONG, dtype=torch.int32, device="cuda")
-    col[:long_rows * LONG].view(long_rows, LONG).copy_(one)
-    at = long_rows * LONG
-    ends = [k * LONG for k in range(long_rows + 1)]
-    for s in short:
-        col[at:at + s] = one[:s]
-        at += s
-        ends.append(at)
+    at = 0 if short_last else sum(short)
+    col[at:at + long_rows * LONG].view(long_rows, LONG).copy_(one)
+    for k, end in zip(lengths, ends[1:]):
+        if k < LONG:
+            col[end - k:end] = one[:k]
     rp = torch.tensor(ends, dtype=torch.int32, device="cuda")
     return rp, col, torch.ones(nnz, dtype=torch.float32, device="cuda")
 
 
-def _x_and_sums(short):
+def _x_and_sums(short, short_last=True):
     x = (torch.arange(LONG, device="cuda") * 7 % 5 - 1).to(torch.float32)
     want = torch.full((ROWS,), float(x.double().sum()), dtype=torch.float32, device="cuda")
     for k, s in enumerate(short):
-        want[ROWS - len(short) + k] = float(x[:s].double().sum())
+        want[ROWS - len(short) + k if short_last else k] = float(x[:s].double().sum())
     return x, want
 
 
@@ -58,5 +61,22 @@ def test_batch_rows_of_unequal_length_at_the_last_entries():
     del col, val
     y = torch.full((ROWS,), -7.0, dtype=torch.float32, device="cuda")
     G.Batch([p]).run([x], [y])
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+
+
+def test_tiles_of_the_last_rows():
+    """Long rows packed into tiles, the last of them ending two entries below
+    2^31: the packing lanes step past its end."""
+    short = [127, 127, 128, 128]
+    rp, col, val = _matrix(short, short_last=False)
+    assert col.numel() == (1 << 31) - 2
+    x, want = _x_and_sums(short, short_last=False)
+    print(f"nnz {col.numel()}", flush=True)
+    p = G.Plan(rp, col, val, n=LONG, selector="csr_adaptive")
+    assert p.info()["params"]["long_lds"] == 3 and p.info()["long_rows"] == ROWS - 4
+    del col, val
+    y = torch.full((ROWS,), -7.0, dtype=torch.float32, device="cuda")
+    p.run(x, y)
     torch.cuda.synchronize()
     assert torch.equal(y, want)
