@@ -951,19 +951,9 @@ constexpr int kAloneMax = 8192;
 // | 74.
 constexpr int64_t kExpandBandColumns = 40960;
 
-// They hold up to 3 s + 4 bytes an entry where the XCD panels hold s + 4 and,
-// per row, eight row pointers and partials: where the plan's storage cap lies
-// between the two, the XCD panels are built.
 bool expand_fits(const spmv_plan_s &P, const spmv_params &prm) {
     const int G = 16 / P.elt;
     const int64_t E = expand_block_entries(P.elt), NP = expand_panels(P.n, P.elt);
-    // at most: blocks, their values and slots, and pieces (a partly filled one
-    // per block and panel) with offsets and x
-    const uint64_t nb = (uint64_t)((P.nnz + P.m) / (E - kExpandRowMax) + 1);
-    const uint64_t pieces = (uint64_t)P.nnz / G + nb * NP;
-    const uint64_t bytes = nb * E * (P.elt + 2) + pieces * (16 + 2 * G) + nb * NP * 8 +
-                           (uint64_t)P.m * 4;
-    if (bytes > P.mem_cap) return false;
     return prm.panel_xcd == 0 && prm.panel_kib == 4096 && prm.panel_direct_max <= 0 && P.m > 0 &&
            P.n > 0 && P.nnz > 0 && NP <= kExpandMaxPanels && E / G + NP <= expand_max_pieces() &&
            P.nnz + P.m < (1ll << 31) - 2 * E;
@@ -1037,6 +1027,22 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
         while (p + 1 < NP && start[p + 1] <= v0) ++p;
         chunks.push_back({(int32_t)p, (int32_t)v0, (int32_t)v1, 0});
     }
+    // The row pointers, which only a round trip reads, are kept unless the plan
+    // keeps its CSR copy for the longer rows.
+    const bool keeps_csr = V.long_tpr || V.along.first[8] > 0;
+    // The form holds 3 s + 4 bytes an entry, and up to twice that of the values
+    // and slots where long rows leave blocks part empty; the XCD panels hold s + 4
+    // and, per row, eight row pointers and partials.  Over the plan's storage cap
+    // those are built (build_variant).
+    const uint64_t held =
+        V.bytes() + sizeof(ExpandChunk) * chunks.size() + (uint64_t)pieces * (16 + 2 * G) +
+        (uint64_t)nb * E * (elt + 2) + sizeof(uint32_t) * (uint64_t)nb * (E / expand_per(elt)) +
+        sizeof(int2) * (uint64_t)nb * NP + (keeps_csr ? 0 : sizeof(int32_t) * (uint64_t)(m + 1));
+    if (held > P.mem_cap) {
+        set_error("expanded panels of %llu bytes exceed the storage cap",
+                  (unsigned long long)held);
+        return SPMV_ENOMEM;
+    }
     SMAT_TRY(V.ex_chunks.alloc(sizeof(ExpandChunk) * chunks.size()));
     if (!chunks.empty())
         SMAT_HIP(hipMemcpyAsync(V.ex_chunks.p, chunks.data(), sizeof(ExpandChunk) * chunks.size(),
@@ -1047,9 +1053,11 @@ spmv_status build_expand(const spmv_plan_s &P, const spmv_features &F, Variant &
     SMAT_TRY(V.ex_slot.alloc(sizeof(uint16_t) * (size_t)(nb * E)));
     SMAT_TRY(V.ex_val.alloc((size_t)elt * (size_t)(nb * E)));
     SMAT_TRY(V.ex_runs.alloc(sizeof(int2) * (size_t)(nb * NP)));
-    SMAT_TRY(V.ex_rp.alloc(sizeof(int32_t) * (size_t)(m + 1)));
-    SMAT_HIP(hipMemcpyAsync(V.ex_rp.p, rp, sizeof(int32_t) * (size_t)(m + 1),
-                            hipMemcpyDeviceToDevice, s));
+    if (!keeps_csr) {
+        SMAT_TRY(V.ex_rp.alloc(sizeof(int32_t) * (size_t)(m + 1)));
+        SMAT_HIP(hipMemcpyAsync(V.ex_rp.p, rp, sizeof(int32_t) * (size_t)(m + 1),
+                                hipMemcpyDeviceToDevice, s));
+    }
     SMAT_TRY(launch_expand_fill(elt, m, nb, NP, lmax, lg, rp, col, P.val.p, spos.as<int32_t>(),
                                 V.ex_blocks.as<ExpandBlock>(), runs.as<int32_t>(), stride,
                                 V.ex_off.as<uint16_t>(), V.ex_meta.as<uint32_t>(),
@@ -2688,7 +2696,8 @@ extern "C" spmv_status spmv_convert_roundtrip(spmv_plan_t P, int32_t *rp, int32_
     case SPMV_K_CSR_PANEL:
         if (V.expand) {
             // rows left to other kernels from the CSR copy they read
-            SMAT_HIP(hipMemcpyAsync(rp, V.ex_rp.p, sizeof(int32_t) * (m + 1),
+            const int32_t *from = (P->has_csr ? P->rp : V.ex_rp).as<int32_t>();
+            SMAT_HIP(hipMemcpyAsync(rp, from, sizeof(int32_t) * (m + 1),
                                     hipMemcpyDeviceToDevice, s));
             if (P->has_csr) {
                 SMAT_HIP(hipMemcpyAsync(col, P->col.p, sizeof(int32_t) * nnz,
@@ -2697,7 +2706,7 @@ extern "C" spmv_status spmv_convert_roundtrip(spmv_plan_t P, int32_t *rp, int32_
                                         hipMemcpyDeviceToDevice, s));
             }
             SMAT_TRY(launch_expand_to_csr(elt, V.ex_nb, V.ex_P, V.ex_lmax,
-                                          V.ex_rp.as<int32_t>(), V.ex_blocks.as<ExpandBlock>(),
+                                          from, V.ex_blocks.as<ExpandBlock>(),
                                           V.ex_off.as<uint16_t>(),
                                           V.ex_slot.as<uint16_t>(), V.ex_val.p,
                                           V.ex_runs.as<int2>(), col, val, s));

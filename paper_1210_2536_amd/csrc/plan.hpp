@@ -176,7 +176,6 @@ struct spmv_plan_s {
     bool has_csr = false;
     std::unique_ptr<smat::Variant> var; // the chosen kernel's state
     spmv_plan_info info{};
-    smat::Dev diag_map;                 // diagonal -> slot map (kept only while converting)
     std::vector<int32_t> dia_offsets;
     // segmented plans: one plan per row segment, in row order
     std::vector<spmv_plan_s *> seg;
