@@ -1389,6 +1389,9 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
             break;
         }
         V.prm.long_lds = ll;
+        // the thresholds in effect where the two-step form lowers them
+        if (expand && ll == 3) V.prm.tile_row_min = wg;
+        if (expand && ll != 3) V.prm.adaptive_wg_min = wg_plain;
         V.bin_scratch.release();
         if (!panels) {
             // the launch's rows (bins 0-6 when the long rows left it, else
@@ -1748,12 +1751,24 @@ std::vector<spmv_params> tune_grid(int kernel, const spmv_params &b, const spmv_
             }
         break;
     case SPMV_K_CSR_PANEL: {
+        // (the two-step form records a lower threshold of its own)
+        const int wg = default_params(kernel, F).adaptive_wg_min;
+        if (b.panel_xcd == 0)   // two steps: caching and long rows
+            for (int nt : nts)
+                for (int ll : {1, 2, 3}) {
+                    if (ll == 1 && dtype != SPMV_F64) continue;
+                    spmv_params p = b;
+                    p.stream_nt = nt;
+                    p.long_lds = ll;
+                    add(p);
+                }
         std::vector<std::pair<int, int>> seen;  // (mode, P): kib values giving equal panels
         for (int mode : {1, 2})  // 1: eight panels at a time, one launch; 2: sequential
             for (int kib : {1024, 2048, 4096}) {
                 spmv_params p = b;
                 p.panel_xcd = mode;
                 p.panel_kib = kib;
+                p.adaptive_wg_min = wg;
                 int64_t w;
                 int P;
                 panel_geometry(F, dtype == SPMV_F64 ? 8 : 4, p, &w, &P);
@@ -1775,13 +1790,15 @@ std::vector<spmv_params> tune_grid(int kernel, const spmv_params &b, const spmv_
         for (int d : {-1, 4, 16, 64}) {
             spmv_params p = b;
             p.panel_direct_max = d;
+            p.adaptive_wg_min = wg;
             add(p);
         }
         for (int r : {256, 1024, 4096, 16384}) {
+            if (b.panel_xcd == 0 && r > kTileRowMinMax) continue;
             spmv_params p = b;
             p.long_lds = 3;
             p.tile_row_min = r;
-            p.adaptive_wg_min = std::max(b.adaptive_wg_min, r);
+            p.adaptive_wg_min = std::max(wg, r);
             add(p);
         }
         break;
