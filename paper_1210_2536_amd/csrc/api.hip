@@ -138,7 +138,7 @@ namespace {
 struct FeatureWork {
     Dev scratch;   // RowStats + EntryStats + DiagStats + flags + fit sums
     Dev row_hist;
-    Dev diag_hist; // m + n - 1 bins; later the diagonal -> slot map
+    Dev diag_hist; // m + n - 1 bins
     Dev diag_maps; // bitmap census (none in allocation-free mode)
     bool census = false;       // the census was taken (DIA could be feasible)
     bool census_done = false;  // the census question is settled
@@ -1140,7 +1140,7 @@ spmv_status build_kernel(spmv_plan_s &P, const spmv_features &F, FeatureWork &W,
         V.D = (int)F.ndiags;
         SMAT_TRY(V.dia_off.alloc(sizeof(int32_t) * std::max(1, V.D)));
         if (P.dia_offsets.empty() && V.D > 0) {
-            // compact the census into ascending offsets; bins become slot ids
+            // compact the census into ascending offsets
             int64_t nbins = m + n - 1;
             int64_t nblk = (nbins + 4095) / 4096;
             Dev blk;

@@ -637,8 +637,8 @@ __global__ void k_scan_single(unsigned int *v, int64_t count) {
     }
 }
 
-// Write ascending offsets and turn each occupied histogram bin into its slot.
-__global__ void k_diag_write(int64_t m, int64_t nbins, unsigned int *hist,
+// Write the offsets of the occupied histogram bins, ascending.
+__global__ void k_diag_write(int64_t m, int64_t nbins, const unsigned int *__restrict__ hist,
                              const unsigned int *__restrict__ block_base, int32_t *offsets) {
     __shared__ unsigned int part[kBlock];
     int64_t base = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * kCompactPer;
@@ -658,7 +658,6 @@ __global__ void k_diag_write(int64_t m, int64_t nbins, unsigned int *hist,
         int64_t b = base + q;
         if (b < nbins && hist[b]) {
             offsets[slot] = (int32_t)(b - (m - 1));
-            hist[b] = slot;
             ++slot;
         }
     }
