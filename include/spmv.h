@@ -28,7 +28,8 @@
  *     caller's next synchronisation.
  *   - Thread safety: distinct plans may be used from distinct threads; one
  *     plan must not run on two streams at the same time (its COO carries,
- *     split-row partials and panel partial sums are per-plan scratch).
+ *     split-row and long-row partials, panel partial sums and the expanded x
+ *     of the two-step panels are per-plan scratch).
  */
 #ifndef SMAT_SPMV_H
 #define SMAT_SPMV_H
@@ -122,10 +123,14 @@ typedef struct {
     int32_t panel_xcd;          /* CSR_PANEL: 0 = default: two steps -- x
                                    expanded panel by panel out of LDS, then
                                    blocks of rows summed out of LDS -- unless
-                                   panel_kib or panel_direct_max is given or
-                                   the matrix is beyond that form's indices
+                                   panel_kib other than 4096 or
+                                   panel_direct_max above 0 is given, the
+                                   matrix is beyond that form's indices
                                    (n above about 20 million float32 or 10
-                                   million float64), then as 1;
+                                   million float64), its storage exceeds the
+                                   cap, its columns lie in a narrow band, or a
+                                   row of more than 8192 entries does not go
+                                   to tiles; then as 1;
                                    1 = all panels in one launch,
                                    eight at a time, one per XCD, each panel
                                    summing into its own partial vector that a
@@ -142,8 +147,9 @@ typedef struct {
                                    in [1, 64]; at least the lanes of a block
                                    (16 bytes each: float32 4, float64 8).
                                    0 = default: about 2 lanes per block of
-                                   a mean block row, widened in float64 as
-                                   the 1e-12 bound needs                   */
+                                   a mean block row in float64, 1 in float32,
+                                   widened in float64 as the 1e-12 bound
+                                   needs                                   */
     int32_t long_lds;           /* CSR_ADAPTIVE and CSR_PANEL: where the
                                    rows of the longest bin (a workgroup each
                                    in the binned launch) go.  1 = x chunks
@@ -161,7 +167,10 @@ typedef struct {
                                    partials added in a fixed order in the
                                    launch that follows; 2 = binned launch;
                                    0 = default (tiles from 10 MB of values
-                                   in such rows, else 2).  Tiles
+                                   in such rows, unless their columns lie in
+                                   a band and the rows are short or few; for
+                                   two-step panels also when a row has more
+                                   than 8192 entries; else 2).  Tiles
                                    fall back to chunks
                                    (float64) or 2 where their partials
                                    would exceed 1/5 of the
@@ -175,7 +184,10 @@ typedef struct {
                                    entries go to the tiles (at least 64;
                                    0 = default: by the panel count, 256 to
                                    4096, doubled while the partials would
-                                   cost too much)                          */
+                                   cost too much).  Two-step panels take rows
+                                   of at most 4096 entries into their blocks
+                                   (1024 without tiles) and record the lower
+                                   threshold here and in adaptive_wg_min   */
     int32_t panel_direct_max;   /* CSR_PANEL: rows of at most this many
                                    entries (rounded down to a length-bin
                                    boundary) skip the column panels -- no
@@ -227,7 +239,11 @@ typedef struct {
     uint32_t disable_mask;      /* bit k set: never pick kernel k             */
     uint64_t mem_cap_bytes;     /* cap on the storage of the padded formats
                                    (ELL, DIA, BCSR) and column panels; 0 =
-                                   1/4 of free device memory                */
+                                   1/4 of free device memory.  Scratch that
+                                   planning gives back (histograms, up to 80
+                                   MB of census bitmaps, which it does
+                                   without where they cannot be had) is not
+                                   counted                                  */
     spmv_selector_t model;      /* learned model (NULL: rules)                */
     int32_t autotune;           /* 1: time a few parameter points for the
                                    chosen kernel and keep the fastest (the

@@ -14,12 +14,13 @@ namespace smat {
 constexpr int kWave = 64;           // gfx9 wavefront width
 constexpr int kDiaLaneRows = 4;     // rows of a lane of a DIA tile with 16-byte loads
 // DIA and ELL plans of more matrix bytes stream from HBM (the 256 MB Infinity
-// Cache does not keep them next to x and y until the next run): the direct DIA
-// kernel takes diagonals by groups, and both store y past the caches, where it
-// would displace x, which every diagonal or slot reads.  Measured, DIA direct
-// in cached stores | this (us): 7-point 256^3 float64 218 | 195, float32 114 |
-// 93, 160^3 float64 54 | 52, 130^3 (123 MB) 32.7 | 28.0; below the line 160^3
-// float32 (115 MB) 28.6 | 29.3.
+// Cache does not keep them next to x and y until the next run): under wide loads
+// the direct DIA kernel takes diagonals by groups, and both store y past the
+// caches, where it would displace x, which every diagonal or slot reads (plans
+// this large take wide loads unless told not to; narrow ones store y as ever).
+// Measured, DIA direct in cached stores | this (us): 7-point 256^3 float64 218 |
+// 195, float32 114 | 93, 160^3 float64 54 | 52, 130^3 (123 MB) 32.7 | 28.0; below
+// the line 160^3 float32 (115 MB) 28.6 | 29.3.
 constexpr uint64_t kHbmBytes = uint64_t(120) << 20;
 constexpr int kRowPad = 64;         // ELL / DIA slot stride is m rounded up to this
 constexpr int kFp64MaxDepth = 4096; // longest sequential float64 summation chain

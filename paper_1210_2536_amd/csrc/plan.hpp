@@ -122,7 +122,7 @@ struct Variant {
     int long_tpr = 0;
     int64_t n_long = 0;
     AdaptiveLaunch arest{};
-    Dev long_rows;   // the long rows, longest first
+    Dev long_rows;   // the long rows (x chunks: longest first)
     // long rows by tiles (x panel per workgroup) instead of x chunks
     bool long_tiles = false, tile_nt = false;
     int64_t tile_P = 0, tile_nb = 0;
