@@ -761,13 +761,24 @@ int rules_choose(const spmv_features &F, uint32_t feas) {
 // Kernels a staged search may settle on before the rest stage (DIA, ELL and
 // CSR come before COO in the search order; BCSR's feasibility needs the
 // block count) and the selector inputs known by then (all but R, 8, and the
-// block fill, 10).
+// block fill, 10).  A caller's rule may name column panels, as the interface
+// says; the shipped one leaves them to the network, since rows of dense blocks
+// look like rows of random columns until their blocks are counted.
 constexpr uint32_t kStageKernels =
     (1u << SPMV_K_CSR_SCALAR) | (1u << SPMV_K_CSR_VECTOR) | (1u << SPMV_K_CSR_ADAPTIVE) |
     (1u << SPMV_K_CSR_PANEL) | (1u << SPMV_K_ELL) | (1u << SPMV_K_DIA) | (1u << SPMV_K_DIA_DIRECT);
 constexpr uint32_t kStageInputs = 0xFFFu & ~((1u << 8) | (1u << 10));
 // ... and those known before the census (all but Ndiags, 5, and the DIA fill, 6)
 constexpr uint32_t kRowInputs = kStageInputs & ~((1u << 5) | (1u << 6));
+
+// Rows of 4x4 blocks more than half full: BCSR reads 2 s + 1/2 bytes an entry at
+// most and asks for x once in 8 entries, where the two steps move 3 s + 4 and
+// more.  The network, which knows such float32 matrices only where x is too
+// small for column panels, ranked panels first beyond: 702k rows of 5 blocks
+// 55 us, BCSR 18, ELL 31; 600k of 4 blocks 39, 11 and 23.  Among 10,000 timed
+// matrices, panels took 2.6 times the best kernel's time or more wherever
+// blocks were over 0.15 full.
+constexpr double kPanelBlockFill = 0.5;
 
 // Leaf of the selector's stage rule reached by these inputs (node 0 is the
 // root; every child index exceeds its parent's, so the walk ends).
@@ -2449,6 +2460,10 @@ static spmv_status plan_create_impl(const spmv_csr *A, const spmv_plan_opts *opt
             if ((feas >> k) & 1u) order.push_back({sc[k], k});
         }
         std::sort(order.begin(), order.end());
+        if (F.block_fill > kPanelBlockFill)   // no longer a choice on scores alone
+            std::stable_partition(order.begin(), order.end(), [](const auto &o) {
+                return o.second != SPMV_K_CSR_PANEL;
+            });
         bool outside = false;
         if (sel->has_domain)
             for (int j = 0; j < 12; ++j)
