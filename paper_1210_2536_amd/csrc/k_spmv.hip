@@ -713,8 +713,9 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_ranks(const int32_t *__re
 // lane: four blocks are in flight now.  float32 lanes used to hold whole blocks
 // (64 bytes a lane, 64 lines a load).
 // Measured, blocks from HBM (before | now, MI355X): 400k rows of 16 blocks
-// float64 54.4 | 44.7 us (4.9 TB/s), float32 29.0 | 27.1; 100k rows 15.4 | 12.6
-// and 9.5 | 8.9; 400k rows of 4 blocks 16.0 | 14.5 and 10.2 | 9.7.
+// float64 54.4 | 44.7 us (4.9 TB/s), 100k rows 15.4 | 12.6, 400k rows of 4 blocks
+// 16.0 | 14.5; float32 (three to nine matrices in turn, default lanes) 31.4 | 29.3,
+// 8.5 | 8.1 and 9.8 | 9.4.
 // A blocks in flight; one matrix from the Infinity Cache, float64, 8 lanes, A = 1
 // | 4 | default lanes, A = 4: 200k rows of 16 blocks 18.8 | 20.5 | 19.9 us, of 32
 // blocks 34.0 | 38.7 | 35.7, 400k rows of 16 40.1 | 44.7 | 44.8.
